@@ -14,8 +14,8 @@
 // between the two half-waves, and the exponentiated scores are already laid out as
 // the B operand of the second product (they never leave registers).  The second
 // product contracts over keys; V stays row-major in LDS and its operand is fetched with
-// the transposing LDS read (ds_read_b64_tr_b16).  K/V tiles are streamed through a 3-stage
-// LDS ring by direct global->LDS loads.
+// the transposing LDS read (ds_read_b64_tr_b16).  K/V tiles are streamed through 4-stage
+// LDS rings by direct global->LDS loads.
 //
 // float kernel: one wavefront per (row, query head), 64 keys per step, plain FMA.
 #include "common.h"
@@ -29,13 +29,58 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegBig = -1.0e30f;
 
 // ---------------------------------------------------------------------------
-constexpr int BKV = 64;                 // keys per tile
-constexpr int ATT_S = 3;                // LDS ring stages (K tile + V tile each)
+constexpr int BKV = 64;                 // keys per tile, walked as two sub-tiles of 32
+constexpr int ATT_S = 4;                // LDS ring stages of the K ring and of the V ring
+constexpr int ATT_NW = 8;               // wavefronts per workgroup: two per SIMD
+constexpr int ATT_WGQ = 32 * ATT_NW;    // flattened queries per workgroup
+constexpr float kLazyMax = 8.f;         // a running maximum may lag behind by a factor 2^8 (see below)
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
-template <int DH, int NQB, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_bf16_kernel(const bf16 *__restrict__ q,
+// LDS reads issued by hand: the compiler waits for every outstanding global->LDS load before a transposing read
+// (it cannot see that the tile being read landed long ago), which would undo the ring.  The results are valid
+// only after att_wait<N>() with at most N younger reads in flight.
+template <int OFF> __device__ __forceinline__ void att_read_k(bf16x8 &dst, unsigned addr) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF));
+}
+template <int OFF> __device__ __forceinline__ void att_read_v(s16x4 &dst, unsigned addr) {
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF));
+}
+template <int N> __device__ __forceinline__ void att_wait() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N)); }
+template <int N> __device__ __forceinline__ void att_vm_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// maximum over the wavefront / over the two half-waves without LDS (the shuffles would count as LDS reads)
+__device__ __forceinline__ float half_swap_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ int wave_max_i32(int v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
+  return v;
+}
+
+template <int V> struct IntC { static constexpr int value = V; };
+
+// What bounds it and how the loop is laid out.  Per 64 keys a wavefront issues 4 DH/16 MFMAs of 32 clocks each for
+// its 32 queries, and two wavefronts share a SIMD, so the matrix core needs 2048 clocks per tile at DH = 128; the
+// operand reads of the 8 wavefronts take about 1340 clocks of LDS, the softmax about 110 vector and 32 transcendental
+// instructions per wavefront.  All three fit side by side if the instruction streams are mixed, so the loop is
+// software-pipelined by hand: a PHASE handles a sub-tile of 32 keys j and interleaves, MFMA by MFMA,
+//     S(j+1) = K(j+1) Q^T        softmax of S(j)        O += V(j-1) P(j-1)
+// none of which depends on another.  Operand reads run two steps ahead (a step = one MFMA of each product).
+// The running maximum is updated lazily: exponents are taken relative to a reference that only moves when a score
+// exceeds it by 2^8, so the accumulators are almost never rescaled (P is bf16 and the sums are float: a common factor
+// costs no precision); a rescale is applied at the end of the phase, after O has taken P(j-1), which was
+// computed relative to the old reference.
+//   K ring, V ring: 4 stages each.  In iteration t (tile t) the phases read K(t), K(t+1) and V(t-1), V(t); the loads of
+//   K(t+3) and V(t+2) are issued, and the barrier at its start waits for the loads of iteration t-2.
+// Measured (32 query heads over 8 kv heads): dense 16 K x 16 K 2233 -> 1940 us (1135 TFLOP/s), 3000 rows over 20.7 K
+// tokens 644 -> 537 us, 500 rows over 3136 tokens 46 -> 40 us with the merge; a tile takes 1.42 us on an otherwise idle
+// chip (1.99 before) and 1.87 us with every CU busy, where power sets the clock.  The same loop on 16x16x32 MFMAs
+// measured 1.59 / 1.82 us, four wavefronts of 64 queries (half the LDS reads) did not fit the register file.
+template <int DH>
+__global__ __launch_bounds__(64 * ATT_NW) void attn_bf16_kernel(const bf16 *__restrict__ q,
                                                         const int32_t *__restrict__ q_pos, int n_rows,
                                                         const bf16 *__restrict__ kc,
                                                         const bf16 *__restrict__ vc, bf16 *__restrict__ o,
@@ -47,20 +92,19 @@ __global__ __launch_bounds__(64 * NW) void attn_bf16_kernel(const bf16 *__restri
                                                         const int32_t *__restrict__ segs, int n_segs) {
   // K and V tiles sit row-major in LDS ([key][channel], no padding) and are filled by direct
   // global->LDS loads: one wavefront-wide 16-byte load writes 1 KB = RPI whole rows.  Instead of
-  // padding, the 16-byte chunk c of row r is stored in slot c ^ f(r), which makes both the
-  // 16-byte K operand reads and the transposing 8-byte V reads conflict-free.
+  // padding, the 16-byte chunk c of row r is stored in slot c ^ f(r).
   constexpr int ROWB = DH * 2;            // bytes per row
   constexpr int CH = DH / 8;              // 16-byte chunks per row
   constexpr int RPI = 1024 / ROWB;        // rows per wavefront-wide load
   constexpr int TILEB = BKV * ROWB;       // bytes of one K (or V) tile
-  constexpr int STAGE = 2 * TILEB;
-  constexpr int LPT = 2 * (BKV / RPI) / NW; // loads per lane per tile (K and V, NW wavefronts)
-  constexpr int WGQ = 32 * NQB * NW;        // flattened queries per workgroup
-  constexpr int KS = DH / 16;             // k-steps of the first product
+  constexpr int LPT = BKV / RPI / ATT_NW; // loads per lane per K tile (and per V tile)
+  constexpr int NST = DH / 16;            // steps per phase: k-steps of S^T, and (16-key group, 32-channel block) pairs of O^T
   constexpr int DB = DH / 32;             // 32-channel blocks of the output
+  static_assert(LPT >= 1 && NST == 2 * DB && NST % 4 == 0, "step and buffer bookkeeping");
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ln = lane & 31, h = lane >> 5;
   const int g = n_q_heads / n_kv_heads;
   const int kvh = blockIdx.x;                          // kv head varies fastest in dispatch order
@@ -87,23 +131,30 @@ __global__ __launch_bounds__(64 * NW) void attn_bf16_kernel(const bf16 *__restri
     if (q_rows) q_rows += row0;
   }
   const int n_flat = n_rows * g;
-  const int m_wg = (qwg - seg_qwg0) * WGQ;             // first flattened query of the workgroup, within its request
-  const int m_pad = qwg * WGQ;                         // the same in the launch-wide numbering of the scratch
-  const int n_flat_pad = (int)gridDim.y * WGQ;
+  const int m_wg = (qwg - seg_qwg0) * ATT_WGQ;         // first flattened query of the workgroup, within its request
+  const int m_pad = qwg * ATT_WGQ;                     // the same in the launch-wide numbering of the scratch
+  const int n_flat_pad = (int)gridDim.y * ATT_WGQ;
 
-  // causal bound of the workgroup = largest position among its rows (they need not be sorted)
-  __shared__ int s_max_pos;
-  if (tid == 0) s_max_pos = -1;
-  __syncthreads();
+  // this lane's query (the loads overlap the search for the causal bound below)
+  const int m_own = m_wg + wave * 32 + ln;
+  const bool valid = m_own < n_flat;
+  const int r_own = (valid ? m_own : n_flat - 1) / g, j_own = (valid ? m_own : n_flat - 1) - r_own * g;
+  const int my_pos = valid ? q_pos[r_own] : -1;
+  const long q_off = ((long)(row0 + r_own) * n_q_heads + kvh * g + j_own) * DH;
+  bf16x8 qf[NST];
   {
-    const int last_m = min(m_wg + WGQ, n_flat) - 1;
-    int mp = -1;
-    for (int r = m_wg / g + tid; r <= last_m / g; r += 64 * NW) mp = max(mp, q_pos[r]);
-    mp = (int)wave_max((float)mp);                     // positions < 2^24: exact in float
-    if (lane == 0 && mp >= 0) atomicMax(&s_max_pos, mp);
+    const long q_src = ((long)(q_rows ? q_rows[r_own] : row0 + r_own) * n_q_heads + kvh * g + j_own) * DH;
+#pragma unroll
+    for (int ks = 0; ks < NST; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(q + q_src + ks * 16 + 8 * h);
   }
-  __syncthreads();
-  const int kv_len = s_max_pos + 1;
+  // causal bound of the workgroup = largest position among its rows (they need not be sorted); every wavefront
+  // looks at all of them, which needs no exchange
+  int max_pos = -1;
+  {
+    const int last_r = (min(m_wg + ATT_WGQ, n_flat) - 1) / g;
+    for (int r = m_wg / g + lane; r <= last_r; r += 64) max_pos = max(max_pos, q_pos[r]);
+  }
+  const int kv_len = __builtin_amdgcn_readfirstlane(wave_max_i32(max_pos)) + 1;
   const int n_tiles_all = (kv_len + BKV - 1) / BKV;
   // the merge launch needs the same bound to know which pieces of the key range ran
   if (gridDim.z > 1 && kvh == 0 && blockIdx.z == 0 && tid == 0) wg_tiles[qwg] = n_tiles_all;
@@ -112,85 +163,57 @@ __global__ __launch_bounds__(64 * NW) void attn_bf16_kernel(const bf16 *__restri
   const int t_begin = blockIdx.z * split_tiles;
   if (t_begin >= n_tiles_all) return;
   const int n_tiles = min(n_tiles_all, t_begin + split_tiles);
+  const int wave_max_pos = __builtin_amdgcn_readfirstlane(wave_max_i32(my_pos));
+  const int wave_min_pos = -__builtin_amdgcn_readfirstlane(wave_max_i32(-my_pos));   // invalid queries (-1) force masking
+  const int t_last = min(n_tiles - 1, wave_max_pos >> 6);   // last tile this wavefront computes on (may be < t_begin)
 
-  // this lane's queries
-  int my_pos[NQB];
-  long q_off[NQB];
-  bool valid[NQB];
-  bf16x8 qf[NQB][KS];
-  int wave_max_pos = -1, wave_min_pos = 0x7fffffff;
-#pragma unroll
-  for (int b = 0; b < NQB; ++b) {
-    const int m = m_wg + (wave * NQB + b) * 32 + ln;
-    valid[b] = m < n_flat;
-    const int mm = valid[b] ? m : n_flat - 1;
-    const int r = mm / g, j = mm - r * g;
-    my_pos[b] = valid[b] ? q_pos[r] : -1;
-    q_off[b] = ((long)(row0 + r) * n_q_heads + kvh * g + j) * DH;
-    const long q_src = ((long)(q_rows ? q_rows[r] : row0 + r) * n_q_heads + kvh * g + j) * DH;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      qf[b][ks] = *reinterpret_cast<const bf16x8 *>(q + q_src + ks * 16 + 8 * h);
-    wave_max_pos = max(wave_max_pos, my_pos[b]);
-    wave_min_pos = min(wave_min_pos, my_pos[b]);       // invalid queries (-1) force masking
-  }
-  wave_max_pos = (int)wave_max((float)wave_max_pos);  // positions < 2^24: exact in float
-  wave_min_pos = -(int)wave_max((float)(-wave_min_pos));
-
-  f32x16 oacc[NQB][DB];
-  float row_max[NQB], row_sum[NQB];
-#pragma unroll
-  for (int b = 0; b < NQB; ++b) {
-    row_max[b] = -INFINITY;
-    row_sum[b] = 0.f;
-#pragma unroll
-    for (int d = 0; d < DB; ++d)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) oacc[b][d][i] = 0.f;
-  }
-
-  // swizzle: DH = 128 rows start at bank 0 -> 16 slots, f(r) = r & 15; DH = 64 rows alternate
-  // between the two bank halves -> 8 slots, f(r) = (r >> 1) & 7
-  auto fswz = [](int r) { return DH == 128 ? (r & 15) : ((r >> 1) & 7); };
+  // Swizzles f(r).  K is read 16 bytes per lane, 32 rows at a time: DH = 128 rows start at bank 0 -> f = r & 15;
+  // DH = 64 rows alternate between the two bank halves -> f = (r >> 1) & 7.  V goes through the transposing
+  // 8-byte read, 16 lanes of which take 32 bytes of each of 4 adjacent keys: those 4 keys have to lie in different
+  // 64-byte groups (f = 4 (r & 3) + ...), else they conflict: 190 against 63 bytes per clock and CU with f = r & 15.
+  auto fk = [](int r) { return DH == 128 ? (r & 15) : ((r >> 1) & 7); };
+  auto fv = [](int r) { return DH == 128 ? (((r & 3) << 2) | ((r >> 2) & 3)) : ((((r >> 1) & 1) << 2) | ((r >> 2) & 3)); };
 
   // ---- global -> LDS: this lane's share of the loads of one tile ----
-  int ld_row[LPT], ld_col[LPT];           // tile row, element offset of the (de-swizzled) chunk
-  bool ld_v[LPT];
+  const unsigned row_bytes = (unsigned)kv_dim * 2;
+  int ld_row[LPT];                        // tile row of load i; K and V loads use the same rows
+  unsigned ld_kcol[LPT], ld_vcol[LPT];    // byte offset of the (de-swizzled) chunk
 #pragma unroll
   for (int i = 0; i < LPT; ++i) {
-    const int gi = wave + NW * i;                      // load group: first K groups, then V groups
-    ld_v[i] = gi >= BKV / RPI;
-    const int gl = ld_v[i] ? gi - BKV / RPI : gi;
-    ld_row[i] = gl * RPI + lane / CH;
-    ld_col[i] = ((lane % CH) ^ fswz(ld_row[i])) * 8 + kvh * DH;
+    ld_row[i] = (wave + ATT_NW * i) * RPI + lane / CH;
+    ld_kcol[i] = (unsigned)((((lane % CH) ^ fk(ld_row[i])) * 8 + kvh * DH) * 2);
+    ld_vcol[i] = (unsigned)((((lane % CH) ^ fv(ld_row[i])) * 8 + kvh * DH) * 2);
   }
-  const bf16 *ld_base[LPT];
-#pragma unroll
-  for (int i = 0; i < LPT; ++i) ld_base[i] = (ld_v[i] ? vc : kc) + (size_t)ld_row[i] * kv_dim + ld_col[i];
-  auto issue = [&](int t) {
-    const int t0 = min(t, n_tiles_all - 1) * BKV;     // clamped: every call issues LPT loads
-    char *stage = smem + (t % ATT_S) * STAGE;
-    const bool whole = t0 + BKV <= kv_len;             // uniform: no row of the tile is past the bound
-    const size_t adv = (size_t)t0 * kv_dim;
-#pragma unroll
-    for (int i = 0; i < LPT; ++i) {
-      const bf16 *src = ld_base[i] + adv;
-      if (!whole) {
-        const int row = min(t0 + ld_row[i], kv_len - 1);
-        src = (ld_v[i] ? vc : kc) + (size_t)row * kv_dim + ld_col[i];
-      }
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                       (__attribute__((address_space(3))) void *)(stage + (wave + NW * i) * 1024),
-                                       16, 0, 0);
-    }
+  const unsigned lds0 = (unsigned)(size_t)smem;
+  // one load of tile t (clamped to the last tile, rows clamped to the causal bound: every call issues its load)
+  auto issue = [&](int t, int i, bool is_v) {
+    const int t0 = min(t, n_tiles_all - 1) * BKV;
+    const char *base = reinterpret_cast<const char *>(is_v ? vc : kc) + (size_t)t0 * row_bytes;
+    const unsigned row = (unsigned)min(ld_row[i], kv_len - 1 - t0);
+    const char *src = base + (size_t)(row * row_bytes + (is_v ? ld_vcol[i] : ld_kcol[i]));
+    char *dst = smem + (is_v ? ATT_S * TILEB : 0) + (t & (ATT_S - 1)) * TILEB + (wave + ATT_NW * i) * 1024;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
   };
-  // ---- LDS read offsets of this lane ----
-  int k_off[KS];                                       // K operand: row ln (+32 kb), chunk 2 ks + h
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) k_off[ks] = ln * ROWB + (((2 * ks + h) ^ fswz(ln)) << 4);
+  for (int i = 0; i < LPT; ++i) issue(t_begin, i, false);
+#pragma unroll
+  for (int i = 0; i < LPT; ++i) issue(t_begin, i, true);
+#pragma unroll
+  for (int i = 0; i < LPT; ++i) issue(t_begin + 1, i, false);
+#pragma unroll
+  for (int i = 0; i < LPT; ++i) issue(t_begin + 1, i, true);
+#pragma unroll
+  for (int i = 0; i < LPT; ++i) issue(t_begin + 2, i, false);
+
+  // ---- LDS read addresses of this lane, kept for the tile being read and moved from stage to stage ----
+  unsigned k_addr[NST], v_addr[DB][2];
+#pragma unroll
+  for (int ks = 0; ks < NST; ++ks)        // K operand: row ln (+ 32 for the second sub-tile), chunk 2 ks + h
+    k_addr[ks] = lds0 + (t_begin & (ATT_S - 1)) * TILEB + ln * ROWB + (((2 * ks + h) ^ fk(ln)) << 4);
   // V operand through the transposing read: lane s of a 16-lane block passes the address of
-  // 4 channels (8 bytes) of key K0 + s/4 and receives, for channel C0 + s, the 4 keys K0..K0+3
-  int v_off[DB][2];
+  // 4 channels (8 bytes) of key K0 + s/4 and receives, for channel C0 + s, the 4 keys K0..K0+3.
+  // Starts one stage back: the first phase's read moves it to tile t_begin (there is no V(t_begin - 1) to read).
   {
     const int s16 = lane & 15, qb = lane >> 4;
 #pragma unroll
@@ -199,151 +222,250 @@ __global__ __launch_bounds__(64 * NW) void attn_bf16_kernel(const bf16 *__restri
       for (int a = 0; a < 2; ++a) {
         const int key = 8 * a + 4 * (qb >> 1) + (s16 >> 2);               // + 16 u per MFMA
         const int ch = d * 32 + 16 * (qb & 1) + 4 * (s16 & 3);
-        v_off[d][a] = TILEB + key * ROWB + (((ch >> 3) ^ fswz(key)) << 4) + (ch & 7) * 2;
+        v_addr[d][a] = lds0 + ATT_S * TILEB + (t_begin & (ATT_S - 1)) * TILEB + key * ROWB + (((ch >> 3) ^ fv(key)) << 4) + (ch & 7) * 2;
       }
   }
 
+  f32x16 oacc[DB], sacc[2];
+  union PF { unsigned w[4]; bf16x8 b; } pf[2][2];   // P of the sub-tile before and of the one in work, two 16-key groups each
+  float ref = -INFINITY, thr = -INFINITY, neg_mc = 0.f, row_sum = 0.f;
+  const float lazy = kLazyMax / scale_log2e;
 #pragma unroll
-  for (int sI = 0; sI < ATT_S - 1; ++sI) issue(t_begin + sI);
-  for (int t = t_begin; t < n_tiles; ++t) {
-    const int t0 = t * BKV;
-    __builtin_amdgcn_s_waitcnt(((ATT_S - 2) * LPT) | (7 << 4) | (0 << 8));   // tile t landed; my LDS reads done
-    asm volatile("s_barrier" ::: "memory");
-    issue(t + ATT_S - 1);
-    if (t0 <= wave_max_pos) {  // wave-uniform: tiles wholly in this wave's future are skipped
-      const char *ck = smem + (t % ATT_S) * STAGE;
-      // ---- S^T = K Q^T ----
-      f32x16 sacc[NQB][2];
+  for (int d = 0; d < DB; ++d)
 #pragma unroll
-      for (int b = 0; b < NQB; ++b)
+    for (int i = 0; i < 16; ++i) oacc[d][i] = 0.f;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) sacc[b][kb][i] = 0.f;
-      {
-        // K operand reads run two steps ahead of the MFMAs that use them (step = (ks, kb))
-        constexpr int NSTEP = 2 * KS;
-        bf16x8 kf[3];
-        kf[0] = *reinterpret_cast<const bf16x8 *>(ck + k_off[0]);
-        kf[1] = *reinterpret_cast<const bf16x8 *>(ck + 32 * ROWB + k_off[0]);
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int st = 0; st < NSTEP; ++st) {
-          if (st + 2 < NSTEP)
-            kf[(st + 2) % 3] = *reinterpret_cast<const bf16x8 *>(ck + ((st + 2) & 1) * 32 * ROWB + k_off[(st + 2) >> 1]);
+      for (int e = 0; e < 4; ++e) pf[a][u].w[e] = 0u;
+
+  bf16x8 kf[4];
+  union VF { s16x4 s[2]; bf16x8 b; } vf[4];
+  // Requests step I of a phase: the K fragment (WK) of k-step I and the V fragment (two transposing reads, WV) of
+  // (16-key group I / DB, channel block I % DB).  ODD: the phase works on S of the first half of the next K
+  // tile and on the first half of the V tile after the one the addresses point at, so its reads move the
+  // addresses on (by dk / dv bytes; dv also serves the first phase, which rereads V(t_begin) against P = 0).
+  auto read_step = [&](auto odd_, auto wk_, auto wv_, auto i_, int dk, int dv) {
+    constexpr int ODD = decltype(odd_)::value, I = decltype(i_)::value, D = I % DB, U = I / DB;
+    if constexpr (decltype(wk_)::value) {
+      if constexpr (ODD) k_addr[I] += dk;
+      att_read_k<(ODD ? 0 : 32 * ROWB)>(kf[I & 3], k_addr[I]);
+    }
+    if constexpr (decltype(wv_)::value) {
+      if constexpr (ODD && U == 0) { v_addr[D][0] += dv; v_addr[D][1] += dv; }
+      att_read_v<((ODD ? 0 : 2) + U) * 16 * ROWB>(vf[I & 3].s[0], v_addr[D][0]);
+      att_read_v<((ODD ? 0 : 2) + U) * 16 * ROWB>(vf[I & 3].s[1], v_addr[D][1]);
+    }
+  };
+
+  // One phase: softmax of sub-tile j = 2t + ODD (SM), S of sub-tile j+1 (WS), O += V P of sub-tile j-1.
+  // NS / NX: whether the phase that follows computes S / exists (its first two steps are requested here).
+  auto phase = [&](auto odd_, auto sm_, auto ws_, auto ns_, auto nx_, int t, int dk, int dv) {
+    constexpr int ODD = decltype(odd_)::value, SM = decltype(sm_)::value, WS = decltype(ws_)::value;
+    constexpr int NS = decltype(ns_)::value, NX = decltype(nx_)::value;
+    f32x16 &sc = sacc[ODD], &sn = sacc[1 - ODD];
+    PF (&pc)[2] = pf[ODD], (&pp)[2] = pf[1 - ODD];
+    bool moved = false;
+    float alpha = 1.f, mx = -INFINITY, psum = 0.f;
+    float e[16];
+    if constexpr (SM) {
+      const int s0 = t * BKV + ODD * 32;
+      if (s0 + 31 > wave_min_pos) {                    // wave-uniform: some key of the sub-tile is masked
 #pragma unroll
-          for (int b = 0; b < NQB; ++b)
-            sacc[b][st & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st % 3], qf[b][st >> 1], sacc[b][st & 1], 0, 0, 0);
+        for (int i = 0; i < 16; ++i) {
+          const int key = s0 + (i >> 2) * 8 + h * 4 + (i & 3);
+          sc[i] = key <= my_pos ? sc[i] : -INFINITY;
         }
       }
-      // ---- online softmax (per lane = per query), in the raw score domain: p = 2^((s - m) c) ----
-      bf16x8 pf[NQB][4];
-      const bool diag = t0 + BKV - 1 > wave_min_pos;     // wave-uniform: some key of the tile is masked
+    }
+    auto fold = [&](int i) {                           // pair i: into the sum, and to bf16
+      psum += e[2 * i];
+      psum += e[2 * i + 1];
+      const bf16x2 w = {(bf16)e[2 * i], (bf16)e[2 * i + 1]};
+      pc[i >> 2].w[i & 3] = __builtin_bit_cast(unsigned, w);
+      asm volatile("" : "+v"(psum), "+v"(pc[i >> 2].w[i & 3]));
+    };
+    // vector work of half-step c (two per step): the maximum in the first four half-steps, then the 16
+    // exponentials with their sums and conversions spread over the rest
+    auto vec = [&](auto c_) {
+      constexpr int C = decltype(c_)::value, C0 = 3, NC = 2 * NST - C0;
+      if constexpr (SM) {
+        if constexpr (C == 0) {
 #pragma unroll
-      for (int b = 0; b < NQB; ++b) {
-        // masked scores are -inf; a query that has seen no key yet (possible inside a later piece of
-        // the key range, or for the padding lanes) keeps max = -inf and gets p = 0 everywhere
-        float mx = -INFINITY;
-        if (diag) {
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-              const int key = t0 + kb * 32 + (i >> 2) * 8 + h * 4 + (i & 3);
-              sacc[b][kb][i] = key <= my_pos[b] ? sacc[b][kb][i] : -INFINITY;
-            }
-        }
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) mx = fmaxf(mx, sacc[b][kb][i]);
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const float new_max = fmaxf(row_max[b], mx);
-        const float neg_mc = new_max == -INFINITY ? 0.f : -new_max * scale_log2e;
-        float psum = 0.f;
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const float pv = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[b][kb][i], scale_log2e, neg_mc));
-            psum += pv;
-            pf[b][kb * 2 + (i >> 3)][i & 7] = (bf16)pv;
+          for (int i = 0; i < 8; ++i) mx = fmaxf(fmaxf(mx, sc[i]), sc[i + 8]);
+        } else if constexpr (C == 1) {
+          mx = half_swap_max(mx);
+        } else if constexpr (C == 2) {
+          if (__any(mx > thr)) {
+            // masked scores are -inf; a query that has seen no key yet (possible inside a later piece of
+            // the key range, or for the padding lanes) keeps ref = -inf and gets p = 0 everywhere
+            const float nr = fmaxf(ref, mx);
+            alpha = nr > ref ? __builtin_amdgcn_exp2f((ref - nr) * scale_log2e) : 1.f;
+            ref = nr;
+            thr = nr + lazy;
+            neg_mc = nr == -INFINITY ? 0.f : -nr * scale_log2e;
+            moved = true;
           }
-        // the accumulators only need rescaling when some query's running max moved, which
-        // becomes rare after the first tiles
-        if (__any(new_max > row_max[b])) {
-          const float alpha = new_max > row_max[b] ? __builtin_amdgcn_exp2f((row_max[b] - new_max) * scale_log2e) : 1.f;
-          row_sum[b] *= alpha;
+        } else {
+          constexpr int B0 = 16 * (C - C0) / NC, B1 = 16 * (C - C0 + 1) / NC;
 #pragma unroll
-          for (int d = 0; d < DB; ++d)
+          for (int i = B0; i < B1; ++i) {
+            e[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[i], scale_log2e, neg_mc));
+            asm volatile("" : "+v"(e[i]));             // keeps the instruction in its slot
+          }
+          // conversion and sum of the pairs finished one half-step ago
+          constexpr int A0 = C == C0 ? 0 : 16 * (C - C0 - 1) / NC / 2, A1 = C == C0 ? 0 : B0 / 2;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) oacc[b][d][i] *= alpha;
-          row_max[b] = new_max;
-        }
-        row_sum[b] += psum;
-      }
-      // ---- O^T += V^T P^T ----
-      {
-        // V operand (two transposing reads) fetched one step ahead; step = (u, d)
-        constexpr int NSTEP = 4 * DB;
-        union VF { s16x4 s[2]; bf16x8 b; } vf[2];
-        auto vread = [&](int st, VF &dst) {
-          const int u = st / DB, d = st % DB;
-          dst.s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (__attribute__((address_space(3))) s16x4 *)(ck + u * 16 * ROWB + v_off[d][0]));
-          dst.s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              (__attribute__((address_space(3))) s16x4 *)(ck + u * 16 * ROWB + v_off[d][1]));
-        };
-        vread(0, vf[0]);
-#pragma unroll
-        for (int st = 0; st < NSTEP; ++st) {
-          if (st + 1 < NSTEP) vread(st + 1, vf[(st + 1) & 1]);
-#pragma unroll
-          for (int b = 0; b < NQB; ++b)
-            oacc[b][st % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[st & 1].b, pf[b][st / DB], oacc[b][st % DB], 0, 0, 0);
+          for (int i = A0; i < A1; ++i) {
+            fold(i);
+          }
         }
       }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto step = [&](auto i_) {
+      constexpr int I = decltype(i_)::value;
+      constexpr int PER = 2 + (WS ? 1 : 0), PERN = 2 + (NS ? 1 : 0);       // reads per step: this phase, the next
+      constexpr int N1 = I + 1 < NST ? PER : (NX ? PERN : 0), N2 = I + 2 < NST ? PER : (NX ? PERN : 0);
+      if constexpr (I + 2 < NST) read_step(odd_, ws_, IntC<1>{}, IntC<I + 2>{}, dk, dv);
+      else if constexpr (NX) read_step(IntC<1 - ODD>{}, ns_, IntC<1>{}, IntC<I + 2 - NST>{}, dk, dv);
+      att_wait<N1 + N2>();
+      if constexpr (WS) {
+        asm volatile("" : "+v"(kf[I & 3]));
+        if constexpr (I == 0) {
+          f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0], qf[0], z, 0, 0, 0);
+        } else {
+          sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[I & 3], qf[I], sn, 0, 0, 0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      vec(IntC<2 * I>{});
+      asm volatile("" : "+v"(vf[I & 3].s[0]), "+v"(vf[I & 3].s[1]));
+      oacc[I % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[I & 3].b, pp[I / DB].b, oacc[I % DB], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      vec(IntC<2 * I + 1>{});
+      // the loads of this iteration ride along in the even phase
+      if constexpr (!ODD && SM && (I & 1)) {
+        constexpr int L = I / 2;                       // NST / 2 = 2 LPT slots (DH = 128: 4, DH = 64: 2)
+        if constexpr (L < LPT) issue(t + 3, L, false);
+        else if constexpr (L < 2 * LPT) issue(t + 2, L - LPT, true);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    step(IntC<0>{}); step(IntC<1>{}); step(IntC<2>{}); step(IntC<3>{});
+    if constexpr (NST == 8) { step(IntC<4>{}); step(IntC<5>{}); step(IntC<6>{}); step(IntC<7>{}); }
+    if constexpr (SM) {
+      constexpr int A0 = 16 * (2 * NST - 4) / (2 * NST - 3) / 2;           // pairs of the last half-step
+#pragma unroll
+      for (int i = A0; i < 8; ++i) {
+        fold(i);
+      }
+      if (moved) {
+        row_sum *= alpha;
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) oacc[d][i] *= alpha;
+      }
+      row_sum += psum;
+    }
+  };
+  // byte step from the stage of tile t to the stage of tile t + 1
+  auto stage_step = [&](int t) { return (t & (ATT_S - 1)) == ATT_S - 1 ? -(ATT_S - 1) * TILEB : TILEB; };
+
+  // ---- S of the first sub-tile ----
+  att_vm_wait<4 * LPT>();                  // K(t_begin) landed
+  asm volatile("s_barrier" ::: "memory");
+  if (t_begin <= t_last) {
+    att_read_k<0>(kf[0], k_addr[0]);
+    att_read_k<0>(kf[1], k_addr[1]);
+    auto sstep = [&](auto i_) {
+      constexpr int I = decltype(i_)::value;
+      if constexpr (I + 2 < NST) att_read_k<0>(kf[(I + 2) & 3], k_addr[I + 2]);
+      att_wait<(I + 2 < NST ? 2 : I + 1 < NST ? 1 : 0)>();
+      asm volatile("" : "+v"(kf[I & 3]));
+      if constexpr (I == 0) {
+        f32x16 z = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0], qf[0], z, 0, 0, 0);
+      } else {
+        sacc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[I & 3], qf[I], sacc[0], 0, 0, 0);
+      }
+    };
+    sstep(IntC<0>{}); sstep(IntC<1>{}); sstep(IntC<2>{}); sstep(IntC<3>{});
+    if constexpr (NST == 8) { sstep(IntC<4>{}); sstep(IntC<5>{}); sstep(IntC<6>{}); sstep(IntC<7>{}); }
+  }
+  // iteration t begins once K(t + 1) and V(t) have landed everywhere
+  att_vm_wait<2 * LPT>();
+  asm volatile("s_barrier" ::: "memory");
+  int t = t_begin;
+  if (t_begin <= t_last) {
+    // nothing was requested by a phase before; V(t_begin) stands in for V(t_begin - 1), its P is zero
+    read_step(IntC<0>{}, IntC<1>{}, IntC<1>{}, IntC<0>{}, 0, 0);
+    read_step(IntC<0>{}, IntC<1>{}, IntC<1>{}, IntC<1>{}, 0, 0);
+    int dv = 0;
+    for (; t < t_last; ++t) {
+      const int dk = stage_step(t);
+      phase(IntC<0>{}, IntC<1>{}, IntC<1>{}, IntC<1>{}, IntC<1>{}, t, dk, dv);
+      phase(IntC<1>{}, IntC<1>{}, IntC<1>{}, IntC<1>{}, IntC<1>{}, t, dk, dv);
+      dv = dk;
+      att_vm_wait<2 * LPT>();
+      asm volatile("s_barrier" ::: "memory");
+    }
+    phase(IntC<0>{}, IntC<1>{}, IntC<1>{}, IntC<0>{}, IntC<1>{}, t, 0, dv);
+    phase(IntC<1>{}, IntC<1>{}, IntC<0>{}, IntC<0>{}, IntC<1>{}, t, 0, dv);
+    phase(IntC<0>{}, IntC<0>{}, IntC<0>{}, IntC<0>{}, IntC<0>{}, t, 0, 0);     // O += V P of the last sub-tile
+    if (++t < n_tiles) {
+      att_vm_wait<2 * LPT>();
+      asm volatile("s_barrier" ::: "memory");
     }
   }
-  __builtin_amdgcn_s_waitcnt(7 << 4);      // drain the clamped tail loads before the workgroup ends
+  // the rest of the piece lies in this wavefront's future: it only takes part in the loads
+  for (; t < n_tiles; ++t) {
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) issue(t + 3, i, false);
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) issue(t + 2, i, true);
+    if (t + 1 < n_tiles) {
+      att_vm_wait<2 * LPT>();
+      asm volatile("s_barrier" ::: "memory");
+    }
+  }
+  att_vm_wait<0>();                        // drain the clamped tail loads before the workgroup ends
   if (gridDim.z > 1) {
-    // ---- partial results: O (un-normalised), running max and sum per (kv head, query, split) ----
-#pragma unroll
-    for (int b = 0; b < NQB; ++b) {
-      const float tot = row_sum[b] + __shfl_xor(row_sum[b], 32, 64);
-      if (!valid[b]) continue;
-      const int m = m_pad + (wave * NQB + b) * 32 + ln;
-      const size_t slot = ((size_t)kvh * n_flat_pad + m) * gridDim.z + blockIdx.z;
-      if (h == 0) {
-        part_ml[slot * 2] = row_max[b] * scale_log2e;
-        part_ml[slot * 2 + 1] = tot;
-      }
-      float *dst = part_o + slot * DH;
-#pragma unroll
-      for (int d = 0; d < DB; ++d)
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-          *reinterpret_cast<float4 *>(dst + d * 32 + a * 8 + h * 4) =
-              make_float4(oacc[b][d][a * 4 + 0], oacc[b][d][a * 4 + 1], oacc[b][d][a * 4 + 2],
-                          oacc[b][d][a * 4 + 3]);
+    // ---- partial results: O (un-normalised), reference and sum per (kv head, query, split) ----
+    const float tot = row_sum + __shfl_xor(row_sum, 32, 64);
+    if (!valid) return;
+    const int m = m_pad + wave * 32 + ln;
+    const size_t slot = ((size_t)kvh * n_flat_pad + m) * gridDim.z + blockIdx.z;
+    if (h == 0) {
+      part_ml[slot * 2] = ref * scale_log2e;
+      part_ml[slot * 2 + 1] = tot;
     }
-    return;
-  }
-  // ---- normalise and store ----
-#pragma unroll
-  for (int b = 0; b < NQB; ++b) {
-    const float tot = row_sum[b] + __shfl_xor(row_sum[b], 32, 64);
-    const float inv = 1.f / tot;
-    if (!valid[b]) continue;
-    bf16 *dst = o + q_off[b];
+    float *dst = part_o + slot * DH;
 #pragma unroll
     for (int d = 0; d < DB; ++d)
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        bf16x4 w = {(bf16)(oacc[b][d][a * 4 + 0] * inv), (bf16)(oacc[b][d][a * 4 + 1] * inv),
-                    (bf16)(oacc[b][d][a * 4 + 2] * inv), (bf16)(oacc[b][d][a * 4 + 3] * inv)};
-        *reinterpret_cast<bf16x4 *>(dst + d * 32 + a * 8 + h * 4) = w;
-      }
+      for (int a = 0; a < 4; ++a)
+        *reinterpret_cast<float4 *>(dst + d * 32 + a * 8 + h * 4) =
+            make_float4(oacc[d][a * 4 + 0], oacc[d][a * 4 + 1], oacc[d][a * 4 + 2], oacc[d][a * 4 + 3]);
+    return;
   }
+  // ---- normalise and store ----
+  const float tot = row_sum + __shfl_xor(row_sum, 32, 64);
+  const float inv = 1.f / tot;
+  if (!valid) return;
+  bf16 *dst = o + q_off;
+#pragma unroll
+  for (int d = 0; d < DB; ++d)
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      bf16x4 w = {(bf16)(oacc[d][a * 4 + 0] * inv), (bf16)(oacc[d][a * 4 + 1] * inv),
+                  (bf16)(oacc[d][a * 4 + 2] * inv), (bf16)(oacc[d][a * 4 + 3] * inv)};
+      *reinterpret_cast<bf16x4 *>(dst + d * 32 + a * 8 + h * 4) = w;
+    }
 }
 
 // Merge of the KV-split partials: o = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s over the
@@ -456,10 +578,6 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__
     if (lane + 64 * c < DH) orow[lane + 64 * c] = acc[c] / run_sum;
 }
 
-// Workgroup = 8 wavefronts x 32 flattened queries (two wavefronts per SIMD: one runs its softmax
-// on the VALU while the other feeds the matrix core, and neither needs more than 256 registers).
-constexpr int ATT_NW = 8, ATT_WGQ = 32 * ATT_NW;
-
 // Split plan of the bf16 kernel.  Few query workgroups (the selective layers) leave most CUs idle,
 // so the key range is cut into pieces of split_tiles tiles handled by separate workgroups
 // (workgroup z takes tiles [z*split_tiles, (z+1)*split_tiles) and exits when its own causal
@@ -544,21 +662,21 @@ hipError_t launch_attention(int dtype, const void *q, const int32_t *q_rows, con
   float *part_o = partial;
   float *part_ml = partial ? partial + slots * dh : nullptr;
   int32_t *wg_tiles = partial ? reinterpret_cast<int32_t *>(part_ml + slots * 2) : nullptr;
-#define CB_ATTN(DH_, NQB_, NW_)                                                                     \
+#define CB_ATTN(DH_)                                                                                \
   do {                                                                                              \
-    constexpr int smem = ATT_S * 2 * BKV * DH_ * 2;                                                 \
+    constexpr int smem = 2 * ATT_S * BKV * DH_ * 2;                                                 \
     static std::once_flag once_;                                                                    \
     std::call_once(once_, [] {                                                                      \
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_kernel<DH_, NQB_, NW_>),  \
+      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_bf16_kernel<DH_>),             \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, smem);                  \
     });                                                                                             \
-    hipLaunchKernelGGL((attn_bf16_kernel<DH_, NQB_, NW_>), dim3(hkv, (unsigned)n_qwg, n_splits),    \
-                       dim3(64 * NW_), smem, s, (const bf16 *)q, q_pos, n_rows, (const bf16 *)kc,   \
+    hipLaunchKernelGGL((attn_bf16_kernel<DH_>), dim3(hkv, (unsigned)n_qwg, n_splits),               \
+                       dim3(64 * ATT_NW), smem, s, (const bf16 *)q, q_pos, n_rows, (const bf16 *)kc, \
                        (const bf16 *)vc, (bf16 *)o, hq, hkv, scale_log2e, split_tiles, part_o,      \
                        part_ml, q_rows, wg_tiles, segs, n_segs);                                    \
   } while (0)
-  if (dh == 64) CB_ATTN(64, 1, ATT_NW);
-  else CB_ATTN(128, 1, ATT_NW);
+  if (dh == 64) CB_ATTN(64);
+  else CB_ATTN(128);
 #undef CB_ATTN
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || n_splits == 1) return e;
