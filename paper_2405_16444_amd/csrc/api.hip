@@ -38,6 +38,7 @@ struct cb_ctx {
   std::vector<hipEvent_t> load_events;   // pipelined loading: [0] = entry fence, [1 + l] = layer l landed
   std::vector<int32_t> seg_tab_host;     // batched calls: host copy of the request tables being uploaded
   mutable std::vector<size_t> partial_memo;   // [rows] -> scratch floats layer calls with <= rows rows can use
+  mutable std::vector<size_t> partial_own;    // [rows] -> the same for exactly that row count
   void *static_scratch;                  // this device's copy of the built-in scratch array (cb_fuse_layer_static)
 };
 
@@ -120,13 +121,12 @@ int xn_pitch(const cb_ctx *c) { return c->m.d_model + xn_lo_off(c); }
 size_t partial_floats_needed(const cb_ctx *c, int max_rows) {
   const cb_model_desc &m = c->m;
   const int d = m.d_model, q_dim = m.n_q_heads * m.head_dim, kv_dim = m.n_kv_heads * m.head_dim;
-  const int rh = m.rope_layout == CB_ROPE_HALF, hl = xn_lo_off(c) > 0, w8 = m.weight_format == CB_W_INT8;
+  const int rh = m.rope_layout == CB_ROPE_HALF, hl = xn_lo_off(c) > 0 ? 2 * kv_dim : 0, w8 = m.weight_format == CB_W_INT8;
   std::vector<size_t> &memo = c->partial_memo;
-  if (memo.empty()) memo.push_back(0);
+  if (memo.empty()) { memo.push_back(0); c->partial_own.push_back(0); }
   while ((int)memo.size() <= max_rows) {
     const int M = (int)memo.size();
-    size_t need = memo.back();
-    need = std::max(need, gemm_partial_floats(m.dtype, EPI_SEG, M, 2 * kv_dim, d, hl, 1, rh, m.head_dim, w8));   // K|V, checked
+    size_t need = gemm_partial_floats(m.dtype, EPI_SEG, M, 2 * kv_dim, d, hl, 1, rh, m.head_dim, w8);             // K|V, checked
     need = std::max(need, gemm_partial_floats(m.dtype, EPI_SEG, M, 2 * kv_dim, d, hl, 0, rh, m.head_dim, w8));   // K|V, every row kept
     need = std::max(need, gemm_partial_floats(m.dtype, EPI_SEG, M, q_dim, d, 0, 0, rh, m.head_dim, w8));         // Q
     need = std::max(need, gemm_partial_floats(m.dtype, EPI_F32, M, d, q_dim, 0, 0, 0, 0, w8));
@@ -134,7 +134,8 @@ size_t partial_floats_needed(const cb_ctx *c, int max_rows) {
     need = std::max(need, gemm_partial_floats(m.dtype, EPI_SWIGLU, M, m.d_ff, d, 0, 0, 0, 0, w8));
     // the attention KV split borrows the same scratch (the two are never live together)
     need = std::max(need, attention_partial_floats_bound(m.dtype, M, m.n_q_heads, m.n_kv_heads, m.head_dim));
-    memo.push_back(need);
+    c->partial_own.push_back(need);
+    memo.push_back(std::max(need, memo.back()));
   }
   return memo[max_rows];
 }
@@ -319,15 +320,29 @@ int fuse_layer_impl(cb_ctx *c, const cb_layer_weights *w, const float *h_in, con
   // so the keys and values get a float-accurate input.  With a check they go to the workspace and the
   // launch that finishes them also measures every candidate's deviation from its cached K/V; without
   // one every row is kept and they are written straight into the cache.
-  g.a_rows = nullptr; g.M = n; g.n_seg = 2; g.a_lo_off = lo_off;
+  // Q of the rows that are kept (Sec. 4.2) takes plain bf16 operands.  Few more rows reach a layer than it keeps
+  // (except on the first checked one), so Q of ALL of them usually rides along in the same launch: one launch, one
+  // finish launch and one partly filled round of workgroups less; attention then reads it through the selection.
+  // The split of the merged launch is capped by what the other projections of this row count park, so that a call
+  // needs no more workspace for it.
+  const bool w8 = m.weight_format == CB_W_INT8 && gemm_int8_in_kernel(1, d);
+  const size_t own = n < (int)c->partial_own.size() ? c->partial_own[n] : 0;
+  const bool merged = dt == CB_BF16 && (m.weight_format != CB_W_INT8 || w8) && own > 0 &&
+                      gemm_merge_pays(n, 2 * kv_dim, rows, q_dim, d, check, w8, own);
+  g.a_rows = nullptr; g.M = n; g.n_seg = merged ? 3 : 2; g.a_lo_off = lo_off; g.n_hl_seg = 2;
+  if (merged) g.split_floats = own;
   {
-    const void *wm[2] = {w->wk, w->wv};
-    const float *sc[2] = {w->wk_scale, w->wv_scale};
-    const int wr[2] = {kv_dim, kv_dim};
-    CB_TRY(stage_weights(c, s, ws, 2, wm, sc, wr, d, &wv));
+    const void *wm[3] = {w->wk, w->wv, w->wq};
+    const float *sc[3] = {w->wk_scale, w->wv_scale, w->wq_scale};
+    const int wr[3] = {kv_dim, kv_dim, q_dim};
+    CB_TRY(stage_weights(c, s, ws, g.n_seg, wm, sc, wr, d, &wv));
   }
   g.row_pos = row_pos;
-  const double kv_flops = 2.0 * n * d * 2 * kv_dim, kv_bytes = ((double)2 * kv_dim * d + (double)n * d + (double)n * 2 * kv_dim) * es;
+  if (merged) g.seg[2] = {wv.w[2], q_dim, ws.qbuf, q_dim, nullptr, 1, nullptr, wv.scale[2]};
+  const int cols = 2 * kv_dim + (merged ? q_dim : 0);
+  // algorithmic work: Q of the kept rows only, whatever rides along
+  const double kv_flops = 2.0 * n * d * 2 * kv_dim + (merged ? 2.0 * rows * d * q_dim : 0.0);
+  const double kv_bytes = ((double)cols * d + (double)n * d + (double)n * 2 * kv_dim + (merged ? (double)rows * q_dim : 0.0)) * es;
   if (check) {
     g.seg[0] = {wv.w[0], kv_dim, ws.kvnew, 2 * kv_dim, nullptr, 1, kc, wv.scale[0]};
     g.seg[1] = {wv.w[1], kv_dim, (char *)ws.kvnew + (size_t)kv_dim * es, 2 * kv_dim, nullptr, 0, vc, wv.scale[1]};
@@ -377,18 +392,18 @@ int fuse_layer_impl(cb_ctx *c, const cb_layer_weights *w, const float *h_in, con
     g.seg[1] = {wv.w[1], kv_dim, vc, kv_dim, crow, 0, nullptr, wv.scale[1]};
     CB_TRY(run_gemm(c, s, g, CB_PROF_REDUCE, kv_flops, kv_bytes, 0));
   }
-  // Q of the rows that are kept (Sec. 4.2), gathered through the selection; plain bf16 operands
-  g.a_rows = sel_rows; g.M = rows; g.n_seg = 1; g.a_lo_off = 0;
-  {
+  if (!merged) {
+    g.a_rows = sel_rows; g.M = rows; g.n_seg = 1; g.a_lo_off = 0; g.n_hl_seg = 0;
     const void *wm[1] = {w->wq};
     const float *sc[1] = {w->wq_scale};
     const int wr[1] = {q_dim};
     CB_TRY(stage_weights(c, s, ws, 1, wm, sc, wr, d, &wv));
+    g.seg[0] = {wv.w[0], q_dim, ws.qbuf, q_dim, nullptr, 1, nullptr, wv.scale[0]};
+    g.row_pos = pos_out;
+    CB_TRY(run_gemm(c, s, g, CB_PROF_REDUCE, 2.0 * rows * d * q_dim,
+                    ((double)q_dim * d + (double)rows * d + (double)rows * q_dim) * es, 0));
   }
-  g.seg[0] = {wv.w[0], q_dim, ws.qbuf, q_dim, nullptr, 1, nullptr, wv.scale[0]};
-  g.row_pos = pos_out;
-  CB_TRY(run_gemm(c, s, g, CB_PROF_REDUCE, 2.0 * rows * d * q_dim,
-                  ((double)q_dim * d + (double)rows * d + (double)rows * q_dim) * es, 0));
+  const int32_t *q_rows = merged ? sel_rows : nullptr;
   {
     // attention is per request: its rows against its own cache slab -- all requests in one launch
     // through the device table (bf16), else a launch per request
@@ -402,14 +417,15 @@ int fuse_layer_impl(cb_ctx *c, const cb_layer_weights *w, const float *h_in, con
         total_qwg += attention_query_workgroups(segs[b].k + segs[b].S, m.n_q_heads, m.n_kv_heads);
         max_t = std::max(max_t, segs[b].T);
       }
-      CB_HIP(launch_attention(dt, ws.qbuf, nullptr, pos_out, rows, kc, vc, ws.obuf, m.n_q_heads,
+      CB_HIP(launch_attention(dt, ws.qbuf, q_rows, pos_out, rows, kc, vc, ws.obuf, m.n_q_heads,
                               m.n_kv_heads, m.head_dim, max_t, ws.partial, ws.partial_floats, s, seg_dev, n_segs,
                               total_qwg));
     }
     for (int b = 0; b < n_segs && !varlen; ++b) {
       const int rows_b = segs[b].k + segs[b].S;
-      const char *q_b = (const char *)ws.qbuf + (size_t)out_off * q_dim * es;
-      CB_HIP(launch_attention(dt, q_b, nullptr, pos_out + out_off, rows_b,
+      // (several requests without a table: q_rows, when set, index the stacked rows)
+      const char *q_b = (const char *)ws.qbuf + (q_rows ? 0 : (size_t)out_off * q_dim * es);
+      CB_HIP(launch_attention(dt, q_b, q_rows ? q_rows + out_off : nullptr, pos_out + out_off, rows_b,
                               (char *)kc + (size_t)b * cache_stride * kv_dim * es,
                               (char *)vc + (size_t)b * cache_stride * kv_dim * es,
                               (char *)ws.obuf + (size_t)out_off * q_dim * es, m.n_q_heads, m.n_kv_heads,

@@ -48,6 +48,8 @@ struct GemmParams {
   int raw_partial;      // the main kernel only parks its sums in `partial`; the finish launch applies the epilogue
   int a_lo_off;         // > 0: the activations are a (high, low) bf16 pair, the low parts a_lo_off elements after
                         // the high parts of the same row; both are multiplied and their products added
+  int hl_cols;          // output columns that take the pair (the leading ones; the others take the high parts alone)
+  int hl_tiles_m, hl_tiles_n;   // direct-to-LDS kernel: tiles of those columns
   float *out_f32;
   const float *resid;
   const int32_t *resid_rows;
@@ -375,17 +377,17 @@ __global__ __launch_bounds__(256) void swiglu_tail_kernel(GemmParams p, int tile
   }
 }
 
-// HL (EPI_SEG only): the activations are (high, low) bf16 pairs.  The activation tile then holds
-// BM/2 logical rows twice -- their high parts in its first half, their low parts in its second --
-// so the wavefronts with wm = 0 multiply the high parts and those with wm = 1 the low parts of the
-// SAME output rows, and the two sets of sums are added in LDS before the epilogue.
+// HL (EPI_SEG only): the leading p.hl_cols output columns take (high, low) bf16 pairs of the activations.  The
+// activation tile of such a column tile holds BM/2 logical rows twice -- their high parts in its first half, their low
+// parts in its second -- so the wavefronts with wm = 0 multiply the high parts and those with wm = 1 the low parts
+// of the SAME output rows, and the two sets of sums are added in LDS before the epilogue.  Tiles of the
+// other columns (Q beside K and V in one launch) are ordinary ones; which kind a workgroup has is uniform.
 // W8: the weights are int8 (one byte per element in memory and in LDS, half the traffic of both); a fragment
 // is expanded to bf16 in registers right before its k-step and the per-column scales multiply the finished sums.
 template <int I, int NB, int EPI, int NWV, bool HL = false, bool W8 = false>
 __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
   constexpr int BM = 32 * I, BN = 64 * NB, SW = dma_w_stages(I, BN, W8), DMA_CP = BN + 4;
   constexpr int WE = W8 ? 1 : 2;                         // bytes per weight element
-  constexpr int BMO = HL ? BM / 2 : BM;                  // output rows per tile
   static_assert(!HL || EPI == EPI_SEG, "operand pairs are for the K/V projection only");
   constexpr int A_STAGE = BM * 128, W_STAGE = BN * 64 * WE, W_RING = DMA_SA * A_STAGE;
   constexpr int WN = NWV / 2;                            // wavefronts as 2 x WN
@@ -411,18 +413,27 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
     j = (p.tail_first >> 3) + v / p.tail_splits;
   }
   int z, nt, mt;
-  if (EPI != EPI_SWIGLU && p.xcd_split) {
-    const int groups = 8 / p.splits;                 // XCDs that share one split
-    z = xcd % p.splits;
-    xcd_tile(j, xcd / p.splits, tiles_m, (tiles_n + groups - 1) / groups, &nt, &mt, groups);
-  } else {
-    const int nblk = (tiles_n + 7) >> 3;
-    const int per_z = nblk * tiles_m;
-    z = j / per_z;
-    xcd_tile(j - z * per_z, xcd, tiles_m, nblk, &nt, &mt);
+  bool hl = false;                                       // this tile takes the pair
+  {
+    // a split-dealing launch: XCDs that share one split; else all 8 share every split
+    const bool dealt = EPI != EPI_SWIGLU && p.xcd_split;
+    const int groups = dealt ? 8 / p.splits : 8, x = dealt ? xcd / p.splits : xcd;
+    const int nblk = (tiles_n + groups - 1) / groups;
+    const int nblk_hl = HL ? (p.hl_tiles_n + groups - 1) / groups : 0, cnt_hl = HL ? nblk_hl * p.hl_tiles_m : 0;
+    const int per_z = nblk * tiles_m + cnt_hl;
+    z = dealt ? xcd % p.splits : j / per_z;
+    int r = dealt ? j : j - z * per_z;
+    hl = HL && r < cnt_hl;                               // the pair tiles come first (they do twice the work per output)
+    if (hl) {
+      xcd_tile(r, x, p.hl_tiles_m, nblk_hl, &nt, &mt, groups);
+      if (nt >= p.hl_tiles_n) return;
+    } else {
+      xcd_tile(r - cnt_hl, x, tiles_m, nblk, &nt, &mt, groups);
+      if (nt >= tiles_n) return;
+      if (HL) nt += p.hl_tiles_n;                        // hl_cols is a multiple of BN
+    }
   }
-  if (nt >= tiles_n) return;
-  const int m0 = mt * BMO, n0 = nt * OUT_COLS;
+  const int m0 = mt * (hl ? BM / 2 : BM), n0 = nt * OUT_COLS;
   const int kps = tail_z >= 0 ? p.tail_k_per_split : p.k_per_split;
   const int kb = (tail_z >= 0 ? tail_z : z) * kps;
   const int ke = min(p.K, kb + kps);
@@ -435,10 +446,11 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
   for (int i = 0; i < LA; ++i) {
     const int r = (wave + NWV * i) * 8 + (lane >> 3);         // row of the activation tile
     const int chunk = (lane & 7) ^ ((r & 7) ^ ((r >> 3) & 1));
-    int ar = min(m0 + (HL ? r % BMO : r), p.M - 1);
+    const bool low = HL && hl && r >= BM / 2;
+    int ar = min(m0 + (low ? r - BM / 2 : r), p.M - 1);
     if (p.a_rows) ar = p.a_rows[ar];
     src_a[i] = reinterpret_cast<const bf16 *>(p.a) + (size_t)ar * p.lda + chunk * 8 + kb +
-               (HL && r >= BMO ? p.a_lo_off : 0);
+               (low ? p.a_lo_off : 0);
   }
 #pragma unroll
   for (int i = 0; i < LW; ++i) {
@@ -499,7 +511,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
     const int a_off = (wm * IH * 32) * 128, b_off = (wn * (BN / WN)) * 128;
     int blk_ok = 0;                                    // bit i: 16-row block i of this wavefront holds a real row
 #pragma unroll
-    for (int i = 0; i < RB; ++i) blk_ok |= (m0 + (HL ? 0 : wm * IH * 32) + i * 16 < p.M) << i;
+    for (int i = 0; i < RB; ++i) blk_ok |= (m0 + (hl ? 0 : wm * IH * 32) + i * 16 < p.M) << i;
     blk_ok = __builtin_amdgcn_readfirstlane(blk_ok);
     // one scalar flag per block, re-read through an empty asm at every test: left alone the compiler hoists the
     // tests out of the loop as lane masks and rebuilds their complements with vector instructions inside it
@@ -741,7 +753,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
   vm_wait<0>();
   __syncthreads();
   float *sC = reinterpret_cast<float *>(smem);
-  if (HL) {
+  if (HL && hl) {
     // the sums over the high parts are parked first, the sums over the low parts added to them
 #pragma unroll
     for (int part = 0; part < 2; ++part) {
@@ -757,7 +769,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
       }
       __syncthreads();
     }
-    lds_epilogue<bf16, EPI, BN>(sC, DMA_CP, BMO, m0, n0, z, p);
+    lds_epilogue<bf16, EPI, BN>(sC, DMA_CP, BM / 2, m0, n0, z, p);
     return;
   }
   // park and walk the tile in passes of at most 128 rows (LDS holds 128 x 260 floats)
@@ -964,31 +976,68 @@ __device__ __forceinline__ float4 sum_splits(const GemmParams &p, size_t e) {
 // EPI_SEG rows: rotary embedding, conversion to the storage type, store (optionally through the
 // segment's row map) and -- for rows < n_dev -- the KV deviation of the row (Sec. 4.1, Sec. 6):
 // the squared distance of the values as stored from the cached row, over the segments that name a cache.
+// Workgroup (r, 0) takes columns [0, first) of row r, all columns with a deviation among them; workgroup (r, y) the
+// y-th run of kFinishCols columns after those.  A row alone is too little work in flight: a lane keeps two column groups
+// in work and requests four splits of both before the first addition.  Bound by the parked sums it reads; on the 7B
+// shape (30 .. 500 rows, K|V and Q) 9.4 us per launch where a loop of one load after the other took 13.5 us for K|V
+// and 13.5 us for Q.
+constexpr int kFinishCols = 2048;
 template <typename T>
-__global__ __launch_bounds__(256) void seg_finish_kernel(GemmParams p) {
+__global__ __launch_bounds__(256) void seg_finish_kernel(GemmParams p, int first) {
   __shared__ float red[4];
   const int r = blockIdx.x;
-  const bool want_dev = p.dev_out != nullptr && r < p.n_dev;
+  const int cb = blockIdx.y == 0 ? 0 : first + ((int)blockIdx.y - 1) * kFinishCols;
+  const int ce = blockIdx.y == 0 ? first : min(p.N, cb + kFinishCols);
+  const bool want_dev = p.dev_out != nullptr && blockIdx.y == 0 && r < p.n_dev;
   const int crow = want_dev ? p.dev_row[r] : 0;
+  const size_t stride = (size_t)p.M * p.N;
   float dsum = 0.f;
-  for (int c = threadIdx.x * 4; c < p.N; c += 1024) {
-    const size_t e = (size_t)r * p.N + c;
-    const float4 acc = sum_splits(p, e);
-    float4 partner = acc;
-    if (p.rope_half) partner = sum_splits(p, (size_t)((long)e + rope_partner_offset(p, c)));
-    int s, lc;
-    const float4 v = seg_rotate(acc, partner, r, c, p, &s, &lc);
-    const int dr = p.row_map[s] ? p.row_map[s][r] : r;
-    store4<T>(reinterpret_cast<T *>(p.dst[s]) + (size_t)dr * p.ld[s] + lc, v.x, v.y, v.z, v.w);
-    if (want_dev && p.dev_cache[s]) {
-      const float4 old = load4<T>(reinterpret_cast<const T *>(p.dev_cache[s]) +
-                                  (size_t)crow * (p.nb[s + 1] - p.nb[s]) + lc);
-      const float d0 = as_stored<T>(v.x) - old.x, d1 = as_stored<T>(v.y) - old.y;
-      const float d2 = as_stored<T>(v.z) - old.z, d3 = as_stored<T>(v.w) - old.w;
-      dsum += d0 * d0 + d1 * d1 + d2 * d2 + d3 * d3;
+  for (int c = cb + threadIdx.x * 4; c < ce; c += 2048) {
+    const bool two = c + 1024 < ce;
+    const float *src = p.partial + (size_t)r * p.N + c;
+    const int off1 = two ? 1024 : 0;
+    float4 a0 = make_float4(0, 0, 0, 0), a1 = a0;
+    auto add = [](float4 &a, const float4 &v) { a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w; };
+    int z = 0;
+    for (; z + 4 <= p.splits; z += 4, src += 4 * stride) {
+      float4 v0[4], v1[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        v0[i] = *reinterpret_cast<const float4 *>(src + i * stride);
+        v1[i] = *reinterpret_cast<const float4 *>(src + i * stride + off1);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { add(a0, v0[i]); add(a1, v1[i]); }
+    }
+    for (; z < p.splits; ++z, src += stride) {
+      const float4 v0 = *reinterpret_cast<const float4 *>(src), v1 = *reinterpret_cast<const float4 *>(src + off1);
+      add(a0, v0);
+      add(a1, v1);
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float4 acc = i ? a1 : a0;
+      float4 partner = acc;
+      if (p.rope_half) {
+        // a head's other half is head_dim / 8 lanes away (heads are whole and 1024 columns hold whole heads)
+        const int o = p.head_dim / 8;
+        partner = make_float4(__shfl_xor(acc.x, o, 64), __shfl_xor(acc.y, o, 64), __shfl_xor(acc.z, o, 64), __shfl_xor(acc.w, o, 64));
+      }
+      if (i == 1 && !two) continue;
+      int s, lc;
+      const float4 v = seg_rotate(acc, partner, r, c + i * 1024, p, &s, &lc);
+      const int dr = p.row_map[s] ? p.row_map[s][r] : r;
+      store4<T>(reinterpret_cast<T *>(p.dst[s]) + (size_t)dr * p.ld[s] + lc, v.x, v.y, v.z, v.w);
+      if (want_dev && p.dev_cache[s]) {
+        const float4 old = load4<T>(reinterpret_cast<const T *>(p.dev_cache[s]) +
+                                    (size_t)crow * (p.nb[s + 1] - p.nb[s]) + lc);
+        const float d0 = as_stored<T>(v.x) - old.x, d1 = as_stored<T>(v.y) - old.y;
+        const float d2 = as_stored<T>(v.z) - old.z, d3 = as_stored<T>(v.w) - old.w;
+        dsum += d0 * d0 + d1 * d1 + d2 * d2 + d3 * d3;
+      }
     }
   }
-  if (p.dev_out != nullptr) {              // uniform over the workgroup
+  if (p.dev_out != nullptr && blockIdx.y == 0) {     // uniform over the workgroup
     dsum = block_sum_256(dsum, red);
     if (want_dev && threadIdx.x == 0) p.dev_out[r] = dsum;
   }
@@ -1101,9 +1150,11 @@ struct GemmPlan {
   int kind;        // 0 float, 1 register-staged bf16, 2 direct-to-LDS bf16
   int I, NB;       // kind 2: the kernel's tile = 32I activation-tile rows x 64NB columns
   int nwv;         // kind 2: wavefronts per workgroup (4, or 8 = two per SIMD for the 256-column tiles)
-  int hl;          // the activations are (high, low) pairs (bf16 EPI_SEG only)
-  int bm, out_cols, bk;   // bm: OUTPUT rows per tile (half the activation-tile rows with hl, kind 2)
+  int hl;          // output columns that take (high, low) activation pairs (bf16 EPI_SEG only)
+  int bm, out_cols, bk;   // bm: output rows per tile (of the columns without pairs, kind 2)
+  int hl_tiles_m, hl_tiles_n;             // kind 2: tiles of the columns with pairs; tiles_m, tiles_n: of the others
   int tiles_m, tiles_n, splits, k_per_split;
+  double cost;     // estimated us of the main and the finish launch (kind 2, not EPI_SWIGLU)
   int tail_first, tail_splits, tail_k_per_split;   // EPI_SWIGLU tail sharing (tail_splits <= 1: none)
   long grid_ids;                                   // kind 2: workgroups of the main launch
   int xcd_split;                                   // kind 2: splits dealt to XCDs (see GemmParams)
@@ -1142,15 +1193,17 @@ struct DmaShape { int I, NB; double t_full; };
 static const DmaShape kDmaShapes[] = {{2, 2, 0.80}, {4, 2, 1.23}, {6, 2, 1.02}, {8, 2, 1.28},
                                       {4, 4, 1.14}, {6, 4, 1.54}, {8, 4, 1.90}};
 
-static void pick_dma_plan(int M, int N, int K, int max_splits, bool parked, size_t out_elems, bool w8, GemmPlan *pl) {
+// Output columns [0, hl_cols) take (high, low) activation pairs, i.e. twice the tile rows per output row.
+static void pick_dma_plan(int M, int N, int hl_cols, int K, int max_splits, bool parked, bool w8, GemmPlan *pl) {
   const int k_tiles = K / DMA_BK;
-  const double park_us = (double)out_elems * 4.0e-6 * 0.258;   // per split
-  double best = 1e30;
+  const double park_us = (double)M * N * 4.0e-6 * 0.258;   // per split
+  pl->cost = 1e30;
   for (const DmaShape &c : kDmaShapes) {
-    if (c.I == 2 && M > 64) continue;
     const int bm = 32 * c.I, bn = 64 * c.NB;
+    if (c.I == 2 && (hl_cols ? 2 * M : M) > 64) continue;
+    if (hl_cols < N && hl_cols % bn != 0) continue;        // a tile's columns are of one kind
     const int slots = dma_smem_bytes(c.I, bn, w8) <= 80 * 1024 ? 512 : 256;
-    const long tiles = (long)ceil_div(M, bm) * ceil_div(N, bn);
+    const long tiles = (long)ceil_div(2 * M, bm) * ceil_div(hl_cols, bn) + (long)ceil_div(M, bm) * ceil_div(N - hl_cols, bn);
     for (int sp = 1; sp <= 16 && sp <= max_splits; ++sp) {
       if (sp > 1 && k_tiles / sp < 4) break;
       const long wgs = tiles * sp;
@@ -1159,7 +1212,7 @@ static void pick_dma_plan(int M, int N, int K, int max_splits, bool parked, size
       const double relief = slots == 512 ? 0.69 : 0.45;
       const double per_tile = full * c.t_full + (last > 0 ? c.t_full * (1.0 - relief + relief * last) : 0.0);
       const double cost = per_tile * ceil_div(k_tiles, sp) + 9.9 + (sp > 1 || parked ? sp * park_us + 2.3 : 0.0);
-      if (cost < best - 1e-9) { best = cost; pl->I = c.I; pl->NB = c.NB; pl->splits = sp; }
+      if (cost < pl->cost - 1e-9) { pl->cost = cost; pl->I = c.I; pl->NB = c.NB; pl->splits = sp; }
     }
   }
 }
@@ -1172,7 +1225,7 @@ static bool needs_raw_partial(int dtype, int epi, int rope_half, int head_dim) {
 
 bool gemm_int8_in_kernel(int dtype, int K) { return dtype == 1 && K % DMA_BK == 0; }
 
-// Shape of one problem.  hl: (high, low) activation pairs; force_raw: the caller wants the finish
+// Shape of one problem.  hl: leading output columns with (high, low) activation pairs; force_raw: the caller wants the finish
 // launch (deviation, or the float output's residual + norm); scratch_floats: what `partial` holds
 // (the K split is capped by it; SIZE_MAX when sizing).
 static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int force_raw, int rope_half,
@@ -1181,7 +1234,7 @@ static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int f
   pl.w8 = w8;
   if (w8 && !gemm_int8_in_kernel(dtype, K)) pl.bad = true;
   pl.splits = 1;
-  pl.hl = hl && dtype == 1 && epi == EPI_SEG;
+  pl.hl = dtype == 1 && epi == EPI_SEG ? hl : 0;
   pl.raw = force_raw || epi == EPI_F32 || needs_raw_partial(dtype, epi, rope_half, head_dim);
   const size_t mn = (size_t)M * N;
   const int max_splits = (int)std::min<size_t>(16, std::max<size_t>(1, scratch_floats / std::max<size_t>(1, mn)));
@@ -1201,16 +1254,20 @@ static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int f
     if (c2 < c4) pl.NB = 2;
   } else {
     pl.kind = 2; pl.bk = DMA_BK;
-    // with operand pairs the activation tile holds every output row twice
-    pick_dma_plan(pl.hl ? 2 * M : M, N, K, max_splits, pl.raw, mn, w8, &pl);
+    pick_dma_plan(M, N, pl.hl, K, max_splits, pl.raw, w8, &pl);
+    if (pl.I == 0) { pl.bad = true; pl.I = 8; pl.NB = 4; }     // no tile width divides the columns with pairs
   }
   if (pl.kind == 2) {
     pl.nwv = (pl.NB == 4 && pl.I >= 4) ? 8 : 4;
-    pl.bm = pl.hl ? 16 * pl.I : 32 * pl.I;
+    pl.bm = 32 * pl.I;
     pl.out_cols = (epi == EPI_SWIGLU ? 32 : 64) * pl.NB;
   }
   pl.tiles_m = ceil_div(M, pl.bm);
-  pl.tiles_n = ceil_div(N, pl.out_cols);
+  pl.tiles_n = ceil_div(pl.kind == 2 ? N - pl.hl : N, pl.out_cols);
+  if (pl.kind == 2 && pl.hl) {
+    pl.hl_tiles_m = ceil_div(M, pl.bm / 2);
+    pl.hl_tiles_n = ceil_div(pl.hl, pl.out_cols);
+  }
   const int k_tiles = ceil_div(K, pl.bk);
   const long tiles = (long)pl.tiles_m * pl.tiles_n;
   if (pl.kind == 1 && epi != EPI_SWIGLU && tiles < 256) {
@@ -1230,12 +1287,10 @@ static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int f
   pl.partial_floats = pl.raw ? (size_t)pl.splits * mn : 0;
   pl.tail_splits = 1;
   if (pl.kind == 2) {
-    const long ids = 8L * ceil_div(pl.tiles_n, 8) * pl.tiles_m;
-    pl.grid_ids = ids * pl.splits;
-    if (epi != EPI_SWIGLU && (pl.splits == 2 || pl.splits == 4 || pl.splits == 8)) {
-      pl.xcd_split = 1;
-      pl.grid_ids = 8L * ceil_div(pl.tiles_n, 8 / pl.splits) * pl.tiles_m;
-    }
+    pl.xcd_split = epi != EPI_SWIGLU && (pl.splits == 2 || pl.splits == 4 || pl.splits == 8);
+    const int groups = pl.xcd_split ? 8 / pl.splits : 8;
+    const long ids = 8L * (ceil_div(pl.tiles_n, groups) * pl.tiles_m + ceil_div(pl.hl_tiles_n, groups) * pl.hl_tiles_m);
+    pl.grid_ids = pl.xcd_split ? ids : ids * pl.splits;
     pl.tail_first = (int)pl.grid_ids;
     if (epi == EPI_SWIGLU) {
       // The last round of 256 workgroups, when less than half full, is shared: ts workgroups per
@@ -1295,19 +1350,32 @@ static GemmPlan fill_params(const GemmArgs &g, GemmParams *pp) {
   p.dev_out = g.dev_out; p.n_dev = g.n_dev; p.dev_row = g.dev_row;
   p.norm_gain = g.norm_gain; p.norm_out = g.norm_out; p.norm_ld = g.norm_ld; p.norm_lo_off = g.norm_lo_off;
   p.norm_eps = g.norm_eps;
-  GemmPlan pl = make_plan(g.dtype, g.epi, g.M, p.N, g.K, g.a_lo_off > 0, g.dev_out != nullptr, g.rope_half,
-                          g.head_dim, g.partial ? g.partial_floats : 0, g.seg[0].w_scale != nullptr);
+  const int hl_cols = g.a_lo_off > 0 ? p.nb[g.n_hl_seg > 0 ? std::min(g.n_hl_seg, p.n_seg) : p.n_seg] : 0;
+  const size_t scratch = g.partial ? (g.split_floats ? std::min(g.split_floats, g.partial_floats) : g.partial_floats) : 0;
+  GemmPlan pl = make_plan(g.dtype, g.epi, g.M, p.N, g.K, hl_cols, g.dev_out != nullptr, g.rope_half, g.head_dim, scratch,
+                          g.seg[0].w_scale != nullptr);
+  if (pl.kind != 2 && hl_cols != 0 && hl_cols != p.N) pl.bad = true;   // the other kernels treat all columns alike
   // every matrix of a launch is in the same format
   const int n_w = g.epi == EPI_SEG ? g.n_seg : (g.epi == EPI_SWIGLU ? 2 : 1);
   for (int i = 1; i < n_w; ++i)
     if ((g.seg[i].w_scale != nullptr) != (g.seg[0].w_scale != nullptr)) pl.bad = true;
   p.a_lo_off = pl.hl ? g.a_lo_off : 0;
+  p.hl_cols = pl.hl; p.hl_tiles_m = pl.hl_tiles_m; p.hl_tiles_n = pl.hl_tiles_n;
   p.raw_partial = pl.raw;
   p.splits = pl.splits;
   p.k_per_split = pl.k_per_split;
   p.tail_first = pl.tail_first; p.tail_splits = pl.tail_splits; p.tail_k_per_split = pl.tail_k_per_split;
   p.xcd_split = pl.xcd_split;
   return pl;
+}
+
+bool gemm_merge_pays(int M, int hl_cols, int M_rest, int n_rest, int K, int force_raw, int w8, size_t split_floats) {
+  if (M <= 0 || M_rest <= 0 || K % DMA_BK != 0) return false;
+  const GemmPlan one = make_plan(1, EPI_SEG, M, hl_cols + n_rest, K, hl_cols, force_raw, 0, 0, split_floats, w8);
+  if (one.bad || one.kind != 2) return false;
+  const GemmPlan kv = make_plan(1, EPI_SEG, M, hl_cols, K, hl_cols, force_raw, 0, 0, split_floats, w8);
+  const GemmPlan q = make_plan(1, EPI_SEG, M_rest, n_rest, K, 0, 0, 0, 0, split_floats, w8);
+  return one.cost < kv.cost + q.cost;
 }
 
 bool gemm_needs_finish(const GemmArgs &g) {
@@ -1409,8 +1477,12 @@ hipError_t launch_gemm_finish(const GemmArgs &g, hipStream_t s) {
   if (!pl.raw) return hipSuccess;
   const dim3 grid((unsigned)g.M);
   if (g.epi == EPI_SEG) {
-    if (g.dtype == 0) hipLaunchKernelGGL(seg_finish_kernel<float>, grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL(seg_finish_kernel<bf16>, grid, dim3(256), 0, s, p);
+    int first = std::min(p.N, kFinishCols);
+    for (int i = 0; i < p.n_seg; ++i)
+      if (p.dev_cache[i]) first = std::max(i == 0 ? 0 : first, p.nb[i + 1]);
+    const dim3 fgrid((unsigned)g.M, 1 + ceil_div(p.N - first, kFinishCols));
+    if (g.dtype == 0) hipLaunchKernelGGL(seg_finish_kernel<float>, fgrid, dim3(256), 0, s, p, first);
+    else hipLaunchKernelGGL(seg_finish_kernel<bf16>, fgrid, dim3(256), 0, s, p, first);
   } else {
 #define CB_ROW(NC_)                                                                                        \
   do {                                                                                                     \

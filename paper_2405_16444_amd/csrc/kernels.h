@@ -74,6 +74,8 @@ struct GemmArgs {
   const int32_t *a_rows;   // gather: logical row r reads a[a_rows[r]] (NULL: r)
   int a_lo_off;            // bf16 EPI_SEG: > 0 = every row also holds the rounding remainders of its K values,
                            // a_lo_off elements further on; both parts are multiplied (float-accurate input)
+  int n_hl_seg;            // with a_lo_off: the first n_hl_seg segments take both parts, the others the values alone
+                           // (0: every segment takes both)
   int M, K;
   int epi;
   int n_seg;               // EPI_SEG: 1..3 segments; EPI_SWIGLU: seg[0]=gate, seg[1]=up
@@ -99,10 +101,11 @@ struct GemmArgs {
   const int32_t *dev_row;
   float *partial;          // scratch for parked sums (gemm_partial_floats); the K split is capped by it
   size_t partial_floats;
+  size_t split_floats;     // > 0: a smaller cap of the K split than the scratch at hand
 };
 // Floats of scratch a problem of this shape parks its sums in when the scratch is not the limit
 // (0 when the main kernel finishes the outputs itself); N is the total number of output columns
-// (d_ff for EPI_SWIGLU); hl: (high, low) activation pairs; force_raw: a deviation is wanted; w8: int8
+// (d_ff for EPI_SWIGLU); hl: leading output columns with (high, low) activation pairs; force_raw: a deviation is wanted; w8: int8
 // weights (read by the kernel itself where it can).
 // For workspace sizing.
 // whether the projection kernels read int8 weights themselves for this storage type and K (else the caller
@@ -110,6 +113,9 @@ struct GemmArgs {
 bool gemm_int8_in_kernel(int dtype, int K);
 size_t gemm_partial_floats(int dtype, int epi, int M, int N, int K, int hl, int force_raw, int rope_half,
                            int head_dim, int w8 = 0);
+// Whether ONE launch over hl_cols columns with (high, low) pairs and n_rest columns without, all for M rows, is estimated
+// to take less time than a launch per kind, the second for M_rest rows only (bf16 EPI_SEG).  split_floats caps the scratch.
+bool gemm_merge_pays(int M, int hl_cols, int M_rest, int n_rest, int K, int force_raw, int w8, size_t split_floats);
 // Main kernel.  EPI_F32 problems, problems with a deviation, and problems split along K
 // (gemm_needs_finish) leave raw sums in g.partial and must be completed by launch_gemm_finish on
 // the same stream.  EPI_F32 and deviation problems REQUIRE partial_floats >= M * N.
