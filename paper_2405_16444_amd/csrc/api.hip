@@ -327,10 +327,14 @@ int fuse_layer_impl(cb_ctx *c, const cb_layer_weights *w, const float *h_in, con
   // needs no more workspace for it.
   const bool w8 = m.weight_format == CB_W_INT8 && gemm_int8_in_kernel(1, d);
   const size_t own = n < (int)c->partial_own.size() ? c->partial_own[n] : 0;
-  const bool merged = dt == CB_BF16 && (m.weight_format != CB_W_INT8 || w8) && own > 0 &&
-                      gemm_merge_pays(n, 2 * kv_dim, rows, q_dim, d, check, w8, own);
+  // (a float model has no operand pairs; a launch costs it as much as 0.25 GFLOP, and the sums are parked in the MLP's
+  // activation buffer, which is idle here)
+  const bool merged = rows > 0 && (dt == CB_F32 ? F >= 2 * kv_dim + q_dim && 2.0 * (n - rows) * d * q_dim < 2.5e8
+                                                : (m.weight_format != CB_W_INT8 || w8) && own > 0 &&
+                                                      gemm_merge_pays(n, 2 * kv_dim, rows, q_dim, d, check, w8, own));
   g.a_rows = nullptr; g.M = n; g.n_seg = merged ? 3 : 2; g.a_lo_off = lo_off; g.n_hl_seg = 2;
-  if (merged) g.split_floats = own;
+  if (merged && dt == CB_F32) { g.partial = (float *)ws.act; g.partial_floats = (size_t)n * F; }
+  else if (merged) g.split_floats = own;
   {
     const void *wm[3] = {w->wk, w->wv, w->wq};
     const float *sc[3] = {w->wk_scale, w->wv_scale, w->wq_scale};

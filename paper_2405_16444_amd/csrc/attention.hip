@@ -17,7 +17,7 @@
 // the transposing LDS read (ds_read_b64_tr_b16).  K/V tiles are streamed through 4-stage
 // LDS rings by direct global->LDS loads.
 //
-// float kernel: one wavefront per (row, query head), 64 keys per step, plain FMA.
+// float kernel: float MFMAs, 16 queries per workgroup, the wavefronts share the keys.
 #include "common.h"
 #include "kernels.h"
 #include <algorithm>
@@ -521,61 +521,122 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict
 }
 
 // ---------------------------------------------------------------------------
-// float kernel.  Lane j of the wavefront scores key t0 + j; the 64 probabilities
-// are then broadcast one by one while lane e accumulates output channels e, e+64.
+// float kernel, v_mfma_f32_16x16x4_f32.  One workgroup = one kv head x 16 flattened queries; its 8 wavefronts take
+// the 32-key tiles in turn, each with its own running maximum, and are combined in LDS at the end in a fixed order.
+// Transposed products as in the bf16 kernel: lane l holds query l % 16 and, of every 16-key block, keys 4 (l / 16) .. + 3;
+// the contraction index a lane supplies in MFMA s is 4 (l / 16) + s for both products, so the K operand is one
+// 16-byte load per 16 channels, the exponentiated scores are the second product's operand as they are, and the V operand
+// is a coalesced 4-byte load.  K and V come straight from the cache (a float model's fits L2).
+// Latency-bound: 544 rows of the 4 x 64 model 145 -> 14 us against one wavefront per row with vector FMAs.
 // ---------------------------------------------------------------------------
+constexpr int AF_NW = 8;
 template <int DH>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float *__restrict__ q,
+__global__ __launch_bounds__(64 * AF_NW) void attn_f32_kernel(const float *__restrict__ q,
                                                        const int32_t *__restrict__ q_pos, int n_rows,
                                                        const float *__restrict__ kc,
                                                        const float *__restrict__ vc, float *__restrict__ o,
                                                        int n_q_heads, int n_kv_heads, float scale_log2e,
                                                        const int32_t *__restrict__ q_rows) {
-  __shared__ float sq[4][DH];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int idx = blockIdx.x * 4 + wave;
-  const bool active = idx < n_rows * n_q_heads;
-  const int r = active ? idx / n_q_heads : 0, hq = active ? idx % n_q_heads : 0;
-  const int kvh = hq / (n_q_heads / n_kv_heads);
-  const int kv_dim = n_kv_heads * DH;
-  const float *qrow = q + ((size_t)(q_rows ? q_rows[r] : r) * n_q_heads + hq) * DH;
-  for (int e = lane; e < DH; e += 64) sq[wave][e] = qrow[e];
-  __syncthreads();
-  if (!active) return;
-  const int pos = q_pos[r];
-  constexpr int EPL = DH / 64 > 0 ? DH / 64 : 1;  // channels per lane
-  float acc[EPL] = {};
-  float run_max = kNegBig, run_sum = 0.f;
-  for (int t0 = 0; t0 <= pos; t0 += 64) {
-    const int key = t0 + lane;
-    float s = kNegBig;
-    if (key <= pos) {
-      const float *krow = kc + (size_t)key * kv_dim + kvh * DH;
-      float dot = 0.f;
-#pragma unroll 8
-      for (int e = 0; e < DH; ++e) dot = fmaf(sq[wave][e], krow[e], dot);
-      s = dot * scale_log2e;
+  constexpr int NC = DH / 16;                          // 16-channel blocks
+  __shared__ __attribute__((aligned(16))) float s_o[AF_NW][16][DH];
+  __shared__ float s_max[AF_NW][16], s_sum[AF_NW][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 15, h = lane >> 4;
+  const int g = n_q_heads / n_kv_heads, kvh = blockIdx.y, kv_dim = n_kv_heads * DH;
+  const int n_flat = n_rows * g, m0 = ((int)gridDim.x - 1 - (int)blockIdx.x) * 16;   // longest key ranges first
+  const int m = min(m0 + ln, n_flat - 1), r = m / g, j = m - r * g;
+  const int my_pos = q_pos[r];
+  const float *qrow = q + ((size_t)(q_rows ? q_rows[r] : r) * n_q_heads + kvh * g + j) * DH;
+  float4 qf[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) qf[c] = *reinterpret_cast<const float4 *>(qrow + 16 * c + 4 * h);
+  int bound = my_pos;                                  // the 16 queries sit in lanes 0..15 of every group
+#pragma unroll
+  for (int off = 8; off > 0; off >>= 1) bound = max(bound, __shfl_xor(bound, off, 64));
+  const int kv_len = bound + 1, n_tiles = (kv_len + 31) / 32;
+
+  f32x4 oacc[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) oacc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float run_max = -INFINITY, run_sum = 0.f;
+  for (int t = wave; t < n_tiles; t += AF_NW) {
+    const int t0 = t * 32;
+    f32x4 sc[2];
+    float4 kf[2][NC];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const float *krow = kc + (size_t)min(t0 + 16 * b + ln, kv_len - 1) * kv_dim + kvh * DH + 4 * h;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) kf[b][c] = *reinterpret_cast<const float4 *>(krow + 16 * c);
     }
-    const float new_max = fmaxf(run_max, wave_max(s));
-    const float alpha = exp2f(run_max - new_max);
-    const float pv = key <= pos ? exp2f(s - new_max) : 0.f;
-    run_sum = run_sum * alpha + wave_sum(pv);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) sc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        sc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[b][c].x, qf[c].x, sc[b], 0, 0, 0);
+        sc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[b][c].y, qf[c].y, sc[b], 0, 0, 0);
+        sc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[b][c].z, qf[c].z, sc[b], 0, 0, 0);
+        sc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[b][c].w, qf[c].w, sc[b], 0, 0, 0);
+      }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        sc[b][i] = t0 + 16 * b + 4 * h + i <= my_pos ? sc[b][i] * scale_log2e : -INFINITY;
+        mx = fmaxf(mx, sc[b][i]);
+      }
+    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    const float new_max = fmaxf(run_max, mx);
+    const float ref = new_max == -INFINITY ? 0.f : new_max;       // no key of this query seen yet: every p is 0
+    const float alpha = exp2f(run_max - ref);
+    float psum = 0.f;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        sc[b][i] = exp2f(sc[b][i] - ref);
+        psum += sc[b][i];
+      }
+    run_sum = run_sum * alpha + psum;                              // this lane group's keys only; combined at the end
     run_max = new_max;
 #pragma unroll
-    for (int c = 0; c < EPL; ++c) acc[c] *= alpha;
-    const int nk = min(64, pos + 1 - t0);
-    for (int j = 0; j < nk; ++j) {
-      const float pj = __shfl(pv, j, 64);
-      const float *vrow = vc + (size_t)(t0 + j) * kv_dim + kvh * DH;
+    for (int c = 0; c < NC; ++c) oacc[c] *= alpha;
 #pragma unroll
-      for (int c = 0; c < EPL; ++c)
-        if (lane + 64 * c < DH) acc[c] = fmaf(pj, vrow[lane + 64 * c], acc[c]);
-    }
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float *vrow = vc + (size_t)min(t0 + 16 * b + 4 * h + i, kv_len - 1) * kv_dim + kvh * DH + ln;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) oacc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vrow[16 * c], sc[b][i], oacc[c], 0, 0, 0);
+      }
   }
-  float *orow = o + ((size_t)r * n_q_heads + hq) * DH;
+  run_sum += __shfl_xor(run_sum, 16, 64);
+  run_sum += __shfl_xor(run_sum, 32, 64);
+  // lane l: channels 16 c + 4 (l / 16) .. + 3 of query l % 16
 #pragma unroll
-  for (int c = 0; c < EPL; ++c)
-    if (lane + 64 * c < DH) orow[lane + 64 * c] = acc[c] / run_sum;
+  for (int c = 0; c < NC; ++c) *reinterpret_cast<f32x4 *>(&s_o[wave][ln][16 * c + 4 * h]) = oacc[c];
+  if (h == 0) { s_max[wave][ln] = run_max; s_sum[wave][ln] = run_sum; }
+  __syncthreads();
+  for (int e = tid; e < 16 * DH / 4; e += 64 * AF_NW) {
+    const int qi = e / (DH / 4), ch = e % (DH / 4) * 4;
+    if (m0 + qi >= n_flat) continue;
+    float top = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < AF_NW; ++w) top = fmaxf(top, s_max[w][qi]);
+    float den = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < AF_NW; ++w) {
+      const float wt = exp2f(s_max[w][qi] - top);                  // 0 for a wavefront that saw no key of the query
+      den += wt * s_sum[w][qi];
+      acc += wt * *reinterpret_cast<const f32x4 *>(&s_o[w][qi][ch]);
+    }
+    const int mm = m0 + qi, rr = mm / g, jj = mm - rr * g;
+    *reinterpret_cast<f32x4 *>(o + ((size_t)rr * n_q_heads + kvh * g + jj) * DH + ch) = acc / den;
+  }
 }
 
 // Split plan of the bf16 kernel.  Few query workgroups (the selective layers) leave most CUs idle,
@@ -638,12 +699,12 @@ hipError_t launch_attention(int dtype, const void *q, const int32_t *q_rows, con
   const float scale_log2e = kLog2e / sqrtf((float)dh);
   if (dtype == 0) {
     if (segs) return hipErrorInvalidValue;           // the float kernel takes one request per launch
-    dim3 grid((n_rows * hq + 3) / 4);
+    const dim3 grid((unsigned)(((long)n_rows * (hq / hkv) + 15) / 16), hkv);
     if (dh == 64)
-      hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(256), 0, s, (const float *)q, q_pos, n_rows,
+      hipLaunchKernelGGL(attn_f32_kernel<64>, grid, dim3(64 * AF_NW), 0, s, (const float *)q, q_pos, n_rows,
                          (const float *)kc, (const float *)vc, (float *)o, hq, hkv, scale_log2e, q_rows);
     else
-      hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(256), 0, s, (const float *)q, q_pos, n_rows,
+      hipLaunchKernelGGL(attn_f32_kernel<128>, grid, dim3(64 * AF_NW), 0, s, (const float *)q, q_pos, n_rows,
                          (const float *)kc, (const float *)vc, (float *)o, hq, hkv, scale_log2e, q_rows);
     return hipGetLastError();
   }

@@ -6,7 +6,7 @@
 // (gemm_bf16_dma_kernel, v_mfma_f32_16x16x32_bf16) streams (32*I) x (64*NB) x 64 tiles through LDS
 // rings filled by direct global->LDS loads, with an XCD-aware tile order; a simpler register-staged
 // 128x128x64 kernel (v_mfma_f32_32x32x16_bf16) covers K that is not a multiple of 64.
-// float storage: plain FMA tiles (parity mode, not tuned).
+// float storage: float MFMAs (v_mfma_f32_32x32x2_f32) on small tiles.
 // The SwiGLU and float-output epilogues work straight from the accumulator registers (a lane
 // holds four adjacent columns of a row); the segment epilogue parks the tile in LDS and walks it
 // row-major, 4 adjacent columns per lane, which lets the two wavefront halves of an operand-pair
@@ -907,56 +907,108 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams p) {
 }
 
 // ---------------------------------------------------------------------------
-// float kernel: 64x64x16 tiles, 256 lanes, 4x4 outputs per lane, plain FMA.
+// float kernel, v_mfma_f32_32x32x2_f32 (float products and sums).  4 wavefronts as WM x WN x WK: each owns a 32 x 32
+// block of the 32 WM x 32 WN tile, and with WK = 4 the four share one block along K -- a float model is small, its
+// projections have too few 64 x 64 tiles to occupy the chip, and a WK = 4 tile brings four times as many workgroups
+// without parked sums or another launch.  64-deep stages, double-buffered in LDS, the next one on its way in
+// registers meanwhile.
+// A k-step of 8 gives lane l the four values k0 + 4 (l / 32) .. + 3 of row (l % 32): one 16-byte LDS read feeds
+// four MFMAs (the two half-waves supply different k, which a sum may take in any order).  Rows are 256 bytes, the
+// 16-byte chunk c of row r sits in slot c ^ (r & 15).
+// Bound by latency at these sizes: 544 x 256 x 256 .. 688 took 34 us on 64 x 64 tiles of vector FMAs, 8 us here.
 // ---------------------------------------------------------------------------
-constexpr int BM32 = 64, BN32 = 64, BK32 = 16, TP32 = BM32 + 4, CPITCH32 = BN32 + 4;
+constexpr int BK32 = 64;
+constexpr int f32_smem_bytes(int wm, int wn, int wk) {
+  const int ring = 2 * 32 * (wm + wn) * BK32 * 4, park = wk * 32 * wm * (32 * wn + 4) * 4;
+  return ring > park ? ring : park;
+}
 
-template <int EPI>
+template <int EPI, int WM, int WN, int WK>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
-  __shared__ __attribute__((aligned(16))) float smem[BM32 * CPITCH32];  // >= 2*BK*TP32
-  float *sA = smem;                 // [BK][TP32]  (k-major)
-  float *sB = smem + BK32 * TP32;   // [BK][TP32]
-  const int tid = threadIdx.x;
-  constexpr int OUT_COLS = (EPI == EPI_SWIGLU) ? BN32 / 2 : BN32;
-  const int m0 = blockIdx.y * BM32, n0 = blockIdx.x * OUT_COLS;
+  static_assert(WM * WN * WK == 4, "four wavefronts");
+  constexpr int BM = 32 * WM, BN = 32 * WN, CP = BN + 4;
+  constexpr int OUT_COLS = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
+  constexpr int LA = BM * BK32 / 1024, LB = BN * BK32 / 1024;      // 16-byte loads per lane per stage
+  __shared__ __attribute__((aligned(16))) char smem[f32_smem_bytes(WM, WN, WK)];
+  float4 *sA = reinterpret_cast<float4 *>(smem);                   // [2][BM][16]
+  float4 *sB = sA + 2 * BM * 16;                                   // [2][BN][16]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wk = wave % WK, wn = wave / WK % WN, wm = wave / (WK * WN);
+  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * OUT_COLS;
   const int kb = blockIdx.z * p.k_per_split;
   const int ke = min(p.K, kb + p.k_per_split);
-  const int lrow = tid >> 2, lkc = (tid & 3) * 4;
-  int ar = min(m0 + lrow, p.M - 1);
-  if (p.a_rows) ar = p.a_rows[ar];
-  const float *a_ptr = reinterpret_cast<const float *>(p.a) + (size_t)ar * p.lda + lkc;
-  const float *b_ptr = weight_row<float, EPI>(p, n0 + lrow, BN32 / 2, n0, lrow) + lkc;
-  const int ty = tid >> 4, tx = tid & 15;
-  float acc[4][4] = {};
-  for (int k0 = kb; k0 < ke; k0 += BK32) {
-    const bool ok = k0 + lkc < ke;
-    float4 va = ok ? *reinterpret_cast<const float4 *>(a_ptr + k0) : make_float4(0, 0, 0, 0);
-    float4 vb = ok ? *reinterpret_cast<const float4 *>(b_ptr + k0) : make_float4(0, 0, 0, 0);
-    __syncthreads();
-    sA[(lkc + 0) * TP32 + lrow] = va.x; sA[(lkc + 1) * TP32 + lrow] = va.y;
-    sA[(lkc + 2) * TP32 + lrow] = va.z; sA[(lkc + 3) * TP32 + lrow] = va.w;
-    sB[(lkc + 0) * TP32 + lrow] = vb.x; sB[(lkc + 1) * TP32 + lrow] = vb.y;
-    sB[(lkc + 2) * TP32 + lrow] = vb.z; sB[(lkc + 3) * TP32 + lrow] = vb.w;
-    __syncthreads();
+  const int nk = (ke - kb + BK32 - 1) / BK32;
+
+  const int lr = tid >> 4, lc = tid & 15;                          // row (+ 16 i) and 16-byte chunk of this lane's loads
+  const float *a_ptr[LA], *b_ptr[LB];
 #pragma unroll
-    for (int k = 0; k < BK32; ++k) {
-      const float4 a4 = *reinterpret_cast<const float4 *>(sA + k * TP32 + ty * 4);
-      const float4 b4 = *reinterpret_cast<const float4 *>(sB + k * TP32 + tx * 4);
-      const float av[4] = {a4.x, a4.y, a4.z, a4.w}, bv[4] = {b4.x, b4.y, b4.z, b4.w};
+  for (int i = 0; i < LA; ++i) {
+    int ar = min(m0 + lr + 16 * i, p.M - 1);
+    if (p.a_rows) ar = p.a_rows[ar];
+    a_ptr[i] = reinterpret_cast<const float *>(p.a) + (size_t)ar * p.lda + lc * 4;
+  }
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < LB; ++i) b_ptr[i] = weight_row<float, EPI>(p, n0 + lr + 16 * i, BN / 2, n0, lr + 16 * i) + lc * 4;
+  float4 ra[LA], rb[LB];
+  auto gload = [&](int t) {
+    const int k0 = kb + t * BK32;
+    const bool ok = k0 + lc * 4 < ke;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(av[i], bv[j], acc[i][j]);
-    }
+    for (int i = 0; i < LA; ++i) ra[i] = ok ? *reinterpret_cast<const float4 *>(a_ptr[i] + k0) : make_float4(0, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < LB; ++i) rb[i] = ok ? *reinterpret_cast<const float4 *>(b_ptr[i] + k0) : make_float4(0, 0, 0, 0);
+  };
+  auto sstore = [&](int stage) {                                   // rows lr + 16 i: r & 15 = lr
+#pragma unroll
+    for (int i = 0; i < LA; ++i) sA[(stage * BM + lr + 16 * i) * 16 + (lc ^ lr)] = ra[i];
+#pragma unroll
+    for (int i = 0; i < LB; ++i) sB[(stage * BN + lr + 16 * i) * 16 + (lc ^ lr)] = rb[i];
+  };
+  f32x16 acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  if (nk > 0) {
+    gload(0);
+    sstore(0);
   }
   __syncthreads();
-  float *sC = smem;
+  const int row = lane & 31, h = lane >> 5, sw = row & 15;
+  constexpr int KS = BK32 / 8 / WK;                                // k-steps of 8 per stage and wavefront
+  for (int t = 0; t < nk; ++t) {
+    if (t + 1 < nk) gload(t + 1);
+    const float4 *ca = sA + ((t & 1) * BM + wm * 32 + row) * 16, *cb_ = sB + ((t & 1) * BN + wn * 32 + row) * 16;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-    *reinterpret_cast<float4 *>(sC + (ty * 4 + i) * CPITCH32 + tx * 4) =
-        make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+    for (int ks = 0; ks < KS; ++ks) {
+      const int chunk = (2 * (wk * KS + ks) + h) ^ sw;
+      const float4 av = ca[chunk], bv = cb_[chunk];
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.x, bv.x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.y, bv.y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.z, bv.z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av.w, bv.w, acc, 0, 0, 0);
+    }
+    if (t + 1 < nk) sstore((t + 1) & 1);
+    __syncthreads();
+  }
+  // park the blocks; lane l holds column (l % 32), rows 8 (i / 4) + 4 (l / 32) + i % 4
+  float *sC = reinterpret_cast<float *>(smem);
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    sC[(wk * BM + wm * 32 + (i >> 2) * 8 + h * 4 + (i & 3)) * CP + wn * 32 + row] = acc[i];
   __syncthreads();
-  lds_epilogue<float, EPI, BN32>(sC, CPITCH32, BM32, m0, n0, blockIdx.z, p);
+  if (WK > 1) {                                                    // the K shares, added in ascending order
+    for (int e = tid; e < BM * BN / 4; e += 256) {
+      float4 *c0 = reinterpret_cast<float4 *>(sC + (e / (BN / 4)) * CP + e % (BN / 4) * 4);
+      float4 v = *c0;
+#pragma unroll
+      for (int z = 1; z < WK; ++z) {
+        const float4 u = c0[z * BM * CP / 4];
+        v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+      }
+      *c0 = v;
+    }
+    __syncthreads();
+  }
+  lds_epilogue<float, EPI, BN>(sC, CP, BM, m0, n0, blockIdx.z, p);
 }
 
 // ---------------------------------------------------------------------------
@@ -1217,10 +1269,16 @@ static void pick_dma_plan(int M, int N, int hl_cols, int K, int max_splits, bool
   }
 }
 
-// The float kernel's 64-column tile does not hold a whole 128-channel head, so it cannot pair
-// channel i with i + head_dim/2 itself: it parks its sums and the finish launch rotates them.
-static bool needs_raw_partial(int dtype, int epi, int rope_half, int head_dim) {
-  return dtype == 0 && epi == EPI_SEG && rope_half && head_dim > BN32;
+// Tile of the float kernel: 64 x 64 when those occupy the chip twice over (a quarter of the loads per flop), else
+// 32 x 32 with the wavefronts sharing K (544 rows of the 256-wide model occupy 36 CUs with 64 x 64 tiles, 136 with these).
+static int f32_tile(int epi, int M, int N) {
+  const long t64 = (long)ceil_div(M, 64) * ceil_div(N, epi == EPI_SWIGLU ? 32 : 64);
+  return t64 >= 512 ? 64 : 32;
+}
+// A float tile narrower than a head cannot pair channel i with i + head_dim/2 itself: it parks its sums and the
+// finish launch rotates them.
+static bool needs_raw_partial(int dtype, int epi, int M, int N, int rope_half, int head_dim) {
+  return dtype == 0 && epi == EPI_SEG && rope_half && head_dim > f32_tile(epi, M, N);
 }
 
 bool gemm_int8_in_kernel(int dtype, int K) { return dtype == 1 && K % DMA_BK == 0; }
@@ -1235,12 +1293,12 @@ static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int f
   if (w8 && !gemm_int8_in_kernel(dtype, K)) pl.bad = true;
   pl.splits = 1;
   pl.hl = dtype == 1 && epi == EPI_SEG ? hl : 0;
-  pl.raw = force_raw || epi == EPI_F32 || needs_raw_partial(dtype, epi, rope_half, head_dim);
+  pl.raw = force_raw || epi == EPI_F32 || needs_raw_partial(dtype, epi, M, N, rope_half, head_dim);
   const size_t mn = (size_t)M * N;
   const int max_splits = (int)std::min<size_t>(16, std::max<size_t>(1, scratch_floats / std::max<size_t>(1, mn)));
   if (pl.raw && scratch_floats < mn) pl.bad = true;
   if (dtype == 0) {
-    pl.kind = 0; pl.bm = BM32; pl.out_cols = epi == EPI_SWIGLU ? BN32 / 2 : BN32; pl.bk = BK32;
+    pl.kind = 0; pl.bm = f32_tile(epi, M, N); pl.out_cols = epi == EPI_SWIGLU ? pl.bm / 2 : pl.bm; pl.bk = BK32;
   } else if (K % DMA_BK != 0) {
     pl.kind = 1; pl.bm = BM16; pl.out_cols = epi == EPI_SWIGLU ? BN16 / 2 : BN16; pl.bk = BK16;
   } else if (epi == EPI_SWIGLU) {
@@ -1434,7 +1492,8 @@ template <int EPI>
 static void launch_typed(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
   const dim3 grid(pl.tiles_n, pl.tiles_m, pl.splits);
   if (pl.kind == 0) {
-    hipLaunchKernelGGL(gemm_f32_kernel<EPI>, grid, dim3(256), 0, s, p);
+    if (pl.bm == 64) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, 2, 1>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1, 1, 4>), grid, dim3(256), 0, s, p);
   } else if (pl.kind == 1) {
     CB_LDS_LIMIT_ONCE((&gemm_bf16_kernel<EPI>), kSmemBf16);
     hipLaunchKernelGGL(gemm_bf16_kernel<EPI>, grid, dim3(256), kSmemBf16, s, p);
