@@ -31,7 +31,8 @@ struct cb_ctx {
   cb_model_desc m;
   int max_tokens;
   int device;
-  float2 *rope_tab;  // device [max_tokens][head_dim/2]
+  float2 *rope_tab;  // device [max_tokens][head_dim/2], followed by the two integers of `pick`
+  unsigned long long *pick;              // device scratch of the greedy pick (cb_first_token); zero between calls
   int profiling;                         // 0 off, 1 every launch and the two phases, 2 the two phases only
   std::vector<ProfRec> recs;
   std::vector<hipEvent_t> free_events;
@@ -527,6 +528,7 @@ int cb_create(const cb_model_desc *desc, int32_t max_tokens, cb_ctx **out) {
   std::vector<float2> tab;
   std::vector<double> freq;
   try {
+    tab.reserve((size_t)max_tokens * half + 2);
     tab.resize((size_t)max_tokens * half);
     freq.resize(half);
   } catch (...) {                       // no exception may cross the C boundary
@@ -539,7 +541,9 @@ int cb_create(const cb_model_desc *desc, int32_t max_tokens, cb_ctx **out) {
       const double a = (double)p * freq[i];
       tab[(size_t)p * half + i] = make_float2((float)std::cos(a), (float)std::sin(a));
     }
+  tab.resize(tab.size() + 2, make_float2(0.f, 0.f));
   if (hipMalloc(&c->rope_tab, tab.size() * sizeof(float2)) != hipSuccess) { delete c; return CB_ENOMEM; }
+  c->pick = reinterpret_cast<unsigned long long *>(c->rope_tab + (tab.size() - 2));
   if (hipMemcpy(c->rope_tab, tab.data(), tab.size() * sizeof(float2), hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipFree(c->rope_tab);
     delete c;
@@ -986,15 +990,9 @@ int cb_first_token(cb_ctx *c, const float *final_hidden, int32_t n_suffix, const
   if (d % 8 != 0 || d > 16384) return CB_EUNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
   const size_t es = esize(c);
-  {
-    ProfScope ps(c, s, CB_PROF_HEAD, 2.0 * vocab * d, (double)vocab * d * es + (double)vocab * 4);
-    CB_HIP(launch_lm_head(c->m.dtype, final_hidden + (size_t)(n_suffix - 1) * d, final_norm, lm_head, d, vocab,
-                          c->m.rms_eps, logits, s));
-  }
-  {
-    ProfScope ps(c, s, CB_PROF_HEAD, 0, (double)vocab * 4);
-    CB_HIP(launch_argmax(logits, vocab, token, s));
-  }
+  ProfScope ps(c, s, CB_PROF_HEAD, 2.0 * vocab * d, (double)vocab * d * es + (double)vocab * 4);
+  CB_HIP(launch_lm_head(c->m.dtype, final_hidden + (size_t)(n_suffix - 1) * d, final_norm, lm_head, d, vocab,
+                        c->m.rms_eps, logits, token, c->pick, s));
   return CB_OK;
 }
 

@@ -146,10 +146,9 @@ long attention_query_workgroups(int n_rows, int n_q_heads, int n_kv_heads);
 
 // ---- head.hip ---------------------------------------------------------------
 // logits[v] = T(rmsnorm(h_row) * gain) . w[v, :], v < vocab; w row-major [vocab, d]; d % 8 == 0,
-// d <= 16384 (the normalised row is held in LDS).
+// d <= 16384 (the normalised row is held in LDS).  token[0] = smallest index among the largest logits.
+// pick: device uint64[2], zero before the first call and left zero by every call; calls that share it must not overlap.
 hipError_t launch_lm_head(int dtype, const float *h_row, const void *gain, const void *w, int d, int vocab,
-                          float eps, float *logits, hipStream_t s);
-// token[0] = smallest index among the largest of logits[0..n).
-hipError_t launch_argmax(const float *logits, int n, int32_t *token, hipStream_t s);
+                          float eps, float *logits, int32_t *token, unsigned long long *pick, hipStream_t s);
 
 }  // namespace cb
