@@ -285,11 +285,13 @@ int run_gemm(cb_ctx *c, hipStream_t s, const GemmArgs &g, int finish_class, doub
 // xn_ready: ws.xn already holds the normalised input rows (left there by the previous layer's
 // call through next_gain).  next_gain (NULL: none): gain of the RMSNorm that will read h_out;
 // the normalised rows are then left in ws.xn by the launch that finishes h_out.
+// kv_only: nothing will read h_out (the last layer of a call without query rows): the layer ends once
+// its keys and values are in the cache.
 int fuse_layer_impl(cb_ctx *c, const cb_layer_weights *w, const float *h_in, const int32_t *row_pos,
                     const int32_t *cache_row, const Seg *segs, int n_segs, size_t cache_stride, void *kc,
                     void *vc, const int32_t *forced, float *h_out, int32_t *pos_out, int32_t *cache_row_out,
                     float *dev_out, const LayerWs &ws, hipStream_t s, bool xn_ready, const void *next_gain,
-                    const int32_t *seg_dev = nullptr) {
+                    bool kv_only, const int32_t *seg_dev = nullptr) {
   const cb_model_desc &m = c->m;
   const int dt = m.dtype;
   const size_t es = esize(c);
@@ -330,7 +332,7 @@ int fuse_layer_impl(cb_ctx *c, const cb_layer_weights *w, const float *h_in, con
   const size_t own = n < (int)c->partial_own.size() ? c->partial_own[n] : 0;
   // (a float model has no operand pairs; a launch costs it as much as 0.25 GFLOP, and the sums are parked in the MLP's
   // activation buffer, which is idle here)
-  const bool merged = rows > 0 && (dt == CB_F32 ? F >= 2 * kv_dim + q_dim && 2.0 * (n - rows) * d * q_dim < 2.5e8
+  const bool merged = rows > 0 && !kv_only && (dt == CB_F32 ? F >= 2 * kv_dim + q_dim && 2.0 * (n - rows) * d * q_dim < 2.5e8
                                                 : (m.weight_format != CB_W_INT8 || w8) && own > 0 &&
                                                       gemm_merge_pays(n, 2 * kv_dim, rows, q_dim, d, check, w8, own));
   g.a_rows = nullptr; g.M = n; g.n_seg = merged ? 3 : 2; g.a_lo_off = lo_off; g.n_hl_seg = 2;
@@ -397,6 +399,7 @@ int fuse_layer_impl(cb_ctx *c, const cb_layer_weights *w, const float *h_in, con
     g.seg[1] = {wv.w[1], kv_dim, vc, kv_dim, crow, 0, nullptr, wv.scale[1]};
     CB_TRY(run_gemm(c, s, g, CB_PROF_REDUCE, kv_flops, kv_bytes, 0));
   }
+  if (kv_only) return CB_OK;
   if (!merged) {
     g.a_rows = sel_rows; g.M = rows; g.n_seg = 1; g.a_lo_off = 0; g.n_hl_seg = 0;
     const void *wm[1] = {w->wq};
@@ -637,7 +640,7 @@ int cb_fuse_layer(cb_ctx *c, int32_t layer, const cb_layer_weights *w, const flo
   if (ws.bytes > workspace_bytes) return CB_EWORKSPACE;
   const Seg seg = {n_rows, n_suffix, k_keep, n_tokens_total};
   return fuse_layer_impl(c, w, h_in, row_pos, nullptr, &seg, 1, 0, k_cache, v_cache, forced_sel, h_out, pos_out,
-                         nullptr, dev_out, ws, (hipStream_t)stream, false, nullptr);
+                         nullptr, dev_out, ws, (hipStream_t)stream, false, nullptr, false);
 }
 
 size_t cb_static_scratch_bytes(void) { return CB_STATIC_SCRATCH_BYTES; }
@@ -768,7 +771,7 @@ int prefill_impl(cb_ctx *c, const cb_layer_weights *layers, const void *x, const
     // the launch that finishes a layer's output also normalises it for the next layer
     st = fuse_layer_impl(c, &layers[l], h_cur, p_cur, nullptr, &seg, 1, 0, k_cache_layers[l], v_cache_layers[l],
                          forced, h_nxt, p_nxt, nullptr, dev_out, ws, s, l > 0,
-                         l + 1 < L ? layers[l + 1].attn_norm : nullptr);
+                         l + 1 < L ? layers[l + 1].attn_norm : nullptr, n_suffix == 0 && l + 1 == L);
     if (st != CB_OK) return st;
     if (sel_dump && sel_dump[l] && k > 0)
       CB_HIP(hipMemcpyAsync(sel_dump[l], p_nxt, (size_t)k * 4, hipMemcpyDeviceToDevice, s));
@@ -944,7 +947,7 @@ int cb_fuse_prefill_batched(cb_ctx *c, const cb_layer_weights *layers, int32_t n
     int st = fuse_layer_impl(c, &layers[l], h_cur, p_cur, r_cur, segs.data(), B, (size_t)cache_stride,
                              k_cache_layers[l], v_cache_layers[l], nullptr, h_nxt, p_nxt, r_nxt,
                              dev_dump ? dev_dump[l] : nullptr, ws, s, l > 0,
-                             l + 1 < L ? layers[l + 1].attn_norm : nullptr,
+                             l + 1 < L ? layers[l + 1].attn_norm : nullptr, total_suffix == 0 && l + 1 == L,
                              B > 1 ? seg_tab + (size_t)l * (B + 1) * kSegInts : nullptr);
     if (st != CB_OK) return st;
     int o = 0;

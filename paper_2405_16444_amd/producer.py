@@ -1,6 +1,7 @@
 """Producer of the pre-computed chunk caches KV^pre (paper Sec. 4.1): every chunk is
 prefilled alone at positions 0.. .  This is the step *before* the fusing path and is
-not timed; it drives the same cb_fuse_layer entry point with every row kept."""
+not part of a request's time.  A chunk is a fusing pass of its own that keeps every row and has no query
+rows: one cb_fuse_prefill call, which leaves out the part of the last layer that no key or value depends on."""
 from __future__ import annotations
 
 from typing import Dict, Sequence
@@ -15,19 +16,28 @@ def chunk_prefill(ctx: B.Context, layers: Sequence[Dict[str, torch.Tensor]], x_c
     """Returns (k_layers, v_layers): per layer a [n_rows_alloc, Hkv, dh] tensor whose
     rows [0, sum(chunk_lens)) hold the chunks' K/V as cached at positions 0.. ."""
     m = ctx.model
-    dev = ctx.device
-    ks = [torch.zeros((n_rows_alloc, m.n_kv_heads, m.head_dim), dtype=ctx.dtype, device=dev)
-          for _ in range(m.n_layers)]
-    vs = [torch.zeros_like(k) for k in ks]
-    max_len = max(chunk_lens)
-    ws = torch.empty(B.cb_layer_workspace_bytes(ctx, max_len), dtype=torch.uint8, device=dev)
-    o = 0
+    n_ctx = sum(chunk_lens)
+    # one allocation for all layers; the chunks fill rows [0, n_ctx), only the rest has to be cleared
+    kv = torch.empty((2 * m.n_layers, n_rows_alloc, m.n_kv_heads, m.head_dim), dtype=ctx.dtype, device=ctx.device)
+    if n_rows_alloc > n_ctx:
+        kv[:, n_ctx:] = 0
+    caches = list(kv)
+    ks, vs = caches[:m.n_layers], caches[m.n_layers:]
+    ws = torch.empty(B.cb_prefill_workspace_bytes(ctx, max(chunk_lens)), dtype=torch.uint8, device=ctx.device)
+    structs, o = None, 0
     for ln in chunk_lens:
-        h = x_ctx[o:o + ln].to(torch.float32).contiguous()
-        pos = torch.arange(ln, dtype=torch.int32, device=dev)
-        for l in range(m.n_layers):
-            # the chunk's cache rows are a contiguous slice, addressed as a cache of ln tokens
-            h, _, _ = B.cb_fuse_layer(ctx, l, layers[l], h, pos, 0, ks[l][o:o + ln], vs[l][o:o + ln],
-                                      ln, workspace=ws)
+        # the chunk's cache rows are a contiguous slice, addressed as a cache of ln tokens
+        kc, vc = [k[o:o + ln] for k in ks], [v[o:o + ln] for v in vs]
+        x = x_ctx[o:o + ln]
         o += ln
+        if x.dtype == ctx.dtype:
+            out = B.cb_fuse_prefill(ctx, layers, x.contiguous(), [ln], 0, kc, vc, [ln] * m.n_layers, workspace=ws,
+                                    weight_structs=structs)
+            structs = out.weight_structs
+            continue
+        # an input of another precision than the model's storage type is not rounded to it: layer by layer
+        h = x.to(torch.float32).contiguous()
+        pos = torch.arange(ln, dtype=torch.int32, device=ctx.device)
+        for l in range(m.n_layers):
+            h, _, _ = B.cb_fuse_layer(ctx, l, layers[l], h, pos, 0, kc[l], vc[l], ln, workspace=ws)
     return ks, vs
