@@ -206,18 +206,16 @@ __device__ __forceinline__ void lds_epilogue(const float *sC, int pitch, int row
 // ---------------------------------------------------------------------------
 // Main bf16 kernel.
 //   tile        BM = 32*I rows (I = 2,4,6,8) x BN = 64*NB columns (NB = 4, or 2 when that
-//               fills the CUs better) x 64 k per stage (128-byte
+//               fills the CUs better or few rows leave the weights as the bound) x 64 k per stage (128-byte
 //               rows: every global request is a whole cache line)
-//   wavefronts  NWV = 4 as 2 x 2 (128-column tiles; two such workgroups share a CU when the
-//               rings fit twice) or NWV = 8 as 2 x 4 (256-column tiles: two wavefronts per
+//   wavefronts  NWV = 4 as 2 x 2 (128-column tiles) or NWV = 8 as 2 x 4 (256-column tiles: two wavefronts per
 //               SIMD, each (BM/2) x 64).  A wavefront's sub-tile is cut into 16 x 16 blocks, one
 //               v_mfma_f32_16x16x32_bf16 each per 32-deep k-step.  Operand reads are issued by
 //               hand (inline ds_read_b128 + explicit s_waitcnt lgkmcnt) one half-step (half of
 //               the wavefront's rows of one k-step) ahead of the MFMAs that use them, slotted
 //               between those MFMAs.
-//   LDS rings   activation tile (BM rows x 128 bytes): 2 stages; weight tile (256 rows x
-//               128 bytes): the 3-4 stages that still fit in 160 KB -- weights stream
-//               from HBM once and need the deeper queue, activations mostly hit L2.
+//   LDS rings   activation tile (BM rows x 128 bytes) and weight tile (BN rows x 128 bytes), as
+//               many stages of both as fit in 160 KB, up to 6 (dma_even_stages below).
 //               Both are filled by global_load_lds_dwordx4 (no register staging).  A
 //               wavefront-wide load writes 1 KB contiguously (lane l -> byte 16*l),
 //               i.e. 8 rows x 8 chunks; lane l fetches global chunk (l%8) ^ f(row) of
@@ -241,28 +239,36 @@ __device__ __forceinline__ void lds_epilogue(const float *sC, int pitch, int row
 // Requires K % 64 == 0 and k_per_split % 64 == 0.
 // ---------------------------------------------------------------------------
 constexpr int DMA_BK = 64;
-// Two rings: the activation tile (mostly L2 hits) is double-buffered, the weight tile (streamed
-// from HBM, long latency) gets every remaining stage that fits in 160 KB, up to 4.
-constexpr int DMA_SA = 2;
-// w8: int8 weights, 64 bytes per weight row and stage instead of 128, so up to 6 stages fit.
+// Stages of the two rings.  The waits count outstanding loads in issue order, so the depth that counts is that of the
+// SHALLOWER ring: once a wavefront waits for its youngest needed activation tile, every weight tile requested before
+// that has to be there too.  Both rings are therefore equally deep wherever the tile leaves room for three stages or more
+// (all 128-column tiles, the 256-column ones up to 128 rows, and every tile over int8 weights); the two tall bf16 tiles
+// keep two activation stages and three weight stages, their k-tiles last as long as a load takes.  With two activation
+// stages everywhere (and 80 KB rings, two workgroups per CU, for the small tiles) a weight tile was never more than one
+// k-tile ahead.  Launch with finish, bf16, before -> after: gate/up 28672 x 4096 at 64 / 128 / 256 rows 57 -> 54, 61 -> 58,
+// 76 -> 67 us, at 640 rows of 57344 x 8192 603 -> 554 us; down 4096 x 14336 at 64 / 128 / 256 rows 36 -> 32, 41 -> 37, 51 -> 46 us;
+// int8 gate/up 57344 x 8192 at 64 / 165 / 300 rows 146 -> 130, 192 -> 166, 356 -> 315 us.
+// w8: int8 weights, 64 bytes per weight row and stage instead of 128 (the smallest tile: 80 KB, two workgroups per CU).
+constexpr int dma_even_stages(int I, int BN, bool w8) {
+  const int n = 160 * 1024 / (32 * I * 128 + BN * (w8 ? 64 : 128)), most = w8 && I == 2 && BN == 128 ? 5 : 6;
+  return n > most ? most : n;
+}
+constexpr int dma_a_stages(int I, int BN, bool w8 = false) {
+  return dma_even_stages(I, BN, w8) >= 3 ? dma_even_stages(I, BN, w8) : 2;
+}
 constexpr int dma_w_stages(int I, int BN, bool w8 = false) {
-  const int stage = BN * (w8 ? 64 : 128), cap = w8 ? 6 : 4;
-  if (BN == 128 && I <= 4) {                           // <= 80 KB: two workgroups per CU
-    const int n = (80 * 1024 - DMA_SA * 32 * I * 128) / stage;
-    return w8 ? (n > cap ? cap : n) : 3;
-  }
-  const int left = 160 * 1024 - DMA_SA * 32 * I * 128;
-  return left / stage > cap ? cap : left / stage;
+  return dma_even_stages(I, BN, w8) >= 3 ? dma_even_stages(I, BN, w8) : 3;
 }
 constexpr int dma_smem_bytes(int I, int BN, bool w8 = false) {
-  const int ring = DMA_SA * 32 * I * 128 + dma_w_stages(I, BN, w8) * BN * (w8 ? 64 : 128);
+  const int ring = dma_a_stages(I, BN, w8) * 32 * I * 128 + dma_w_stages(I, BN, w8) * BN * (w8 ? 64 : 128);
   const int park = (I < 4 ? 32 * I : 128) * (BN + 4) * 4;
   return ring > park ? ring : park;
 }
 
-#define CB_GLDS16(gptr, lptr)                                                              \
+#define CB_GLDS16(gptr, lptr, cache)                                                       \
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr), \
-                                   (__attribute__((address_space(3))) void *)(lptr), 16, 0, 0)
+                                   (__attribute__((address_space(3))) void *)(lptr), 16, 0, cache)
+constexpr int kCacheNt = 2;                            // the instruction's nt bit
 
 // LDS operand read issued by hand: the result registers are valid only after a matching
 // lds_wait<N>() (N = number of younger reads that may still be in flight).
@@ -384,17 +390,19 @@ __global__ __launch_bounds__(256) void swiglu_tail_kernel(GemmParams p, int tile
 // other columns (Q beside K and V in one launch) are ordinary ones; which kind a workgroup has is uniform.
 // W8: the weights are int8 (one byte per element in memory and in LDS, half the traffic of both); a fragment
 // is expanded to bf16 in registers right before its k-step and the per-column scales multiply the finished sums.
-template <int I, int NB, int EPI, int NWV, bool HL = false, bool W8 = false>
+// NT: the weight loads are non-temporal (GemmPlan::nt).
+template <int I, int NB, int EPI, int NWV, bool HL = false, bool W8 = false, bool NT = false>
 __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
-  constexpr int BM = 32 * I, BN = 64 * NB, SW = dma_w_stages(I, BN, W8), DMA_CP = BN + 4;
+  constexpr int BM = 32 * I, BN = 64 * NB, SA = dma_a_stages(I, BN, W8), SW = dma_w_stages(I, BN, W8), DMA_CP = BN + 4;
   constexpr int WE = W8 ? 1 : 2;                         // bytes per weight element
   static_assert(!HL || EPI == EPI_SEG, "operand pairs are for the K/V projection only");
-  constexpr int A_STAGE = BM * 128, W_STAGE = BN * 64 * WE, W_RING = DMA_SA * A_STAGE;
+  constexpr int A_STAGE = BM * 128, W_STAGE = BN * 64 * WE, W_RING = SA * A_STAGE;
   constexpr int WN = NWV / 2;                            // wavefronts as 2 x WN
   constexpr int NBW = 2 * NB / WN;                       // 32-column groups per wavefront
   constexpr int LA = BM / (8 * NWV), LW = W_STAGE / (1024 * NWV);   // 16-byte loads per lane per tile (1 KB per wavefront each)
   static_assert(LW >= 2 && LW % 2 == 0, "the load schedule issues a weight tile in two halves");
-  static_assert(SW >= 3, "the vmcnt bookkeeping below assumes at least 3 weight stages");
+  static_assert(SA >= 2 && SW >= SA, "the vmcnt bookkeeping below");
+  static_assert(dma_smem_bytes(I, BN, W8) <= 160 * 1024, "LDS of a CU");
   constexpr int IH = I / 2;                              // 32-row groups per wavefront
   constexpr int RB = I, CB = 2 * NBW;                    // 16-row / 16-column MFMA blocks per wavefront
   constexpr int OUT_COLS = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
@@ -475,18 +483,18 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
   auto issue_one = [&](int t, int idx) {
     if (idx < LA) {
       const int k0 = min(t, nk - 1) * DMA_BK;
-      CB_GLDS16(src_a[idx] + k0, smem + (t % DMA_SA) * A_STAGE + (wave + NWV * idx) * 1024);
+      CB_GLDS16(src_a[idx] + k0, smem + (t % SA) * A_STAGE + (wave + NWV * idx) * 1024, 0);
     } else {
-      const int tw = t + SW - DMA_SA;                 // the weight ring runs SW - 2 tiles further ahead
+      const int tw = t + SW - SA;                     // the weight ring runs SW - SA tiles further ahead
       const int k0 = min(tw, nk - 1) * DMA_BK;
-      CB_GLDS16(src_w[idx - LA] + k0 * WE, smem + W_RING + (tw % SW) * W_STAGE + (wave + NWV * (idx - LA)) * 1024);
+      CB_GLDS16(src_w[idx - LA] + k0 * WE, smem + W_RING + (tw % SW) * W_STAGE + (wave + NWV * (idx - LA)) * 1024, NT ? kCacheNt : 0);
     }
   };
   auto issue_w = [&](int t) {
     const int k0 = min(t, nk - 1) * DMA_BK;
 #pragma unroll
     for (int i = 0; i < LW; ++i)
-      CB_GLDS16(src_w[i] + k0 * WE, smem + W_RING + (t % SW) * W_STAGE + (wave + NWV * i) * 1024);
+      CB_GLDS16(src_w[i] + k0 * WE, smem + W_RING + (t % SW) * W_STAGE + (wave + NWV * i) * 1024, NT ? kCacheNt : 0);
   };
 
   // v_mfma_f32_16x16x32_bf16 with the WEIGHT fragment as its first operand: block (i, jb) of a wavefront is
@@ -572,7 +580,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
       const int ab = hs & 1, bb = W8 ? 0 : (hs >> 1) & 1, h = hs & 1;
       const int nab = hsn & 1, nbb = W8 ? 0 : (hsn >> 1) & 1;
       const bool with_w = (hsn & 1) == 0;
-      const unsigned base_a = lds0 + (tn % DMA_SA) * A_STAGE + a_off + (hsn & 1) * (IH * 2048) + rd[hsn >> 1];
+      const unsigned base_a = lds0 + (tn % SA) * A_STAGE + a_off + (hsn & 1) * (IH * 2048) + rd[hsn >> 1];
       const unsigned base_w = lds0 + W_RING + (tn % SW) * W_STAGE + (W8 ? b_off8 + rd8[hsn >> 1] : b_off + rd[hsn >> 1]);
       const int n_reads = next_reads ? IH + (with_w ? CB : 0) : 0;
       // what rides along in MFMA slot j: the global loads q0 .. q1-1 of tile tl, spread evenly over the slots of
@@ -632,21 +640,22 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
       }
     };
 
-    // Issue order: W(0..SW-2), A(0), A(1), W(SW-1) up front; from then on the loads of a tile are
-    // spread over four half-steps so that the memory pipeline never sees a burst: after the barrier
-    // of tile t (its stages are free) the first half of A(t+2); during the first three half-steps of
-    // tile t+1 the second half of A(t+2), then W(t+SW) in two halves.  When tile t+1 is needed,
-    // the only loads that may be younger than the last load of A(t+1) are the LW loads of
-    // W(t+SW-1).
-    constexpr int QA = LA / 2, QW = LA + LW / 2;
+    // Issue order: W(0 .. SW-SA-1), then groups of one activation and one weight tile, [A(j), W(j+SW-SA)] for j = 0 ..
+    // SA-1, up front; from then on the loads of a group are spread over four half-steps so that the memory pipeline never
+    // sees a burst: after the barrier of tile t (its stages are free) the first half of A(t+SA); during the first three
+    // half-steps of tile t+1 the second half of it, then W(t+SW) in two halves.  When tile t+1 is needed, the
+    // groups of the SA-2 tiles after it may still be on their way, and of its own group the weight tile if that runs ahead.
+    constexpr int QA = LA / 2, QW = LA + LW / 2, AHEAD = SA < SW ? LW : 0, YOUNGER = (SA - 2) * NL + AHEAD;
+    static_assert(YOUNGER + NL < 64, "vmcnt has six bits");
 #pragma unroll
-    for (int s = 0; s < SW - 1; ++s) issue_w(s);
+    for (int s = 0; s < SW - SA; ++s) issue_w(s);
 #pragma unroll
-    for (int q = 0; q < LA; ++q) issue_one(0, q);
-    vm_wait<0>();
+    for (int s = 0; s < SA; ++s) {
+#pragma unroll
+      for (int q = 0; q < NL; ++q) issue_one(s, q);
+    }
+    vm_wait<YOUNGER + NL>();
     wg_barrier();
-#pragma unroll
-    for (int q = 0; q < NL; ++q) issue_one(1, q);
 #pragma unroll
     for (int q = 0; q < IH; ++q) read_frag(fa[0][q], lds0 + a_off + rd[0], q);
 #pragma unroll
@@ -663,28 +672,29 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
       else lds_pin(fb[0][q]);
     }
     if (nk > 1) {
-      // tile 0: tile 1 is already on its way
+      // tile 0: the tiles up to SA - 1 are already on their way
       step(0, true, 0, 1, 0, 0, 0);
       step(1, true, 0, 2, 0, 0, 0);
       step(2, true, 0, 3, 0, 0, 0);
-      vm_wait<LW>();
+      vm_wait<YOUNGER>();
       wg_barrier();
-      step(3, true, 1, 0, 0, QA, 2);
+      step(3, true, 1, 0, 0, QA, SA);
     }
     for (int t = 1; t + 1 < nk; ++t) {
-      step(0, true, t, 1, QA, LA, t + 1);
-      step(1, true, t, 2, LA, QW, t + 1);
-      step(2, true, t, 3, QW, NL, t + 1);
+      step(0, true, t, 1, QA, LA, t + SA - 1);
+      step(1, true, t, 2, LA, QW, t + SA - 1);
+      step(2, true, t, 3, QW, NL, t + SA - 1);
       // last half-step: its fragments are in registers, so once tile t+1 has landed everywhere the
       // stages of tile t can be refilled while these MFMAs run
-      vm_wait<LW>();
+      vm_wait<YOUNGER>();
       wg_barrier();
-      step(3, true, t + 1, 0, 0, QA, t + 2);
+      step(3, true, t + 1, 0, 0, QA, t + SA);
     }
     step(0, true, nk - 1, 1, 0, 0, 0);
     step(1, true, nk - 1, 2, 0, 0, 0);
     step(2, true, nk - 1, 3, 0, 0, 0);
     step(3, false, 0, 0, 0, 0, 0);
+    vm_wait<0>();                                      // the clamped loads past the last tile
   }
   // Block (i, jb) of this wavefront, lane l: output row i*16 + l%16 and columns jb*16 + 4*(l/16) .. +3 of its sub-tile
   const int l_row = lane & 15, l_col = (lane >> 4) * 4;
@@ -1211,6 +1221,7 @@ struct GemmPlan {
   long grid_ids;                                   // kind 2: workgroups of the main launch
   int xcd_split;                                   // kind 2: splits dealt to XCDs (see GemmParams)
   int w8;                                          // kind 2: int8 weights read by the kernel itself
+  int nt;                                          // kind 2: non-temporal weight loads
   int raw;                                         // sums are parked in `partial` and a finish launch completes them
   size_t partial_floats;
   bool bad;                                        // needs scratch the caller did not give
@@ -1219,7 +1230,7 @@ struct GemmPlan {
 static int pick_row_blocks(int M) {
   // padded rows divided by a rough efficiency of the tile height
   const int cand[4] = {8, 6, 4, 2};
-  const double eff[4] = {1.0, 0.97, 0.88, 0.62};
+  const double eff[4] = {1.0, 0.97, 0.82, 0.62};
   int best = 8;
   double best_cost = 1e30;
   for (int i = 0; i < 4; ++i) {
@@ -1230,40 +1241,56 @@ static int pick_row_blocks(int M) {
   return best;
 }
 
+// Weight loads are non-temporal for bf16 matrices this large that a single row tile reads: every weight is then read by one
+// workgroup alone.  57344 x 8192 at 16 .. 128 rows 187 -> 165 us, 8192 x 28672 at 64 rows 100 -> 84 us, 28672 x 4096 54 -> 50 us;
+// matrices of 30 .. 50 MB lost up to 10 %, several row tiles (they share weight tiles in L2) up to 20 %, int8 weights up to 20 %.
+constexpr double kNtMinBytes = 128e6;
+
+// XCDs that share one K split (GemmParams::xcd_split): 8 / splits where the splits are dealt to them, else all 8.  One row tile
+// has no activation slices worth keeping apart, and where its column tiles fill the 8 XCDs evenly anyhow the splits stay
+// together: 8192 x 8192 at 64 / 128 rows in 4 splits 49 / 52 us dealt, 43 / 47 us not.
+static int xcd_groups(int splits, int tiles_m, int tiles_n, int hl) {
+  if (tiles_m == 1 && tiles_n % 8 == 0 && !hl) return 8;
+  return splits == 2 || splits == 4 || splits == 8 ? 8 / splits : 8;
+}
+
 // Tile shape and K split of the direct-to-LDS kernel for the Q/K/V, output and down projections,
-// from a cost model in microseconds fitted to a sweep of every (tile, split) pair over the
-// projection shapes of the 7B- and 70B-shaped workloads (row counts 295 .. 1264) on the chip:
-//   main launch   = rounds x t_full x k-tiles per workgroup + 9.9 (launch, pipeline fill, epilogue)
-//   t_full        = time of one 64-deep k-tile with every slot of the chip busy (a slot = one resident
-//                   workgroup: two per CU for the tiles whose rings fit twice into LDS, else one)
-//   partial round = runs faster per tile, because fewer workgroups share the chip's power and its
-//                   L2 -> LDS paths: t_full x (1 - relief x (1 - fill))
-//   finish launch = 2.3 + 0.258 us per MB of parked sums (splits x M x N floats)
-// The model's choice is within 0 .. 5 % (mean 1 %) of the best measured pair on every shape of the sweep.
+// from a cost model in microseconds fitted to a sweep of every (tile, split) pair over these
+// projections of the 7B-, 34B- (bf16) and 70B-shaped workloads (16 .. 760 rows, bf16 and int8 weights, over 5000 pairs each) on the chip:
+//   main launch   = rounds x t x k-tiles per workgroup + 9.5 (launch, pipeline fill, epilogue)
+//                   at least the weights' bytes at 5.2 TB/s (few rows: no point in splitting further than that; the
+//                   operand pairs of K|V are bound by the matrix cores earlier and go by the tiles alone)
+//   rounds        = those of the XCD that is dealt the most workgroups, 32 at a time (one per CU; a partly filled
+//                   round counts whole).  28 column tiles in 9 splits are 252 workgroups, but 36 on four of the XCDs: two
+//                   rounds.  Counted over the chip instead, the model chose such splits: 7168 x 20480 at 96 / 525 rows
+//                   104 / 268 us, 72 / 192 us with the pairs it chooses now.
+//   t             = time of one 64-deep k-tile on every CU
+//   finish launch = 2.3 + 0.5 us per MB of parked sums (splits x M x N floats), stores included
+// Its choice is on average within 1.9 % (bf16) and 0.4 % (int8) of the best pair of the sweep, at most 22 % and 8 %.
+// t = 0: not used with that weight format (the wide tiles are faster at every row count of the sweep; a 256 x 128 tile of
+// bf16 weights is one for the gate/up projection alone).
 // max_splits caps the split (scratch the caller can spare); parked: a finish launch runs anyway.
-struct DmaShape { int I, NB; double t_full; };
-static const DmaShape kDmaShapes[] = {{2, 2, 0.80}, {4, 2, 1.23}, {6, 2, 1.02}, {8, 2, 1.28},
-                                      {4, 4, 1.14}, {6, 4, 1.54}, {8, 4, 1.90}};
+struct DmaShape { int I, NB; double t[2]; };               // t: bf16, int8 weights
+static const DmaShape kDmaShapes[] = {{2, 2, {0.58, 0.72}}, {4, 2, {0.72, 0.94}}, {6, 2, {0.82, 0.0}},
+                                      {4, 4, {0.97, 1.32}}, {6, 4, {1.28, 1.53}}, {8, 4, {1.50, 1.89}}};
 
 // Output columns [0, hl_cols) take (high, low) activation pairs, i.e. twice the tile rows per output row.
 static void pick_dma_plan(int M, int N, int hl_cols, int K, int max_splits, bool parked, bool w8, GemmPlan *pl) {
   const int k_tiles = K / DMA_BK;
-  const double park_us = (double)M * N * 4.0e-6 * 0.258;   // per split
+  const double park_us = (double)M * N * 4.0e-6 * 0.5;     // per split
+  const double read_us = hl_cols ? 0.0 : (double)N * K * (w8 ? 1 : 2) / 5.2e6;
   pl->cost = 1e30;
   for (const DmaShape &c : kDmaShapes) {
     const int bm = 32 * c.I, bn = 64 * c.NB;
-    if (c.I == 2 && (hl_cols ? 2 * M : M) > 64) continue;
+    if (c.t[w8] == 0.0 || (c.I == 2 && M > 64)) continue;
     if (hl_cols < N && hl_cols % bn != 0) continue;        // a tile's columns are of one kind
-    const int slots = dma_smem_bytes(c.I, bn, w8) <= 80 * 1024 ? 512 : 256;
-    const long tiles = (long)ceil_div(2 * M, bm) * ceil_div(hl_cols, bn) + (long)ceil_div(M, bm) * ceil_div(N - hl_cols, bn);
     for (int sp = 1; sp <= 16 && sp <= max_splits; ++sp) {
       if (sp > 1 && k_tiles / sp < 4) break;
-      const long wgs = tiles * sp;
-      const long full = wgs / slots;
-      const double last = (double)(wgs - full * slots) / slots;          // fill of the last round
-      const double relief = slots == 512 ? 0.69 : 0.45;
-      const double per_tile = full * c.t_full + (last > 0 ? c.t_full * (1.0 - relief + relief * last) : 0.0);
-      const double cost = per_tile * ceil_div(k_tiles, sp) + 9.9 + (sp > 1 || parked ? sp * park_us + 2.3 : 0.0);
+      const int groups = xcd_groups(sp, ceil_div(M, bm), ceil_div(N - hl_cols, bn), hl_cols);
+      const long per_xcd = ((long)ceil_div(2 * M, bm) * ceil_div(ceil_div(hl_cols, bn), groups) +
+                            (long)ceil_div(M, bm) * ceil_div(ceil_div(N - hl_cols, bn), groups)) * (groups < 8 ? 1 : sp);
+      const long rounds = (per_xcd + 31) / 32;
+      const double cost = std::max(rounds * c.t[w8] * ceil_div(k_tiles, sp), read_us) + 9.5 + (sp > 1 || parked ? sp * park_us + 2.3 : 0.0);
       if (cost < pl->cost - 1e-9) { pl->cost = cost; pl->I = c.I; pl->NB = c.NB; pl->splits = sp; }
     }
   }
@@ -1305,7 +1332,7 @@ static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int f
     pl.kind = 2; pl.I = pick_row_blocks(M); pl.bk = DMA_BK;
     // 256-column tiles unless 128-column tiles (lower arithmetic intensity: measured ~1.4x
     // slower per flop) fill the rounds of 256 workgroups so much better that they still win,
-    // which happens when there is a single row of tiles (M <= 256)
+    // which happens when there is a single row of tiles (M <= 256).
     pl.NB = 4;
     const long t4 = (long)ceil_div(M, 32 * pl.I) * ceil_div(N, 128), t2 = (long)ceil_div(M, 32 * pl.I) * ceil_div(N, 64);
     const double c4 = (double)((t4 + 255) / 256) * 2.0, c2 = (double)((t2 + 255) / 256) * 1.4;
@@ -1345,8 +1372,9 @@ static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int f
   pl.partial_floats = pl.raw ? (size_t)pl.splits * mn : 0;
   pl.tail_splits = 1;
   if (pl.kind == 2) {
-    pl.xcd_split = epi != EPI_SWIGLU && (pl.splits == 2 || pl.splits == 4 || pl.splits == 8);
-    const int groups = pl.xcd_split ? 8 / pl.splits : 8;
+    const int groups = epi == EPI_SWIGLU ? 8 : xcd_groups(pl.splits, pl.tiles_m, pl.tiles_n, pl.hl);
+    pl.xcd_split = groups < 8;
+    pl.nt = epi != EPI_SEG && !w8 && pl.tiles_m == 1 && (epi == EPI_SWIGLU ? 4.0 : 2.0) * N * K >= kNtMinBytes;
     const long ids = 8L * (ceil_div(pl.tiles_n, groups) * pl.tiles_m + ceil_div(pl.hl_tiles_n, groups) * pl.hl_tiles_m);
     pl.grid_ids = pl.xcd_split ? ids : ids * pl.splits;
     pl.tail_first = (int)pl.grid_ids;
@@ -1453,19 +1481,19 @@ bool gemm_needs_finish(const GemmArgs &g) {
     });                                                                                            \
   } while (0)
 
+template <int I, int NB, int EPI, int NWV, bool HL, bool W8, bool NT>
+static void launch_dma_kernel(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
+  constexpr int smem = dma_smem_bytes(I, 64 * NB, W8);
+  CB_LDS_LIMIT_ONCE((&gemm_bf16_dma_kernel<I, NB, EPI, NWV, HL, W8, NT>), smem);
+  hipLaunchKernelGGL((gemm_bf16_dma_kernel<I, NB, EPI, NWV, HL, W8, NT>), dim3((unsigned)pl.grid_ids), dim3(64 * NWV),
+                     smem, s, p, pl.tiles_m, pl.tiles_n);
+}
+
 template <int I, int NB, int EPI, int NWV, bool HL = false>
 static void launch_dma(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
-  if (pl.w8) {
-    constexpr int smem = dma_smem_bytes(I, 64 * NB, true);
-    CB_LDS_LIMIT_ONCE((&gemm_bf16_dma_kernel<I, NB, EPI, NWV, HL, true>), smem);
-    hipLaunchKernelGGL((gemm_bf16_dma_kernel<I, NB, EPI, NWV, HL, true>), dim3((unsigned)pl.grid_ids), dim3(64 * NWV),
-                       smem, s, p, pl.tiles_m, pl.tiles_n);
-    return;
-  }
-  constexpr int smem = dma_smem_bytes(I, 64 * NB);
-  CB_LDS_LIMIT_ONCE((&gemm_bf16_dma_kernel<I, NB, EPI, NWV, HL>), smem);
-  hipLaunchKernelGGL((gemm_bf16_dma_kernel<I, NB, EPI, NWV, HL>), dim3((unsigned)pl.grid_ids), dim3(64 * NWV), smem,
-                     s, p, pl.tiles_m, pl.tiles_n);
+  if (pl.w8) launch_dma_kernel<I, NB, EPI, NWV, HL, true, false>(pl, p, s);
+  else if (pl.nt) launch_dma_kernel<I, NB, EPI, NWV, HL, false, EPI != EPI_SEG>(pl, p, s);
+  else launch_dma_kernel<I, NB, EPI, NWV, HL, false, false>(pl, p, s);
 }
 
 template <int EPI, bool HL>
