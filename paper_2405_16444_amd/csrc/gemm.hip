@@ -1228,9 +1228,11 @@ struct GemmPlan {
 };
 
 static int pick_row_blocks(int M) {
-  // padded rows divided by a rough efficiency of the tile height
+  // padded rows divided by the tile height's share of the tallest one's rate (k-tile times of kDmaShapes; gate/up at 900 and
+  // 1900 rows with 256 instead of 192 rows per tile: 216 -> 192 and 391 -> 365 us on 28672 x 4096, 719 -> 692 and 1459 ->
+  // 1338 us on 57344 x 8192)
   const int cand[4] = {8, 6, 4, 2};
-  const double eff[4] = {1.0, 0.97, 0.82, 0.62};
+  const double eff[4] = {1.0, 0.92, 0.82, 0.62};
   int best = 8;
   double best_cost = 1e30;
   for (int i = 0; i < 4; ++i) {
