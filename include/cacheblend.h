@@ -252,7 +252,8 @@ int cb_fuse_prefill_batched(cb_ctx *ctx, const cb_layer_weights *layers, int32_t
  *   final_norm   : T [d] gain of the final RMSNorm (eps = desc.rms_eps)
  *   lm_head      : T [vocab, d] row-major
  *   logits       : float [vocab] (out)
- *   token        : int32 [1] (out, device): smallest index among the largest logits
+ *   token        : int32 [1] (out, device): smallest index among the largest logits; a NaN logit counts as less
+ *                  than every number (all NaN: 0)
  * Needs d_model % 8 == 0 and d_model <= 16384 (else CB_EUNSUPPORTED). */
 int cb_first_token(cb_ctx *ctx, const float *final_hidden, int32_t n_suffix, const void *final_norm,
                    const void *lm_head, int32_t vocab, float *logits, int32_t *token, void *stream);

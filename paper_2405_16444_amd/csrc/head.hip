@@ -22,10 +22,13 @@ constexpr int kHeadThreads = 1024, kHeadWaves = kHeadThreads / 64, kHeadWorkgrou
 constexpr int kHeadChunks = 4;          // 16-byte chunks of a row per lane and round
 
 // Order-preserving map of a logit and its index to one integer: a larger logit, then a lower index, is larger.
-// (-0 counts as +0.)
+// (-0 counts as +0; NaN, whatever its sign and payload, counts as less than every number, -infinity included.)  Keys lie
+// strictly between 0 and all ones, the two values the pick below uses for itself: idx < 2^31 keeps the low word above 0,
+// and no number's high word exceeds that of +infinity.
 __device__ __forceinline__ unsigned long long pick_key(float v, int idx) {
   const unsigned u = __float_as_uint(v + 0.f);
-  const unsigned ord = u & 0x80000000u ? ~u : u | 0x80000000u;
+  const bool nan = (u & 0x7FFFFFFFu) > 0x7F800000u;
+  const unsigned ord = nan ? 0u : u & 0x80000000u ? ~u : u | 0x80000000u;
   return ((unsigned long long)ord << 32) | (0xFFFFFFFFu - (unsigned)idx);
 }
 

@@ -43,3 +43,31 @@ def test_pick_is_the_first_largest_logit(P, dtype, vocab):
                               rtol=1e-3, atol=4e-3)
         assert int(token) == int((got == got.max()).nonzero()[0])
     P.cb_destroy(ctx)
+
+
+@pytest.mark.parametrize("bits", [0x7FFFFFFF, 0x7FC00000, 0xFFC00000, 0xFFFFFFFF], ids=hex)
+@pytest.mark.parametrize("rows", [(0,), (0, 1, 2, 3, 16, 4999), (777,)], ids=str)
+def test_nan_logits_lose_and_leave_the_context_usable(P, bits, rows):
+    """A NaN logit, whatever its sign and payload, counts as less than every number; the calls that follow on the same
+    context are unaffected by it.  (A positive one with every payload bit set used to map row 0 to the value that marks
+    the pick's scratch: the token was not written, nor by any later call.)"""
+    announce("greedy pick, NaN logits", hex(bits), rows)
+    vocab, d = 5000, 256
+    g = torch.Generator().manual_seed(5)
+    w = torch.empty(vocab, d).normal_(0, 0.05, generator=g)
+    bad = w.clone()
+    bad.view(torch.int32)[list(rows)] = bits if bits < 2 ** 31 else bits - 2 ** 32
+    h, gain = torch.empty(1, d).normal_(0, 1, generator=g).cuda(), torch.ones(d).cuda()
+    ctx = P.cb_create(ModelShape(1, d, 4, 2, 64, 128, 1e-5, 1e4, "f32", vocab), 8)
+    token = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    for weights, nan_rows in ((bad, rows), (w, ()), (bad, rows), (w, ())):
+        token.fill_(-1)
+        logits, _ = P.cb_first_token(ctx, h, gain, weights.cuda(), token=token)
+        got = logits.cpu()
+        assert got.isnan().nonzero().flatten().tolist() == sorted(nan_rows)
+        got[list(nan_rows)] = -float("inf")
+        assert int(token) == int((got == got.max()).nonzero()[0])
+    token.fill_(-1)
+    P.cb_first_token(ctx, h, gain, torch.full_like(w, float("nan")).cuda(), token=token)
+    assert int(token) == 0
+    P.cb_destroy(ctx)
