@@ -10,8 +10,9 @@
  * Conventions
  *   - Every pointer is a DEVICE pointer unless its comment says HOST.
  *   - All buffers are owned by the caller.  The library allocates only the
- *     cb_ctx (a host struct plus one device table of rotary cos/sin values) in
- *     cb_create and releases it in cb_destroy.
+ *     cb_ctx (a host struct plus one device allocation: the table of rotary
+ *     cos/sin values and 16 bytes that the workgroups of cb_first_token agree
+ *     through) in cb_create and releases it in cb_destroy.
  *   - Storage type T = cb_model_desc.dtype (float or bfloat16) for weights, the
  *     layer-0 input x, and the K/V caches.  The residual stream that crosses the
  *     per-layer boundary (h_in / h_out / final_hidden) is always float.
@@ -254,7 +255,10 @@ int cb_fuse_prefill_batched(cb_ctx *ctx, const cb_layer_weights *layers, int32_t
  *   logits       : float [vocab] (out)
  *   token        : int32 [1] (out, device): smallest index among the largest logits; a NaN logit counts as less
  *                  than every number (all NaN: 0)
- * Needs d_model % 8 == 0 and d_model <= 16384 (else CB_EUNSUPPORTED). */
+ * Needs d_model % 8 == 0 and d_model <= 16384 (else CB_EUNSUPPORTED), and a stream of the device the ctx was
+ * created on (else CB_EINVAL).  The call uses 16 bytes of device memory of the ctx, zero between calls: as for every
+ * call, two of them on one ctx must not overlap -- on two streams, or replayed from a graph beside another call, each
+ * needs a ctx of its own. */
 int cb_first_token(cb_ctx *ctx, const float *final_hidden, int32_t n_suffix, const void *final_norm,
                    const void *lm_head, int32_t vocab, float *logits, int32_t *token, void *stream);
 

@@ -992,6 +992,9 @@ int cb_first_token(cb_ctx *c, const float *final_hidden, int32_t n_suffix, const
   const int d = c->m.d_model;
   if (d % 8 != 0 || d > 16384) return CB_EUNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
+  int device = -1;                             // the launch updates c->pick, which only the ctx's device is sure to reach
+  if ((s ? hipStreamGetDevice(s, &device) : hipGetDevice(&device)) != hipSuccess) return CB_EHIP;
+  if (device != c->device) return CB_EINVAL;
   const size_t es = esize(c);
   ProfScope ps(c, s, CB_PROF_HEAD, 2.0 * vocab * d, (double)vocab * d * es + (double)vocab * 4);
   CB_HIP(launch_lm_head(c->m.dtype, final_hidden + (size_t)(n_suffix - 1) * d, final_norm, lm_head, d, vocab,

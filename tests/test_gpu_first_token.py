@@ -86,3 +86,46 @@ def test_first_token_rejects_bad_arguments(P):
         P.cb_first_token(ctx, torch.zeros(1, 256, device="cuda"), head["final_norm"].cuda(),
                          torch.zeros(0, 256, device="cuda"))
     P.cb_destroy(ctx)
+
+
+def test_first_token_on_streams_and_in_a_graph(P):
+    """A context each on two streams at once, and one call replayed from a graph: every answer is the eager one."""
+    model = ModelShape(1, 512, 8, 2, 64, 128, 1e-5, 1e4, "bf16", 20011)
+    head = {k: v.cuda() for k, v in synth.head_weights(model, 3).items()}
+    announce("first token, two contexts on two streams")
+    h = [torch.randn(1, 512, generator=torch.Generator().manual_seed(i)).cuda() for i in range(2)]
+    ctx = [P.cb_create(model, 8) for _ in h]
+    ref = [tuple(t.clone() for t in P.cb_first_token(c, x, head["final_norm"], head["lm_head"])) for c, x in zip(ctx, h)]
+    out = [(torch.empty(20011, device="cuda"), torch.empty(1, dtype=torch.int32, device="cuda")) for _ in h]
+    streams = [torch.cuda.Stream() for _ in h]
+    torch.cuda.synchronize()
+    for _ in range(20):
+        for c, x, s, (lo, tk) in zip(ctx, h, streams, out):
+            P.cb_first_token(c, x, head["final_norm"], head["lm_head"], stream=s, logits=lo, token=tk)
+    torch.cuda.synchronize()
+    for got, want in zip(out, ref):
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        P.cb_first_token(ctx[0], h[0], head["final_norm"], head["lm_head"], logits=out[0][0], token=out[0][1])
+    for _ in range(3):
+        P.cb_first_token(ctx[0], h[1], head["final_norm"], head["lm_head"], logits=out[0][0], token=out[0][1])
+        torch.cuda.synchronize()
+        assert torch.equal(out[0][0], ref[1][0]) and torch.equal(out[0][1], ref[1][1])
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[0][0], ref[0][0]) and torch.equal(out[0][1], ref[0][1])
+    for c in ctx:
+        P.cb_destroy(c)
+
+
+@pytest.mark.skipif(torch.cuda.device_count() < 2, reason="needs two devices")
+def test_first_token_refuses_a_stream_of_another_device(P):
+    """The pick's scratch lives on the context's device: a launch elsewhere would reach for it across the link."""
+    model = ModelShape(1, 256, 4, 2, 64, 128, 1e-5, 1e4, "f32", 100)
+    ctx = P.cb_create(model, 8)
+    head = {k: v.to("cuda:1") for k, v in synth.head_weights(model, 1).items()}
+    with torch.cuda.device(1), pytest.raises(P.CacheBlendError) as e:
+        P.cb_first_token(ctx, torch.zeros(1, 256, device="cuda:1"), head["final_norm"], head["lm_head"])
+    assert e.value.status == -1
+    P.cb_destroy(ctx)
