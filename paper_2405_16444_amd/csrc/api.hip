@@ -992,8 +992,11 @@ int cb_first_token(cb_ctx *c, const float *final_hidden, int32_t n_suffix, const
   const int d = c->m.d_model;
   if (d % 8 != 0 || d > 16384) return CB_EUNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
-  int device = -1;                             // the launch updates c->pick, which only the ctx's device is sure to reach
-  if ((s ? hipStreamGetDevice(s, &device) : hipGetDevice(&device)) != hipSuccess) return CB_EHIP;
+  // the launch updates c->pick, which only the ctx's device is sure to reach (the default stream and the runtime's special
+  // handles, small integers, stand for streams of the current device and are no objects to ask)
+  int device = -1;
+  const bool object = reinterpret_cast<uintptr_t>(s) > 16;
+  if ((object ? hipStreamGetDevice(s, &device) : hipGetDevice(&device)) != hipSuccess) return CB_EHIP;
   if (device != c->device) return CB_EINVAL;
   const size_t es = esize(c);
   ProfScope ps(c, s, CB_PROF_HEAD, 2.0 * vocab * d, (double)vocab * d * es + (double)vocab * 4);
