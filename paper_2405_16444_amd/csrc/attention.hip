@@ -549,9 +549,12 @@ __global__ __launch_bounds__(64 * AF_NW) void attn_f32_kernel(const float *__res
   float4 qf[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) qf[c] = *reinterpret_cast<const float4 *>(qrow + 16 * c + 4 * h);
-  int bound = my_pos;                                  // the 16 queries sit in lanes 0..15 of every group
+  int bound = my_pos, min_pos = my_pos;                // the 16 queries sit in lanes 0..15 of every group
 #pragma unroll
-  for (int off = 8; off > 0; off >>= 1) bound = max(bound, __shfl_xor(bound, off, 64));
+  for (int off = 8; off > 0; off >>= 1) {
+    bound = max(bound, __shfl_xor(bound, off, 64));
+    min_pos = min(min_pos, __shfl_xor(min_pos, off, 64));
+  }
   const int kv_len = bound + 1, n_tiles = (kv_len + 31) / 32;
 
   f32x4 oacc[NC];
@@ -604,14 +607,50 @@ __global__ __launch_bounds__(64 * AF_NW) void attn_f32_kernel(const float *__res
     run_max = new_max;
 #pragma unroll
     for (int c = 0; c < NC; ++c) oacc[c] *= alpha;
+    float vf[2][4][NC];
 #pragma unroll
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float *vrow = vc + (size_t)min(t0 + 16 * b + 4 * h + i, kv_len - 1) * kv_dim + kvh * DH + ln;
 #pragma unroll
-        for (int c = 0; c < NC; ++c) oacc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vrow[16 * c], sc[b][i], oacc[c], 0, 0, 0);
+        for (int c = 0; c < NC; ++c) vf[b][i][c] = vrow[16 * c];
       }
+    // A query sees cache rows 0 .. its own position, but the product below multiplies every row of the tile, by 0 where it
+    // lies past the position -- and 0 times a value that is not finite is not 0.  Only tiles with such a pair are looked at.
+    bool bad = false;
+    if (t0 + 31 > min_pos) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int c = 0; c < NC; ++c) bad |= !(fabsf(vf[b][i][c]) < INFINITY);
+    }
+    if (__any(bad)) {
+      // the same sums key by key, each query up to its own position; p of key 16 b + 4 j + i is held by lane group j
+#pragma unroll 1
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float pk = __shfl(sc[b][i], 16 * j + ln, 64);
+            const int key = t0 + 16 * b + 4 * j + i;
+            const float *vrow = vc + (size_t)min(key, kv_len - 1) * kv_dim + kvh * DH + 4 * h;
+            if (key <= my_pos) {
+#pragma unroll
+              for (int c = 0; c < NC; ++c) oacc[c] += pk * *reinterpret_cast<const f32x4 *>(vrow + 16 * c);
+            }
+          }
+      continue;
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) oacc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[b][i][c], sc[b][i], oacc[c], 0, 0, 0);
   }
   run_sum += __shfl_xor(run_sum, 16, 64);
   run_sum += __shfl_xor(run_sum, 32, 64);

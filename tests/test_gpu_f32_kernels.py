@@ -44,3 +44,22 @@ def test_float_layer(P, case):
         assert max_abs_rel(dev.numpy(), dev_ref) < tol
     assert max_abs_rel(to_np(kg), ko) < tol and max_abs_rel(to_np(vg), vo) < tol
     assert max_abs_rel(to_np(h_out), h_ref) < tol
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")], ids=str)
+@pytest.mark.parametrize("dh,n_rows,n_tokens", [(64, 40, 90), (64, 300, 700), (128, 33, 70)])
+def test_a_bad_value_row_reaches_only_the_rows_that_see_it(P, dh, n_rows, n_tokens, value):
+    """A reused value row that is not finite belongs to the queries at and after its position; the queries before it that
+    share an attention block with some of those match the oracle on a clean cache, which never shows them that row."""
+    model = ModelShape(1, 256, 4, 2, dh, 688, 1e-5, 1e4, "f32")
+    lw, h, pos, kc, vc = layer_case(model, n_tokens, n_rows, 2, seed=dh + n_rows, std=0.05)
+    h_ref, _, _, _, _ = oracle_layer(model, lw, h, pos, kc, vc, 2, n_rows - 2, None)
+    reused = np.setdiff1d(np.arange(n_tokens), pos.numpy())
+    for at in (reused[0], reused[len(reused) // 3], reused[len(reused) // 2], reused[-1]):
+        announce("float attention, bad value row", dh, n_rows, int(at), value)
+        bad = vc.clone()
+        bad[int(at), :, dh - 1] = value
+        h_out, pos_out, _, _, _ = run_layer_both(P, model, lw, h, pos, kc, bad, 2, n_rows - 2, want_dev=False)
+        before = pos_out.numpy() < at
+        assert max_abs_rel(to_np(h_out)[before], h_ref[before]) < TOL["f32"]
+        assert not np.isfinite(h_out.numpy()[~before]).all(axis=1).any()
