@@ -16,6 +16,7 @@ def chunk_prefill(ctx: B.Context, layers: Sequence[Dict[str, torch.Tensor]], x_c
     """Returns (k_layers, v_layers): per layer a [n_rows_alloc, Hkv, dh] tensor whose
     rows [0, sum(chunk_lens)) hold the chunks' K/V as cached at positions 0.. ."""
     m = ctx.model
+    layers = layers[:m.n_layers]            # a longer list is fine, as for a program that keeps more than it runs
     n_ctx = sum(chunk_lens)
     # one allocation for all layers; the chunks fill rows [0, n_ctx), only the rest has to be cleared
     kv = torch.empty((2 * m.n_layers, n_rows_alloc, m.n_kv_heads, m.head_dim), dtype=ctx.dtype, device=ctx.device)

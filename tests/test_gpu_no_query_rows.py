@@ -40,6 +40,23 @@ def test_producer(P, name, lens, extra, as_float):
             assert max_abs_rel(to_np(got[:w.n_ctx].cpu()), ref) < TOL[model.dtype], f"layer {l}"
 
 
+def test_producer_takes_a_longer_list_of_layers(P):
+    """The first n_layers entries are the model's; what follows them is not looked at."""
+    model = replace(MODELS["bf16"], n_layers=2)
+    announce("producer, longer list of layers")
+    w, layers, x, npl, xn, kpre, vpre = e2e_case(model, (30, 41), 2, seed=190)
+    ctx = P.cb_create(model, w.n_tokens)
+    dl = dev_layers(layers)
+    for longer in (dl + [dl[0]], tuple(dl) + (None,)):
+        ks, vs = producer.chunk_prefill(ctx, longer, x[:w.n_ctx].cuda(), (30, 41), w.n_ctx)
+        torch.cuda.synchronize()
+        assert len(ks) == len(vs) == 2
+        for l in range(2):
+            assert max_abs_rel(to_np(ks[l].cpu()), kpre[l]) < TOL["bf16"]
+            assert max_abs_rel(to_np(vs[l].cpu()), vpre[l]) < TOL["bf16"]
+    P.cb_destroy(ctx)
+
+
 def test_batched_requests_without_a_suffix(P):
     model = replace(MODELS["bf16"], n_layers=3)
     announce("batched, no suffix")
