@@ -32,7 +32,10 @@ def chunk_prefill(ctx: B.Context, layers: Sequence[Dict[str, torch.Tensor]], x_c
         x = x_ctx[o:o + ln]
         o += ln
         if x.dtype == ctx.dtype:
-            out = B.cb_fuse_prefill(ctx, layers, x.contiguous(), [ln], 0, kc, vc, [ln] * m.n_layers, workspace=ws,
+            x = x.contiguous()
+            if x.dtype != torch.float32 and x.data_ptr() % 16:
+                x = x.clone()               # 16-bit rows may start anywhere (a float input is read where it lies, below too)
+            out = B.cb_fuse_prefill(ctx, layers, x, [ln], 0, kc, vc, [ln] * m.n_layers, workspace=ws,
                                     weight_structs=structs)
             structs = out.weight_structs
             continue

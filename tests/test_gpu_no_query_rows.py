@@ -57,6 +57,24 @@ def test_producer_takes_a_longer_list_of_layers(P):
     P.cb_destroy(ctx)
 
 
+def test_producer_takes_16_bit_rows_at_any_address(P):
+    model = replace(MODELS["bf16"], n_layers=2)
+    announce("producer, input not on a 16-byte boundary")
+    w, layers, x, npl, xn, kpre, vpre = e2e_case(model, (30, 41), 2, seed=200)
+    ctx = P.cb_create(model, w.n_tokens)
+    xc = torch.empty(w.n_ctx * model.d_model + 8, dtype=torch.bfloat16, device="cuda")
+    for shift in (1, 4):
+        xs = xc[shift:shift + w.n_ctx * model.d_model].view(w.n_ctx, model.d_model)
+        xs.copy_(x[:w.n_ctx])
+        assert xs.data_ptr() % 16 == 2 * shift
+        ks, vs = producer.chunk_prefill(ctx, dev_layers(layers), xs, (30, 41), w.n_ctx)
+        torch.cuda.synchronize()
+        for l in range(2):
+            assert max_abs_rel(to_np(ks[l].cpu()), kpre[l]) < TOL["bf16"]
+            assert max_abs_rel(to_np(vs[l].cpu()), vpre[l]) < TOL["bf16"]
+    P.cb_destroy(ctx)
+
+
 def test_batched_requests_without_a_suffix(P):
     model = replace(MODELS["bf16"], n_layers=3)
     announce("batched, no suffix")
