@@ -18,12 +18,13 @@ def chunk_prefill(ctx: B.Context, layers: Sequence[Dict[str, torch.Tensor]], x_c
     m = ctx.model
     layers = layers[:m.n_layers]            # a longer list is fine, as for a program that keeps more than it runs
     n_ctx = sum(chunk_lens)
-    # one allocation for all layers; the chunks fill rows [0, n_ctx), only the rest has to be cleared
-    kv = torch.empty((2 * m.n_layers, n_rows_alloc, m.n_kv_heads, m.head_dim), dtype=ctx.dtype, device=ctx.device)
+    # a tensor of its own for every layer's K and V: each can be kept, saved or freed without the others.  The chunks fill
+    # rows [0, n_ctx), only the rest has to be cleared.
+    shape = (n_rows_alloc, m.n_kv_heads, m.head_dim)
+    ks = [torch.empty(shape, dtype=ctx.dtype, device=ctx.device) for _ in range(m.n_layers)]
+    vs = [torch.empty(shape, dtype=ctx.dtype, device=ctx.device) for _ in range(m.n_layers)]
     if n_rows_alloc > n_ctx:
-        kv[:, n_ctx:] = 0
-    caches = list(kv)
-    ks, vs = caches[:m.n_layers], caches[m.n_layers:]
+        torch._foreach_zero_([t[n_ctx:] for t in ks + vs])
     ws = torch.empty(B.cb_prefill_workspace_bytes(ctx, max(chunk_lens)), dtype=torch.uint8, device=ctx.device)
     structs, o = None, 0
     for ln in chunk_lens:

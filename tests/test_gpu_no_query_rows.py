@@ -75,6 +75,22 @@ def test_producer_takes_16_bit_rows_at_any_address(P):
     P.cb_destroy(ctx)
 
 
+@pytest.mark.parametrize("extra", [0, 3])
+def test_every_layer_of_the_producer_is_a_tensor_of_its_own(P, extra, tmp_path):
+    """Keeping or saving one layer's K keeps or saves that layer's K."""
+    model = replace(MODELS["bf16"], n_layers=3)
+    announce("producer, storage of the layers", extra)
+    w, layers, x, npl, xn, kpre, vpre = e2e_case(model, (30, 41), 2, seed=210)
+    ctx = P.cb_create(model, w.n_tokens)
+    ks, vs = producer.chunk_prefill(ctx, dev_layers(layers), x[:w.n_ctx].cuda(), (30, 41), w.n_ctx + extra)
+    size = (w.n_ctx + extra) * model.kv_dim * 2
+    assert all(t.untyped_storage().nbytes() == size and t.storage_offset() == 0 for t in ks + vs)
+    torch.save(ks[1], tmp_path / "k1.pt")
+    assert (tmp_path / "k1.pt").stat().st_size < size + 4096
+    assert torch.equal(torch.load(tmp_path / "k1.pt", weights_only=True), ks[1])
+    P.cb_destroy(ctx)
+
+
 def test_batched_requests_without_a_suffix(P):
     model = replace(MODELS["bf16"], n_layers=3)
     announce("batched, no suffix")
