@@ -135,6 +135,39 @@ def test_selective_layer_at_real_width_with_8bit_weights(P, name, n_tokens, n_ro
     assert err < tol
 
 
+@pytest.mark.parametrize("name,weights,kept", [
+    # 7B shape: 64-, 128-, 192- and 256-row tiles of 128 columns, gate/up loaded non-temporally (235 MB read by one row tile)
+    ("mistral7b", "native", 16), ("mistral7b", "native", 64), ("mistral7b", "native", 96), ("mistral7b", "native", 128),
+    ("mistral7b", "native", 160), ("mistral7b", "native", 192), ("mistral7b", "native", 224), ("mistral7b", "int8", 64),
+    ("mistral7b", "int8", 192),
+    # 70B shape: Wo, gate/up and down non-temporal; 256-column gate/up tiles of 64, 128 and 192 rows
+    ("llama70b", "native", 16), ("llama70b", "native", 64), ("llama70b", "native", 128), ("llama70b", "native", 192),
+    ("llama70b", "int8", 64), ("llama70b", "int8", 128),
+])
+def test_few_kept_rows_at_real_width(P, name, weights, kept):
+    """So few rows that the weight stream bounds the projections: one row tile, K split over most of the chip."""
+    w = WORKLOADS[name]
+    model = replace(w.model, n_layers=1, weight_format=weights)
+    n_suffix, n_rows, n_tokens = 8, kept + 20, 600
+    k_keep = kept - n_suffix
+    announce("few kept rows at real width", name, weights, kept)
+    lw, nlw = full_layer(name)
+    if weights == "int8":
+        lw = synth.quantize_int8(lw)
+        nlw = O.dequantize_int8({k: synth.to_f64(v) for k, v in lw.items()})
+    h, pos, kc, vc = case(model, n_tokens, n_rows, n_suffix, seed=7600 + kept)
+    h_out, pos_out, dev, kg, vg = run_gpu(P, model, lw, h, pos, kc, vc, n_suffix, k_keep, True)
+    tol = TOL["bf16"]
+    sel_pos = pos.numpy()[:n_rows - n_suffix][O.top_k_indices(dev.numpy(), k_keep)]
+    assert np.array_equal(pos_out.numpy()[:k_keep], sel_pos)
+    ko, vo = to_np(kc), to_np(vc)
+    h_ref, _, dev_ref, _ = O.fuse_layer(nlw, model, to_np(h), pos.numpy(), n_suffix, ko, vo, k_keep, forced_sel=sel_pos,
+                                        kv_round=O.round_bf16)
+    assert max_abs_rel(dev.numpy(), dev_ref) < tol
+    assert max_abs_rel(to_np(kg), ko) < tol and max_abs_rel(to_np(vg), vo) < tol
+    assert max_abs_rel(to_np(h_out), h_ref) < tol
+
+
 def _bench_schedule_shapes():
     """(layer, rows in, kept) of layers 1..31 of the default benchmark request: the rows that enter
     a layer are the context rows the layer before kept, plus the 64 query rows."""

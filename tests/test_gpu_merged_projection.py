@@ -1,6 +1,7 @@
-"""K, V and Q of a layer in one projection launch: key/value columns (operand pairs) that fill half a column tile, a
-whole one and several, row counts around the tile edges of both kinds of tiles, with a selection (Q is then computed for
-every candidate and read through the kept list) and without one, both rotary orders and 8-bit weights."""
+"""K, V and Q of a layer in one projection launch (or, where that is estimated to be slower, in two): key/value columns
+(operand pairs) that fill one column tile of 128 and several, row counts around the tile edges of both kinds of columns, with
+a selection (Q is then computed for every candidate and read through the kept list) and without one, both rotary orders and
+8-bit weights.  Column tiles of 256 meet in test_gpu_projection_depth.py and, with a selection, in the real-width tests."""
 import numpy as np
 import pytest
 
