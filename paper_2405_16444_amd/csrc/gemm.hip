@@ -1273,8 +1273,15 @@ static int xcd_groups(int splits, int tiles_m, int tiles_n, int hl) {
 // bf16 weights is one for the gate/up projection alone).
 // max_splits caps the split (scratch the caller can spare); parked: a finish launch runs anyway.
 struct DmaShape { int I, NB; double t[2]; };               // t: bf16, int8 weights
-static const DmaShape kDmaShapes[] = {{2, 2, {0.58, 0.72}}, {4, 2, {0.72, 0.94}}, {6, 2, {0.82, 0.0}},
-                                      {4, 4, {0.97, 1.32}}, {6, 4, {1.28, 1.53}}, {8, 4, {1.50, 1.89}}};
+static constexpr DmaShape kDmaShapes[] = {{2, 2, {0.58, 0.72}}, {4, 2, {0.72, 0.94}}, {6, 2, {0.82, 0.0}},
+                                          {4, 4, {0.97, 1.32}}, {6, 4, {1.28, 1.53}}, {8, 4, {1.50, 1.89}}};
+// whether a plan can ask for a tile: the gate/up projection takes any, the others go by the table above
+constexpr bool dma_tile_planned(int epi, int I, int NB, bool w8) {
+  if (epi == EPI_SWIGLU) return true;
+  for (const DmaShape &c : kDmaShapes)
+    if (c.I == I && c.NB == NB && c.t[w8] != 0.0) return true;
+  return false;
+}
 
 // Output columns [0, hl_cols) take (high, low) activation pairs, i.e. twice the tile rows per output row.
 static void pick_dma_plan(int M, int N, int hl_cols, int K, int max_splits, bool parked, bool w8, GemmPlan *pl) {
@@ -1491,47 +1498,59 @@ static void launch_dma_kernel(const GemmPlan &pl, const GemmParams &p, hipStream
                      smem, s, p, pl.tiles_m, pl.tiles_n);
 }
 
+// Only kernels of tiles that a plan can ask for are built; false for any other.
 template <int I, int NB, int EPI, int NWV, bool HL = false>
-static void launch_dma(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
-  if (pl.w8) launch_dma_kernel<I, NB, EPI, NWV, HL, true, false>(pl, p, s);
-  else if (pl.nt) launch_dma_kernel<I, NB, EPI, NWV, HL, false, EPI != EPI_SEG>(pl, p, s);
-  else launch_dma_kernel<I, NB, EPI, NWV, HL, false, false>(pl, p, s);
+static bool launch_dma(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
+  if (pl.w8) {
+    if constexpr (dma_tile_planned(EPI, I, NB, true)) {
+      launch_dma_kernel<I, NB, EPI, NWV, HL, true, false>(pl, p, s);
+      return true;
+    }
+  } else {
+    if constexpr (dma_tile_planned(EPI, I, NB, false)) {
+      if (pl.nt) launch_dma_kernel<I, NB, EPI, NWV, HL, false, EPI != EPI_SEG>(pl, p, s);
+      else launch_dma_kernel<I, NB, EPI, NWV, HL, false, false>(pl, p, s);
+      return true;
+    }
+  }
+  return false;
 }
 
 template <int EPI, bool HL>
-static void launch_dma_shape(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
+static bool launch_dma_shape(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
   if (pl.NB == 2) {
     switch (pl.I) {
-      case 2: launch_dma<2, 2, EPI, 4, HL>(pl, p, s); break;
-      case 4: launch_dma<4, 2, EPI, 4, HL>(pl, p, s); break;
-      case 6: launch_dma<6, 2, EPI, 4, HL>(pl, p, s); break;
-      default: launch_dma<8, 2, EPI, 4, HL>(pl, p, s); break;
+      case 2: return launch_dma<2, 2, EPI, 4, HL>(pl, p, s);
+      case 4: return launch_dma<4, 2, EPI, 4, HL>(pl, p, s);
+      case 6: return launch_dma<6, 2, EPI, 4, HL>(pl, p, s);
+      default: return launch_dma<8, 2, EPI, 4, HL>(pl, p, s);
     }
-  } else if (pl.nwv == 8) {
-    switch (pl.I) {
-      case 4: launch_dma<4, 4, EPI, 8, HL>(pl, p, s); break;
-      case 6: launch_dma<6, 4, EPI, 8, HL>(pl, p, s); break;
-      default: launch_dma<8, 4, EPI, 8, HL>(pl, p, s); break;
-    }
-  } else {
-    launch_dma<2, 4, EPI, 4, HL>(pl, p, s);
   }
+  if (pl.nwv == 8) {
+    switch (pl.I) {
+      case 4: return launch_dma<4, 4, EPI, 8, HL>(pl, p, s);
+      case 6: return launch_dma<6, 4, EPI, 8, HL>(pl, p, s);
+      default: return launch_dma<8, 4, EPI, 8, HL>(pl, p, s);
+    }
+  }
+  return launch_dma<2, 4, EPI, 4, HL>(pl, p, s);
 }
 
 template <int EPI>
-static void launch_typed(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
+static bool launch_typed(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
   const dim3 grid(pl.tiles_n, pl.tiles_m, pl.splits);
   if (pl.kind == 0) {
     if (pl.bm == 64) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, 2, 1>), grid, dim3(256), 0, s, p);
     else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1, 1, 4>), grid, dim3(256), 0, s, p);
-  } else if (pl.kind == 1) {
+    return true;
+  }
+  if (pl.kind == 1) {
     CB_LDS_LIMIT_ONCE((&gemm_bf16_kernel<EPI>), kSmemBf16);
     hipLaunchKernelGGL(gemm_bf16_kernel<EPI>, grid, dim3(256), kSmemBf16, s, p);
-  } else if (EPI == EPI_SEG && pl.hl) {
-    launch_dma_shape<EPI_SEG, true>(pl, p, s);
-  } else {
-    launch_dma_shape<EPI, false>(pl, p, s);
+    return true;
   }
+  if (EPI == EPI_SEG && pl.hl) return launch_dma_shape<EPI_SEG, true>(pl, p, s);
+  return launch_dma_shape<EPI, false>(pl, p, s);
 }
 
 hipError_t launch_gemm(const GemmArgs &g, hipStream_t s) {
@@ -1539,10 +1558,9 @@ hipError_t launch_gemm(const GemmArgs &g, hipStream_t s) {
   GemmParams p;
   const GemmPlan pl = fill_params(g, &p);
   if (pl.bad) return hipErrorInvalidValue;
-  if (g.epi == EPI_SEG) launch_typed<EPI_SEG>(pl, p, s);
-  else if (g.epi == EPI_SWIGLU) launch_typed<EPI_SWIGLU>(pl, p, s);
-  else launch_typed<EPI_F32>(pl, p, s);
-  return hipGetLastError();
+  const bool built = g.epi == EPI_SEG ? launch_typed<EPI_SEG>(pl, p, s)
+                     : g.epi == EPI_SWIGLU ? launch_typed<EPI_SWIGLU>(pl, p, s) : launch_typed<EPI_F32>(pl, p, s);
+  return built ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm_finish(const GemmArgs &g, hipStream_t s) {
