@@ -1228,9 +1228,12 @@ struct GemmPlan {
 };
 
 static int pick_row_blocks(int M) {
-  // padded rows divided by the tile height's share of the tallest one's rate (k-tile times of kDmaShapes; gate/up at 900 and
-  // 1900 rows with 256 instead of 192 rows per tile: 216 -> 192 and 391 -> 365 us on 28672 x 4096, 719 -> 692 and 1459 ->
-  // 1338 us on 57344 x 8192)
+  // Padded rows divided by the tile height's share of the tallest one's rate, as this projection's own launches show it with
+  // no row padded (1536 .. 6144 rows of 28672 x 4096 and 57344 x 8192, 256-column tiles): 192 rows 0.88 .. 0.94 of 256, int8
+  // weights 0.93 .. 1.00; 128 rows 0.81 .. 0.85, int8 0.76 .. 0.83.  (kDmaShapes has other ratios: those are of the other
+  // projections' short launches.)  The share of 64 rows only has to keep more than 64 rows off that tile.
+  // At 900 and 1900 rows, 256 instead of 192 rows per tile: 216 -> 192 and 391 -> 365 us on 28672 x 4096, 719 -> 692 and
+  // 1459 -> 1338 us on 57344 x 8192.
   const int cand[4] = {8, 6, 4, 2};
   const double eff[4] = {1.0, 0.92, 0.82, 0.62};
   int best = 8;
@@ -1390,7 +1393,10 @@ static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int f
     if (epi == EPI_SWIGLU) {
       // The last round of 256 workgroups, when less than half full, is shared: ts workgroups per
       // tile, each over 1/ts of K, plus a fix-up launch.  Worth it when the time saved on the
-      // round exceeds the round trip of the partial sums (~4 TB/s) and the extra launch.
+      // round exceeds the round trip of the partial sums (~4 TB/s) and the extra launch.  t_tile is more than a
+      // k-tile takes with every CU busy (256, 192, 128 rows x 256 columns 1.54, 1.27, 0.95 us), so the rule leans towards
+      // sharing; it is never wrong by that: at 54 row counts from 200 to 3136 of three shapes, bf16 and int8, every launch
+      // that shares takes 0.76 .. 1.00 of its time without (mean 0.92).
       const long full = ids / 256 * 256, tail = ids - full;
       int ts = tail > 0 ? (int)std::min<long>(4, 256 / tail) : 1;
       while (ts > 1 && k_tiles / ts < 8) --ts;
