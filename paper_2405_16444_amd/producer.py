@@ -16,7 +16,7 @@ def chunk_prefill(ctx: B.Context, layers: Sequence[Dict[str, torch.Tensor]], x_c
     """Returns (k_layers, v_layers): per layer a [n_rows_alloc, Hkv, dh] tensor whose
     rows [0, sum(chunk_lens)) hold the chunks' K/V as cached at positions 0.. ."""
     m = ctx.model
-    layers = layers[:m.n_layers]            # a longer list is fine, as for a program that keeps more than it runs
+    layers = [layers[l] for l in range(m.n_layers)]        # anything indexable; entries past the model's are not looked at
     n_ctx = sum(chunk_lens)
     # a tensor of its own for every layer's K and V: each can be kept, saved or freed without the others.  The chunks fill
     # rows [0, n_ctx), only the rest has to be cleared.
