@@ -13,7 +13,9 @@ selective layers (sum over layers >= 1 of the rows kept, divided by the GPU time
 layers), whole-call TTFT as median / p10 / p90 beside it, the roofline position of the
 dominant kernel class (the MFMA GEMMs) measured with HIP events inside the library, and
 the CPU oracle timed on a bounded sample of the same workload.  The other workloads of
-the configuration list follow in `workloads` (fewer steps each)."""
+the configuration list follow in `workloads` (fewer steps each): their times and rates in the line,
+which stays short enough to survive a reader that keeps the last few KB of the output, and every
+figure of each as a line of its own on stderr."""
 from __future__ import annotations
 
 import argparse
@@ -479,6 +481,24 @@ def copy_ceiling_gbs():
     return 2.0 * (1 << 30) / ms / 1e6
 
 
+def short(v):
+    """v with its floats cut to six significant digits."""
+    if isinstance(v, dict):
+        return {k: short(x) for k, x in v.items()}
+    if isinstance(v, (list, tuple)):
+        return [short(x) for x in v]
+    return float(f"{v:.6g}") if isinstance(v, float) else v
+
+
+def summary(r):
+    """One of the other workloads in the line: its call time, its rate and those of its two large kernel classes."""
+    out = {k: r[k] for k in ("workload", "ratio", "ttft_ms", "hkvd_token_layers_per_s", "launches_per_step") if k in r}
+    for c in ("gemm", "attention"):
+        if c in (r.get("kernel_classes") or {}):
+            out[c + "_tflops"] = r["kernel_classes"][c]["tflops"]
+    return short(out)
+
+
 def main():
     a = parse()
     if a.gpus != 1:
@@ -513,7 +533,8 @@ def main():
                              int8=int8)
             r.pop("_keep")
             r.pop("_workload")
-            extras.append(r)
+            print(json.dumps({"other_workload": r}), file=sys.stderr, flush=True)
+            extras.append(summary(r))
 
     cpu = None
     if not a.no_cpu_baseline:
@@ -531,11 +552,11 @@ def main():
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": w.model.dtype, "data": "synthetic",
         "config": {"workload": w.name, "ratio": w.ratio, "schedule": head["schedule"]},
-        "roofline": head.get("roofline"), "cpu_baseline": cpu,
-        "hbm_copy_ceiling_gbs": copy_ceiling_gbs(),
-        "kernel_classes": head.get("kernel_classes"), "launches_per_step": head.get("launches_per_step"),
-        "first_token": head.get("first_token"), "host_load": head.get("host_load"),
-        "graph_replay": head.get("graph_replay"), "workloads": extras,
+        "roofline": short(head.get("roofline")), "cpu_baseline": short(cpu),
+        "hbm_copy_ceiling_gbs": short(copy_ceiling_gbs()),
+        "kernel_classes": short(head.get("kernel_classes")), "launches_per_step": head.get("launches_per_step"),
+        "first_token": short(head.get("first_token")), "host_load": short(head.get("host_load")),
+        "graph_replay": short(head.get("graph_replay")), "workloads": extras,
     }
     print(json.dumps(res))
 
