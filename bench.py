@@ -102,7 +102,7 @@ def pmc_traffic(workload_name, schedule, ratio):
 
 
 def cpu_baseline(w, keep, full=False):
-    """The oracle as it stands, timed on this box's host cores on a bounded sample of the workload:
+    """The oracle as it stands, timed on this machine's host cores on a bounded sample of the workload:
     one dense (first) layer on a sub-length of the request and one selective layer at the workload's
     own row count against its full-length cache, at all cores and at one thread, with the L-layer
     figure as a labelled linear extrapolation."""
@@ -441,7 +441,7 @@ def run_workload(a, name, ratio, steps, warmup, headline, int8=False):
             kv_bytes = sum(t.numel() * t.element_size() for t in k_host[1:] + v_host[1:])   # layer 0 is recomputed in full, not loaded
             host_load = {"ttft_ms": float(np.median(hl_ms)), "kv_bytes_loaded": kv_bytes,
                          "serial_copy_ms_at_rate_seen": None, "equals_resident_result": same}
-            # plain copy of the same bytes alone, for the PCIe rate of this box
+            # plain copy of the same bytes alone, for the PCIe rate of this machine
             torch.cuda.synchronize()
             t0 = time.perf_counter()
             for dst, src in zip(k_work[1:] + v_work[1:], k_host[1:] + v_host[1:]):
@@ -462,7 +462,7 @@ def run_workload(a, name, ratio, steps, warmup, headline, int8=False):
 
 
 def copy_ceiling_gbs():
-    """Plain device-to-device copy of 1 GiB (read + write counted): the streaming rate this box reaches."""
+    """Plain device-to-device copy of 1 GiB (read + write counted): the streaming rate this machine reaches."""
     import torch
     x = torch.empty(1 << 30, dtype=torch.uint8, device="cuda")
     y = torch.empty_like(x)
@@ -502,7 +502,7 @@ def summary(r):
 def main():
     a = parse()
     if a.gpus != 1:
-        print("bench.py: this build runs on ONE GPU (the path has no collectives); "
+        print("bench.py: the benchmark runs on ONE GPU (the path has no collectives); "
               "--gpus must be 1", file=sys.stderr)
         sys.exit(2)
     import numpy as np

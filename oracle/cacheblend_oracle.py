@@ -71,7 +71,7 @@ def round_bf16(a):
 
 def dequantize_int8(lw):
     """Layer weights stored 8-bit (the paper serves its two larger models with 8-bit weights, Sec. 7.1,
-    without naming a scheme; this build's reading is weight-only symmetric int8 with one scale per output
+    without naming a scheme; this project's reading is weight-only symmetric int8 with one scale per output
     feature -- "parity unpinned" by the paper): every matrix name that comes with a `<name>_scale` vector
     means w[o, i] = q[o, i] * scale[o].  Returns the layer with those matrices in float64; everything
     downstream is the ordinary definition of the block."""
@@ -264,7 +264,7 @@ def realign_keys(k_pre, chunk_lens, m, kv_round=identity):
 def kv_deviation(k_new, v_new, k_old, v_old):
     """Per-token deviation between two KV rows: sum of squared differences over
     every kv head and channel of K and of V (Sec. 4.1 defines it as a difference of the two;
-    the norm is this build's reading)."""
+    the norm is this project's reading)."""
     dk = np.asarray(k_new, F64) - np.asarray(k_old, F64)
     dv = np.asarray(v_new, F64) - np.asarray(v_old, F64)
     n = dk.shape[0]

@@ -11,7 +11,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libcacheblend.so")
 SOURCES = ["elementwise.hip", "select.hip", "gemm.hip", "attention.hip", "head.hip", "api.hip"]
-# packed-fp32 VALU forms are disabled on purpose (they have misbehaved on the test machines)
+# packed-fp32 VALU forms are disabled on purpose (some of them have given wrong results)
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                "-Wno-unused-command-line-argument"]

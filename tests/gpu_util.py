@@ -16,7 +16,7 @@ TOL = {"f32": 1e-4, "bf16": 2e-2}     # max|gpu - oracle| / max|oracle| per tens
 
 
 def announce(*what):
-    """Name the case before the GPU step so a lost box still tells which one ran."""
+    """Name the case before the GPU step so a lost machine still tells which one ran."""
     print("[gpu-case]", *what, flush=True)
     sys.stdout.flush()
 

@@ -1,5 +1,5 @@
 """8-bit projection weights (Sec. 7.1 serves the two larger models with 8-bit weights; the scheme --
-weight-only symmetric int8, one scale per output feature -- is this build's reading, "parity unpinned"
+weight-only symmetric int8, one scale per output feature -- is this project's reading, "parity unpinned"
 by the paper).  The oracle dequantises (w = q * scale) and runs its ordinary definitions; the HIP
 projection kernels read the int8 weights themselves, multiply the exact integers on the matrix cores and
 scale the finished sums (input widths that are multiples of 64), or fall back to expanding a matrix to

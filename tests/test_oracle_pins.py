@@ -633,7 +633,7 @@ def rng_queries(w, seed):
 
 
 # --------------------------------------------------------------------------- #
-# 8-bit weights: w = q * scale per output feature (Sec. 7.1; scheme = this build's reading)
+# 8-bit weights: w = q * scale per output feature (Sec. 7.1; scheme = this project's reading)
 # --------------------------------------------------------------------------- #
 def test_dequantize_int8_hand_values_and_passthrough():
     lw = {"wq": np.array([[1, -2, 0], [127, -127, 64]], dtype=np.int8), "wq_scale": np.array([0.5, 0.01], dtype=np.float32),
