@@ -3,7 +3,7 @@
 // C[M, N] = A[M, K] * W[N, K]^T with both operands K-contiguous.
 //
 // bf16 storage: matrix-core MFMAs with float accumulation.  The main kernel
-// (gemm_bf16_dma_kernel, v_mfma_f32_16x16x32_bf16) streams (32*I) x (64*NB) x 64 tiles through LDS
+// (gemm_bf16_dma_kernel, v_mfma_f32_16x16x32_bf16) streams 64 .. 384 x 128 .. 256 x 64 tiles through LDS
 // rings filled by direct global->LDS loads, with an XCD-aware tile order; a simpler register-staged
 // 128x128x64 kernel (v_mfma_f32_32x32x16_bf16) covers K that is not a multiple of 64.
 // float storage: float MFMAs (v_mfma_f32_32x32x2_f32) on small tiles.
@@ -73,6 +73,7 @@ struct GemmParams {
   // K split dealt to the XCDs (splits = 2, 4 or 8): XCD x computes split x % splits of the n-tiles
   // congruent to x / splits mod 8 / splits, so each L2 holds only its own K slice of the activations
   int xcd_split;
+  int k_stagger;        // column tiles start at different k-tiles and wrap around (see pitch_is_power_of_two)
 };
 
 // weight row that feeds tile column gc (clamped into range)
@@ -205,15 +206,13 @@ __device__ __forceinline__ void lds_epilogue(const float *sC, int pitch, int row
 
 // ---------------------------------------------------------------------------
 // Main bf16 kernel.
-//   tile        BM = 32*I rows (I = 2,4,6,8) x BN = 64*NB columns (NB = 4, or 2 when that
-//               fills the CUs better or few rows leave the weights as the bound) x 64 k per stage (128-byte
-//               rows: every global request is a whole cache line)
-//   wavefronts  NWV = 4 as 2 x 2 (128-column tiles) or NWV = 8 as 2 x 4 (256-column tiles: two wavefronts per
-//               SIMD, each (BM/2) x 64).  A wavefront's sub-tile is cut into 16 x 16 blocks, one
-//               v_mfma_f32_16x16x32_bf16 each per 32-deep k-step.  Operand reads are issued by
-//               hand (inline ds_read_b128 + explicit s_waitcnt lgkmcnt) one half-step (half of
-//               the wavefront's rows of one k-step) ahead of the MFMAs that use them, slotted
-//               between those MFMAs.
+//   tile        BM = 16 RB WM rows x BN = 16 CB WN columns (kDmaTiles) x 64 k per stage (128-byte rows: every global
+//               request is a whole cache line)
+//   wavefronts  WM x WN, each RB x CB blocks of 16 x 16, one v_mfma_f32_16x16x32_bf16 each per 32-deep k-step: 2 x 2 (one per
+//               SIMD) for the 128-column tiles of few rows, 2 x 4 for 256 columns and 4 x 2 for the widths between and the tall
+//               tiles, both two per SIMD.  Operand reads are issued by hand (inline ds_read_b128 + explicit s_waitcnt
+//               lgkmcnt) one half-step (half of the wavefront's row blocks of one k-step) ahead of the MFMAs that use them,
+//               slotted between those MFMAs.
 //   LDS rings   activation tile (BM rows x 128 bytes) and weight tile (BN rows x 128 bytes), as
 //               many stages of both as fit in 160 KB, up to 6 (dma_even_stages below).
 //               Both are filled by global_load_lds_dwordx4 (no register staging).  A
@@ -249,19 +248,19 @@ constexpr int DMA_BK = 64;
 // 76 -> 67 us, at 640 rows of 57344 x 8192 603 -> 554 us; down 4096 x 14336 at 64 / 128 / 256 rows 36 -> 32, 41 -> 37, 51 -> 46 us;
 // int8 gate/up 57344 x 8192 at 64 / 165 / 300 rows 146 -> 130, 192 -> 166, 356 -> 315 us.
 // w8: int8 weights, 64 bytes per weight row and stage instead of 128 (the smallest tile: 80 KB, two workgroups per CU).
-constexpr int dma_even_stages(int I, int BN, bool w8) {
-  const int n = 160 * 1024 / (32 * I * 128 + BN * (w8 ? 64 : 128)), most = w8 && I == 2 && BN == 128 ? 5 : 6;
+constexpr int dma_even_stages(int BM, int BN, bool w8) {
+  const int n = 160 * 1024 / (BM * 128 + BN * (w8 ? 64 : 128)), most = w8 && BM == 64 && BN == 128 ? 5 : 6;
   return n > most ? most : n;
 }
-constexpr int dma_a_stages(int I, int BN, bool w8 = false) {
-  return dma_even_stages(I, BN, w8) >= 3 ? dma_even_stages(I, BN, w8) : 2;
+constexpr int dma_a_stages(int BM, int BN, bool w8 = false) {
+  return dma_even_stages(BM, BN, w8) >= 3 ? dma_even_stages(BM, BN, w8) : 2;
 }
-constexpr int dma_w_stages(int I, int BN, bool w8 = false) {
-  return dma_even_stages(I, BN, w8) >= 3 ? dma_even_stages(I, BN, w8) : 3;
+constexpr int dma_w_stages(int BM, int BN, bool w8 = false) {
+  return dma_even_stages(BM, BN, w8) >= 3 ? dma_even_stages(BM, BN, w8) : 3;
 }
-constexpr int dma_smem_bytes(int I, int BN, bool w8 = false) {
-  const int ring = dma_a_stages(I, BN, w8) * 32 * I * 128 + dma_w_stages(I, BN, w8) * BN * (w8 ? 64 : 128);
-  const int park = (I < 4 ? 32 * I : 128) * (BN + 4) * 4;
+constexpr int dma_smem_bytes(int BM, int BN, bool w8 = false) {
+  const int ring = dma_a_stages(BM, BN, w8) * BM * 128 + dma_w_stages(BM, BN, w8) * BN * (w8 ? 64 : 128);
+  const int park = (BM < 128 ? BM : 128) * (BN + 4) * 4;
   return ring > park ? ring : park;
 }
 
@@ -269,6 +268,9 @@ constexpr int dma_smem_bytes(int I, int BN, bool w8 = false) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(gptr), \
                                    (__attribute__((address_space(3))) void *)(lptr), 16, 0, cache)
 constexpr int kCacheNt = 2;                            // the instruction's nt bit
+// Variants of the main kernel: the start of a workgroup's k range may be staggered (a wrap test per tile, 0.7 % of a large launch)
+// and the weight loads may be non-temporal as well.
+enum { MODE_PLAIN, MODE_STAGGER, MODE_NT };
 
 // LDS operand read issued by hand: the result registers are valid only after a matching
 // lds_wait<N>() (N = number of younger reads that may still be in flight).
@@ -308,78 +310,84 @@ __device__ __forceinline__ void xcd_tile(int j, int xcd, int tiles_m, int nblk, 
   *mt = g * kGroupM + r % gm;
 }
 
-// silu(gate) * up from one wavefront's accumulators (RB x CB blocks of 16 x 16): blocks
-// 0..CB/2-1 of a lane hold gate columns, blocks CB/2..CB-1 the same columns of the up matrix;
-// lane l holds row (l % 16) and columns 4*(l/16) .. +3 of each block.  row0 / col0: first output
-// row / column of the wavefront.
-template <int RB, int CB>
-__device__ __forceinline__ void swiglu_from_registers(const f32x4 (&acc)[RB][CB], const GemmParams &p,
-                                                      int row0, int col0, int lane) {
-  const int l_row = lane & 15, l_col = (lane >> 4) * 4;
+// Swaps the upper 32 lanes of x with the lower 32 lanes of y.
+__device__ __forceinline__ void swap_halves(float &x, float &y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  x = __uint_as_float(r[0]);
+  y = __uint_as_float(r[1]);
+}
+// EPI_SWIGLU: gate and up of one output element have to end up in one lane.  A wavefront with an even number of column
+// blocks holds the gate columns in the first half of them and the same up columns in the second.  With an odd number every block holds 8 gate
+// columns (lanes 0 .. 31) and the same 8 up columns (lanes 32 .. 63), and pairs of blocks exchange halves (1 .. 2 % of the
+// launch, so only there).
+constexpr bool swiglu_mixed_blocks(int CB) { return CB % 2 != 0; }
+// From the sums of two such blocks, x and y, in place: x the gate and y the up values of four adjacent output columns per
+// lane -- lanes 0 .. 31 those of x's block, lanes 32 .. 63 those of y's.
+__device__ __forceinline__ void pair_gate_up(f32x4 &x, f32x4 &y) {
 #pragma unroll
-  for (int i = 0; i < RB; ++i) {
-    const int gr = row0 + i * 16 + l_row;
-    if (gr >= p.M) continue;
-    bf16 *orow = reinterpret_cast<bf16 *>(p.dst[0]) + (size_t)gr * p.ld[0];
+  for (int r = 0; r < 4; ++r) {
+    float a = x[r], b = y[r];
+    swap_halves(a, b);
+    x[r] = a;
+    y[r] = b;
+  }
+}
+// first of the four output columns, within the wavefront's, that a lane holds of block jb (and, mixed, of jb + 1)
+template <int CB> __device__ __forceinline__ int swiglu_lane_col(int jb, int lane) {
+  return swiglu_mixed_blocks(CB) ? (jb + (lane >> 5)) * 8 + ((lane >> 4) & 1) * 4 : jb * 16 + (lane >> 4) * 4;
+}
+// silu(g) * u = g * u / (1 + 2^(-g log2 e)) of four adjacent columns from gc on, into row orow
+__device__ __forceinline__ void store_swiglu(const f32x4 &g, const f32x4 &u, bf16 *orow, int gc, int N) {
+  float o[4];
 #pragma unroll
-    for (int jb = 0; jb < CB / 2; ++jb) {
-      const int gc = col0 + jb * 16 + l_col;
-      float o[4];
+  for (int r = 0; r < 4; ++r) {
+    const float den = 1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g[r]);
+    o[r] = g[r] * u[r] * __builtin_amdgcn_rcpf(den);
+  }
+  if (gc + 3 < N) {
+    store4<bf16>(orow + gc, o[0], o[1], o[2], o[3]);
+  } else {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float gt = acc[i][jb][r], up = acc[i][jb + CB / 2][r];
-        // silu(g) * u = g * u / (1 + 2^(-g log2 e))
-        const float den = 1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gt);
-        o[r] = gt * up * __builtin_amdgcn_rcpf(den);
-      }
-      if (gc + 3 < p.N) {
-        store4<bf16>(orow + gc, o[0], o[1], o[2], o[3]);
-      } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (gc + r < p.N) orow[gc + r] = (bf16)o[r];
-      }
-    }
+    for (int r = 0; r < 4; ++r)
+      if (gc + r < N) orow[gc + r] = (bf16)o[r];
   }
 }
 
 // Completes the tiles that several workgroups of the SwiGLU launch shared along K.  The partial
 // sums lie in register order: [slot][split][wavefront][16-row block i][16-column block jb][lane][4].
-// One wavefront here owns four (wavefront, i, gate block jb) units of a tile in turn: it adds the gate and
-// the up block over the splits in ascending K order and applies the epilogue.
-template <int I, int NB, int NWV>
+// One wavefront here owns four (wavefront, i, pair of blocks) units of a tile in turn: it adds both
+// blocks over the splits in ascending K order and applies the epilogue.
+template <int RB, int CB, int WM, int WN>
 __global__ __launch_bounds__(256) void swiglu_tail_kernel(GemmParams p, int tiles_m, int tiles_n) {
-  constexpr int IH = I / 2, BM = 32 * I, BN = 64 * NB, WN = NWV / 2, NBW = 2 * NB / WN;
-  constexpr int RB = I, CB = 2 * NBW, HB = CB / 2;
-  constexpr int UNITS = NWV * RB * HB;                    // per tile; a multiple of 16
+  constexpr int BM = 16 * RB * WM, BN = 16 * CB * WN, NWV = WM * WN, HB = (CB + 1) / 2;
+  constexpr bool MIXED = swiglu_mixed_blocks(CB);
+  constexpr int UNITS = NWV * RB * HB;                    // per tile
   const int lane = threadIdx.x & 63;
-  const int slot = blockIdx.x / (UNITS / 16);
+  constexpr int PER = (UNITS + 15) / 16;                  // workgroups per tile, four wavefronts of four units
+  const int slot = blockIdx.x / PER;
   const int xcd = slot & 7, j = (p.tail_first >> 3) + (slot >> 3);
   int nt, mt;
   xcd_tile(j, xcd, tiles_m, (tiles_n + 7) >> 3, &nt, &mt);
   if (nt >= tiles_n) return;
-  const int l_row = lane & 15, l_col = (lane >> 4) * 4;
   for (int q = 0; q < 4; ++q) {
-    const int u = ((blockIdx.x % (UNITS / 16)) * 4 + (threadIdx.x >> 6)) * 4 + q;
-    const int wave = u / (RB * HB), i = (u / HB) % RB, jb = u % HB;
+    const int u = ((blockIdx.x % PER) * 4 + (threadIdx.x >> 6)) * 4 + q;
+    if (u >= UNITS) break;
+    const int wave = u / (RB * HB), i = (u / HB) % RB, jb = u % HB * (MIXED ? 2 : 1);
+    const bool two = jb + 1 < CB;                         // MIXED: the last block has no partner
+    const int other = MIXED ? (two ? 64 * 4 : 0) : HB * 64 * 4;
     const float *pg = p.partial + (size_t)slot * p.tail_splits * (BM * BN) + (size_t)wave * (RB * CB * 4 * 64) +
                       (size_t)((i * CB + jb) * 64 + lane) * 4;
-    f32x4 gate = {0.f, 0.f, 0.f, 0.f}, up = {0.f, 0.f, 0.f, 0.f};
+    f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = {0.f, 0.f, 0.f, 0.f};
     for (int zz = 0; zz < p.tail_splits; ++zz, pg += BM * BN) {
-      gate += *reinterpret_cast<const f32x4 *>(pg);
-      up += *reinterpret_cast<const f32x4 *>(pg + HB * 64 * 4);
+      x += *reinterpret_cast<const f32x4 *>(pg);
+      y += *reinterpret_cast<const f32x4 *>(pg + other);
     }
+    if (MIXED) pair_gate_up(x, y);
     const int wm = wave / WN, wn = wave % WN;
-    const int gc = nt * (BN / 2) + wn * (BN / WN / 2) + jb * 16 + l_col;
-    const int gr = mt * BM + wm * IH * 32 + i * 16 + l_row;
-    if (gr >= p.M) continue;
-    bf16 *orow = reinterpret_cast<bf16 *>(p.dst[0]) + (size_t)gr * p.ld[0];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      if (gc + r >= p.N) continue;
-      const float den = 1.f + __builtin_amdgcn_exp2f(-1.4426950408889634f * gate[r]);
-      orow[gc + r] = (bf16)(gate[r] * up[r] * __builtin_amdgcn_rcpf(den));
-    }
+    const int gc = nt * (BN / 2) + wn * CB * 8 + swiglu_lane_col<CB>(jb, lane);
+    const int gr = mt * BM + (WM == 4 ? i * WM + wm : wm * RB + i) * 16 + (lane & 15);
+    if (gr >= p.M || (MIXED && !two && lane >= 32)) continue;
+    store_swiglu(x, y, reinterpret_cast<bf16 *>(p.dst[0]) + (size_t)gr * p.ld[0], gc, p.N);
   }
 }
 
@@ -390,28 +398,33 @@ __global__ __launch_bounds__(256) void swiglu_tail_kernel(GemmParams p, int tile
 // other columns (Q beside K and V in one launch) are ordinary ones; which kind a workgroup has is uniform.
 // W8: the weights are int8 (one byte per element in memory and in LDS, half the traffic of both); a fragment
 // is expanded to bf16 in registers right before its k-step and the per-column scales multiply the finished sums.
-// NT: the weight loads are non-temporal (GemmPlan::nt).
-template <int I, int NB, int EPI, int NWV, bool HL = false, bool W8 = false, bool NT = false>
-__global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
-  constexpr int BM = 32 * I, BN = 64 * NB, SA = dma_a_stages(I, BN, W8), SW = dma_w_stages(I, BN, W8), DMA_CP = BN + 4;
+// MODE: GemmPlan::mode.
+template <int RB, int CB, int WM, int WN, int EPI, bool HL = false, bool W8 = false, int MODE = 0>
+__global__ __launch_bounds__(64 * WM * WN) void gemm_bf16_dma_kernel(GemmParams p, int tiles_m, int tiles_n) {
+  constexpr int NWV = WM * WN, BM = 16 * RB * WM, BN = 16 * CB * WN;
+  constexpr int SA = dma_a_stages(BM, BN, W8), SW = dma_w_stages(BM, BN, W8), DMA_CP = BN + 4;
   constexpr int WE = W8 ? 1 : 2;                         // bytes per weight element
-  static_assert(!HL || EPI == EPI_SEG, "operand pairs are for the K/V projection only");
+  static_assert(!HL || (EPI == EPI_SEG && WM == 2), "operand pairs are for the K/V projection only");
+
   constexpr int A_STAGE = BM * 128, W_STAGE = BN * 64 * WE, W_RING = SA * A_STAGE;
-  constexpr int WN = NWV / 2;                            // wavefronts as 2 x WN
-  constexpr int NBW = 2 * NB / WN;                       // 32-column groups per wavefront
-  constexpr int LA = BM / (8 * NWV), LW = W_STAGE / (1024 * NWV);   // 16-byte loads per lane per tile (1 KB per wavefront each)
-  static_assert(LW >= 2 && LW % 2 == 0, "the load schedule issues a weight tile in two halves");
+  constexpr int A_GROUPS = BM / 8, W_GROUPS = BN * WE / 16;   // wavefront-wide loads (1 KB each) of a tile
+  constexpr int LA = A_GROUPS / NWV, LW = (W_GROUPS + NWV - 1) / NWV;   // per wavefront: 16-byte loads per lane
+  static_assert(A_GROUPS % NWV == 0, "the load schedule");
   static_assert(SA >= 2 && SW >= SA, "the vmcnt bookkeeping below");
-  static_assert(dma_smem_bytes(I, BN, W8) <= 160 * 1024, "LDS of a CU");
-  constexpr int IH = I / 2;                              // 32-row groups per wavefront
-  constexpr int RB = I, CB = 2 * NBW;                    // 16-row / 16-column MFMA blocks per wavefront
+  static_assert(dma_smem_bytes(BM, BN, W8) <= 160 * 1024, "LDS of a CU");
+  constexpr int IH = (RB + 1) / 2;                       // row blocks of a k-step's first half-step; the second has RB - IH
   constexpr int OUT_COLS = (EPI == EPI_SWIGLU) ? BN / 2 : BN;
+  // Four wavefronts along M are dealt the row blocks in turn, so that a partly filled row tile occupies all of them alike (two that
+  // share a SIMD would not gain by it: 28672 x 4096 at 500 rows 115 us with their blocks together, 119 us in turn; with
+  // operand pairs wm = 0 has to be the high parts, wm = 1 the low parts).
+  constexpr int RSTEP = WM == 4 ? 4 : 1;                     // tile row blocks between two blocks of a wavefront
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   // scalar, so that the LDS targets of the loads are computed on the scalar unit: a vector instruction of one
   // wavefront does not overlap the MFMAs of the other wavefront on its SIMD, it costs matrix-core time
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WN, wn = wave % WN;              // 2 x WN wavefronts, (BM/2) x (BN/WN) each
+  const int wm = wave / WN, wn = wave % WN;              // WM x WN wavefronts
+  const int row_blk0 = WM == 4 ? wm : wm * RB;                // block i of this wavefront is block row_blk0 + i * RSTEP of the tile
 
   // XCD-aware tile order
   int xcd = blockIdx.x & 7, j = blockIdx.x >> 3, tail_z = -1;
@@ -422,10 +435,12 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
   }
   int z, nt, mt;
   bool hl = false;                                       // this tile takes the pair
+  int groups = 8;                                        // XCDs that share this split
   {
     // a split-dealing launch: XCDs that share one split; else all 8 share every split
     const bool dealt = EPI != EPI_SWIGLU && p.xcd_split;
-    const int groups = dealt ? 8 / p.splits : 8, x = dealt ? xcd / p.splits : xcd;
+    groups = dealt ? 8 / p.splits : 8;
+    const int x = dealt ? xcd / p.splits : xcd;
     const int nblk = (tiles_n + groups - 1) / groups;
     const int nblk_hl = HL ? (p.hl_tiles_n + groups - 1) / groups : 0, cnt_hl = HL ? nblk_hl * p.hl_tiles_m : 0;
     const int per_z = nblk * tiles_m + cnt_hl;
@@ -446,10 +461,17 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
   const int kb = (tail_z >= 0 ? tail_z : z) * kps;
   const int ke = min(p.K, kb + kps);
   const int nk = (ke - kb) / DMA_BK;
+  const int k_first = MODE != MODE_PLAIN && p.k_stagger && nk > 0 ? (2 * (nt / groups) + nt % groups) % nk : 0;
+  // first k of the t-th tile this workgroup walks (past the last: the last)
+  auto k_of = [&](int t) {
+    const int q = min(t, nk - 1) + k_first;
+    return (MODE != MODE_PLAIN && q >= nk ? q - nk : q) * DMA_BK;
+  };
 
   // global source of each of this lane's loads per tile (row pointer + swizzled chunk)
   const bf16 *src_a[LA];
   const char *src_w[LW];
+  auto w_group = [&](int i) { return W_GROUPS % NWV == 0 ? wave + NWV * i : min(wave + NWV * i, W_GROUPS - 1); };
 #pragma unroll
   for (int i = 0; i < LA; ++i) {
     const int r = (wave + NWV * i) * 8 + (lane >> 3);         // row of the activation tile
@@ -464,13 +486,13 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
   for (int i = 0; i < LW; ++i) {
     // a wavefront-wide load brings 1 KB: 8 rows of 128 bytes, or 16 rows of 64 bytes of int8 weights, whose four
     // 16-byte chunks are swizzled by f8(r) = (r >> 2) & 3 (the 8-byte fragment reads of 16 rows then hit 64 banks)
-    const int r = W8 ? (wave + NWV * i) * 16 + (lane >> 2) : (wave + NWV * i) * 8 + (lane >> 3);   // row of the weight tile
+    // (where the tile's loads do not divide evenly the last ones are repeated: every wavefront issues the same number)
+    const int r = W8 ? w_group(i) * 16 + (lane >> 2) : w_group(i) * 8 + (lane >> 3);   // row of the weight tile
     const int chunk = W8 ? (lane & 3) ^ ((r >> 2) & 3) : (lane & 7) ^ ((r & 7) ^ ((r >> 3) & 1));
     const char *wrow;
     if (EPI == EPI_SWIGLU) {
-      // each wavefront's half of the tile columns holds its gate columns followed by the SAME
-      // up columns, so that a lane ends up with gate and up of one output element
-      constexpr int WC = BN / WN, HC = WC / 2;         // columns per wavefront / per operand
+      // (swiglu_mixed_blocks)
+      constexpr int WC = swiglu_mixed_blocks(CB) ? 16 : BN / WN, HC = WC / 2;   // run of gate, then of the same up columns
       const int which = (r % WC) / HC, oc = min(n0 + (r / WC) * HC + (r % HC), p.N - 1);
       wrow = reinterpret_cast<const char *>(p.w[which]) + (size_t)oc * p.K * WE;
     } else {
@@ -482,19 +504,19 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
   // that every tile issues the same number of loads
   auto issue_one = [&](int t, int idx) {
     if (idx < LA) {
-      const int k0 = min(t, nk - 1) * DMA_BK;
+      const int k0 = k_of(t);
       CB_GLDS16(src_a[idx] + k0, smem + (t % SA) * A_STAGE + (wave + NWV * idx) * 1024, 0);
     } else {
       const int tw = t + SW - SA;                     // the weight ring runs SW - SA tiles further ahead
-      const int k0 = min(tw, nk - 1) * DMA_BK;
-      CB_GLDS16(src_w[idx - LA] + k0 * WE, smem + W_RING + (tw % SW) * W_STAGE + (wave + NWV * (idx - LA)) * 1024, NT ? kCacheNt : 0);
+      const int k0 = k_of(tw);
+      CB_GLDS16(src_w[idx - LA] + k0 * WE, smem + W_RING + (tw % SW) * W_STAGE + w_group(idx - LA) * 1024, MODE == MODE_NT ? kCacheNt : 0);
     }
   };
   auto issue_w = [&](int t) {
-    const int k0 = min(t, nk - 1) * DMA_BK;
+    const int k0 = k_of(t);
 #pragma unroll
     for (int i = 0; i < LW; ++i)
-      CB_GLDS16(src_w[i] + k0 * WE, smem + W_RING + (t % SW) * W_STAGE + (wave + NWV * i) * 1024, NT ? kCacheNt : 0);
+      CB_GLDS16(src_w[i] + k0 * WE, smem + W_RING + (t % SW) * W_STAGE + w_group(i) * 1024, MODE == MODE_NT ? kCacheNt : 0);
   };
 
   // v_mfma_f32_16x16x32_bf16 with the WEIGHT fragment as its first operand: block (i, jb) of a wavefront is
@@ -516,10 +538,10 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
     int rd[2];                                                    // k-step ks (32 deep) reads chunk 4*ks + l/16
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) rd[ks] = (lane & 15) * 128 + (((4 * ks + (lane >> 4)) ^ sw) << 4);
-    const int a_off = (wm * IH * 32) * 128, b_off = (wn * (BN / WN)) * 128;
+    const int a_off = row_blk0 * 16 * 128, b_off = (wn * (BN / WN)) * 128;
     int blk_ok = 0;                                    // bit i: 16-row block i of this wavefront holds a real row
 #pragma unroll
-    for (int i = 0; i < RB; ++i) blk_ok |= (m0 + (hl ? 0 : wm * IH * 32) + i * 16 < p.M) << i;
+    for (int i = 0; i < RB; ++i) blk_ok |= (m0 + (hl ? i : row_blk0 + i * RSTEP) * 16 < p.M) << i;
     blk_ok = __builtin_amdgcn_readfirstlane(blk_ok);
     // one scalar flag per block, re-read through an empty asm at every test: left alone the compiler hoists the
     // tests out of the loop as lane masks and rebuilds their complements with vector instructions inside it
@@ -543,7 +565,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
     for (int ks = 0; ks < 2; ++ks)
       rd8[ks] = (lane & 15) * 64 + (((2 * ks + (lane >> 5)) ^ ((lane >> 2) & 3)) << 4) + ((lane >> 4) & 1) * 8;
     const int b_off8 = (wn * (BN / WN)) * 64;
-    constexpr int NM = IH * CB;                        // MFMAs per half-step per wavefront
+    constexpr int NM = IH * CB;                        // MFMAs per (first) half-step per wavefront
     constexpr int NL = LA + LW;                        // loads per tile per lane
     constexpr int NSLOT = NM > IH + CB ? NM : IH + CB;
     // fragment number n (16 rows each, 2 KB apart) of the operand whose first fragment this lane reads at `base`
@@ -559,6 +581,14 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
         default: lds_read8<7168>(dst, base); break;
       }
     };
+    auto read_fa = [&](bf16x8 &dst, unsigned base, int n) {    // activation fragment: row blocks RSTEP apart
+      switch (n) {
+        case 0: lds_read16<0>(dst, base); break;
+        case 1: lds_read16<2048 * RSTEP>(dst, base); break;
+        case 2: lds_read16<4096 * RSTEP>(dst, base); break;
+        default: lds_read16<6144 * RSTEP>(dst, base); break;
+      }
+    };
     auto read_frag = [&](bf16x8 &dst, unsigned base, int n) {
       switch (n) {
         case 0: lds_read16<0>(dst, base); break;
@@ -571,6 +601,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
         default: lds_read16<14336>(dst, base); break;
       }
     };
+    static_assert(IH <= 4 && CB <= 8, "fragment offsets above");
     const unsigned lds0 = (unsigned)(size_t)smem;
     // One half-step hs of the current tile: its MFMAs, with the operand reads of the half-step that follows
     // (half-step hsn of tile tn: its activation fragments, and the weight fragments too when it opens a
@@ -580,18 +611,19 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
       const int ab = hs & 1, bb = W8 ? 0 : (hs >> 1) & 1, h = hs & 1;
       const int nab = hsn & 1, nbb = W8 ? 0 : (hsn >> 1) & 1;
       const bool with_w = (hsn & 1) == 0;
-      const unsigned base_a = lds0 + (tn % SA) * A_STAGE + a_off + (hsn & 1) * (IH * 2048) + rd[hsn >> 1];
+      const unsigned base_a = lds0 + (tn % SA) * A_STAGE + a_off + (hsn & 1) * (IH * RSTEP * 2048) + rd[hsn >> 1];
       const unsigned base_w = lds0 + W_RING + (tn % SW) * W_STAGE + (W8 ? b_off8 + rd8[hsn >> 1] : b_off + rd[hsn >> 1]);
-      const int n_reads = next_reads ? IH + (with_w ? CB : 0) : 0;
+      const int nia = (hsn & 1) ? RB - IH : IH;        // row blocks of the next half-step
+      const int n_reads = next_reads ? nia + (with_w ? CB : 0) : 0;
       // what rides along in MFMA slot j: the global loads q0 .. q1-1 of tile tl, spread evenly over the slots of
       // this half-step, and one operand read of the next half-step
       auto slot_work = [&](int j) {
 #pragma unroll
         for (int q = q0 + j * (q1 - q0) / NSLOT; q < q0 + (j + 1) * (q1 - q0) / NSLOT; ++q) issue_one(tl, q);
         if (j < n_reads) {
-          if (j < IH) read_frag(fa[nab][j], base_a, j);
-          else if (W8) read_wq(fq[j - IH], base_w, j - IH);
-          else read_frag(fb[nbb][j - IH], base_w, j - IH);
+          if (j < nia) read_fa(fa[nab][j], base_a, j);
+          else if (W8) read_wq(fq[j - nia], base_w, j - nia);
+          else read_frag(fb[nbb][j - nia], base_w, j - nia);
         }
         __builtin_amdgcn_sched_barrier(0);
       };
@@ -610,7 +642,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
         }
       } else {
 #pragma unroll
-      for (int ii = 0; ii < IH; ++ii) {
+      for (int ii = 0; ii < (h ? RB - IH : IH); ++ii) {
         // a 16-row block that lies wholly past the last row (only in the last row tile) is skipped: the
         // wavefront sharing the SIMD gets the matrix core instead.  One scalar branch per row block, not per
         // MFMA; the loads and reads of its slots follow outside the branch, so no register is written on two paths.
@@ -625,11 +657,11 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
       }
       }
 #pragma unroll
-      for (int j = NM; j < NSLOT; ++j) slot_work(j);
+      for (int j = h ? (RB - IH) * CB : NM; j < NSLOT; ++j) slot_work(j);
       if (next_reads) {
         lds_wait<0>();
 #pragma unroll
-        for (int i = 0; i < IH; ++i) lds_pin(fa[nab][i]);
+        for (int i = 0; i < nia; ++i) lds_pin(fa[nab][i]);
         if (with_w) {
 #pragma unroll
           for (int jb = 0; jb < CB; ++jb) {
@@ -657,7 +689,7 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
     vm_wait<YOUNGER + NL>();
     wg_barrier();
 #pragma unroll
-    for (int q = 0; q < IH; ++q) read_frag(fa[0][q], lds0 + a_off + rd[0], q);
+    for (int q = 0; q < IH; ++q) read_fa(fa[0][q], lds0 + a_off + rd[0], q);
 #pragma unroll
     for (int q = 0; q < CB; ++q) {
       if (W8) read_wq(fq[q], lds0 + W_RING + b_off8 + rd8[0], q);
@@ -700,12 +732,14 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
   const int l_row = lane & 15, l_col = (lane >> 4) * 4;
   if (W8) {
     // the sums are over integer weights: scale every output column
+    f32x4 scale[CB];
 #pragma unroll
     for (int jb = 0; jb < CB; ++jb) {
       f32x4 sc = {0.f, 0.f, 0.f, 0.f};
       if (EPI == EPI_SWIGLU) {
-        const int gc = n0 + wn * (BN / WN / 2) + (jb % (CB / 2)) * 16 + l_col;
-        const float *ps = p.w_scale[jb / (CB / 2)];
+        constexpr bool MIXED = swiglu_mixed_blocks(CB);
+        const int gc = n0 + wn * CB * 8 + (MIXED ? jb * 8 + (l_col & 7) : jb % (CB / 2) * 16 + l_col);
+        const float *ps = (MIXED ? lane < 32 : jb < CB / 2) ? p.w_scale[0] : p.w_scale[1];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
           if (gc + r < p.N) sc[r] = ps[gc + r];
@@ -719,8 +753,13 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
         for (int r = 0; r < 4; ++r)
           if (gc + r < p.N) sc[r] = ps[gc + r];
       }
+      scale[jb] = sc;
+    }
 #pragma unroll
-      for (int i = 0; i < RB; ++i) acc[i][jb] *= sc;
+    for (int i = 0; i < RB; ++i) {
+#pragma unroll
+      for (int jb = 0; jb < CB; ++jb) acc[i][jb] *= scale[jb];
+      __builtin_amdgcn_sched_barrier(0);               // in place, one row block at a time
     }
   }
   if (EPI == EPI_SWIGLU && tail_z >= 0) {
@@ -735,14 +774,28 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
     return;
   }
   if (EPI == EPI_SWIGLU) {
-    swiglu_from_registers<RB, CB>(acc, p, m0 + wm * IH * 32, n0 + wn * (BN / WN / 2), lane);
+    constexpr bool MIXED = swiglu_mixed_blocks(CB);
+#pragma unroll
+    for (int i = 0; i < RB; ++i) {
+      __builtin_amdgcn_sched_barrier(0);               // one row block at a time, else the sums and results of several are live
+      const int gr = m0 + (row_blk0 + i * RSTEP) * 16 + l_row;
+      bf16 *orow = reinterpret_cast<bf16 *>(p.dst[0]) + (size_t)gr * p.ld[0];
+#pragma unroll
+      for (int jb = 0; jb < (MIXED ? CB : CB / 2); jb += MIXED ? 2 : 1) {
+        const bool two = jb + 1 < CB;
+        f32x4 g = acc[i][jb], u = acc[i][MIXED ? (two ? jb + 1 : jb) : jb + CB / 2];
+        if (MIXED) pair_gate_up(g, u);
+        if (gr < p.M && (!MIXED || two || lane < 32))
+          store_swiglu(g, u, orow, n0 + wn * CB * 8 + swiglu_lane_col<CB>(jb, lane), p.N);
+      }
+    }
     return;
   }
   if (EPI != EPI_SEG) {
     // raw sums straight from the accumulator registers, four adjacent columns per lane
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
-      const int gr = m0 + wm * IH * 32 + i * 16 + l_row;
+      const int gr = m0 + (row_blk0 + i * RSTEP) * 16 + l_row;
       if (gr >= p.M) continue;
       float *prow = p.partial + ((size_t)z * p.M + gr) * p.N;
 #pragma unroll
@@ -783,15 +836,15 @@ __global__ __launch_bounds__(64 * NWV) void gemm_bf16_dma_kernel(GemmParams p, i
     return;
   }
   // park and walk the tile in passes of at most 128 rows (LDS holds 128 x 260 floats)
-  constexpr int PASSES = (I + 3) / 4;
+  constexpr int BLOCKS = BM / 16, PASSES = (BLOCKS + 7) / 8;
 #pragma unroll
   for (int ps = 0; ps < PASSES; ++ps) {
     const int i0 = ps * 8;                                   // first 16-row block of the pass
-    const int nb = (2 * I - i0) < 8 ? (2 * I - i0) : 8;
+    const int nb = (BLOCKS - i0) < 8 ? (BLOCKS - i0) : 8;
     if (ps > 0) __syncthreads();
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
-      const int ib = wm * RB + i;                            // this wavefront's 16-row block within the tile
+      const int ib = row_blk0 + i * RSTEP;                   // this wavefront's 16-row block within the tile
       if (ib >= i0 && ib < i0 + 8) {
 #pragma unroll
         for (int jb = 0; jb < CB; ++jb)
@@ -1208,10 +1261,26 @@ __global__ __launch_bounds__(256) void resid_norm_finish_row_kernel(GemmParams p
 // ---------------------------------------------------------------------------
 // Host side: choice of kernel, tile height and K split; launches.
 // ---------------------------------------------------------------------------
+// Tiles of the direct-to-LDS kernel: WM x WN wavefronts of RB x CB blocks of 16 x 16.
+struct DmaTile {
+  int RB, CB, WM, WN;
+  constexpr int bm() const { return 16 * RB * WM; }
+  constexpr int bn() const { return 16 * CB * WN; }
+};
+static constexpr DmaTile kDmaTiles[] = {
+    {2, 4, 2, 2}, {4, 4, 2, 2}, {6, 4, 2, 2},                                    // 64, 128, 192 x 128: a wavefront per SIMD
+    {4, 4, 2, 4}, {6, 4, 2, 4}, {8, 4, 2, 4},                                    // 128, 192, 256 x 256, two per SIMD
+    {2, 5, 4, 2}, {2, 7, 4, 2},                                                  // 128 x 160, 224
+    {3, 4, 4, 2}, {3, 5, 4, 2}, {3, 7, 4, 2},                                    // 192 x 128, 160, 224
+    {4, 4, 4, 2}, {4, 5, 4, 2}, {4, 7, 4, 2},                                    // 256 x 128, 160, 224
+    {5, 5, 4, 2}, {5, 6, 4, 2}, {6, 4, 4, 2}, {6, 5, 4, 2}};                     // 320 x 160, 192; 384 x 128, 160
+constexpr int kNumDmaTiles = sizeof(kDmaTiles) / sizeof(kDmaTiles[0]);
+enum { T64x128, T128x128, T192x128, T128x256, T192x256, T256x256, T128x160, T128x224, T192x128w8, T192x160, T192x224,
+       T256x128w8, T256x160, T256x224, T320x160, T320x192, T384x128, T384x160 };
+
 struct GemmPlan {
   int kind;        // 0 float, 1 register-staged bf16, 2 direct-to-LDS bf16
-  int I, NB;       // kind 2: the kernel's tile = 32I activation-tile rows x 64NB columns
-  int nwv;         // kind 2: wavefronts per workgroup (4, or 8 = two per SIMD for the 256-column tiles)
+  int tile;        // kind 2: index into kDmaTiles
   int hl;          // output columns that take (high, low) activation pairs (bf16 EPI_SEG only)
   int bm, out_cols, bk;   // bm: output rows per tile (of the columns without pairs, kind 2)
   int hl_tiles_m, hl_tiles_n;             // kind 2: tiles of the columns with pairs; tiles_m, tiles_n: of the others
@@ -1221,35 +1290,25 @@ struct GemmPlan {
   long grid_ids;                                   // kind 2: workgroups of the main launch
   int xcd_split;                                   // kind 2: splits dealt to XCDs (see GemmParams)
   int w8;                                          // kind 2: int8 weights read by the kernel itself
-  int nt;                                          // kind 2: non-temporal weight loads
+  int mode;                                        // kind 2: MODE_PLAIN, MODE_STAGGER or MODE_NT (non-temporal weight loads)
+  int k_stagger;                                   // kind 2: column tiles start at different k-tiles
   int raw;                                         // sums are parked in `partial` and a finish launch completes them
   size_t partial_floats;
   bool bad;                                        // needs scratch the caller did not give
 };
 
-static int pick_row_blocks(int M) {
-  // Padded rows divided by the tile height's share of the tallest one's rate, as this projection's own launches show it with
-  // no row padded (1536 .. 6144 rows of 28672 x 4096 and 57344 x 8192, 256-column tiles): 192 rows 0.88 .. 0.94 of 256, int8
-  // weights 0.93 .. 1.00; 128 rows 0.81 .. 0.85, int8 0.76 .. 0.83.  (kDmaShapes has other ratios: those are of the other
-  // projections' short launches.)  The share of 64 rows only has to keep more than 64 rows off that tile.
-  // At 900 and 1900 rows, 256 instead of 192 rows per tile: 216 -> 192 and 391 -> 365 us on 28672 x 4096, 719 -> 692 and
-  // 1459 -> 1338 us on 57344 x 8192.
-  const int cand[4] = {8, 6, 4, 2};
-  const double eff[4] = {1.0, 0.92, 0.82, 0.62};
-  int best = 8;
-  double best_cost = 1e30;
-  for (int i = 0; i < 4; ++i) {
-    const int bm = 32 * cand[i];
-    const double cost = (double)ceil_div(M, bm) * bm / eff[i];
-    if (cost < best_cost - 1e-9) { best_cost = cost; best = cand[i]; }
-  }
-  return best;
-}
-
 // Weight loads are non-temporal for bf16 matrices this large that a single row tile reads: every weight is then read by one
 // workgroup alone.  57344 x 8192 at 16 .. 128 rows 187 -> 165 us, 8192 x 28672 at 64 rows 100 -> 84 us, 28672 x 4096 54 -> 50 us;
 // matrices of 30 .. 50 MB lost up to 10 %, several row tiles (they share weight tiles in L2) up to 20 %, int8 weights up to 20 %.
 constexpr double kNtMinBytes = 128e6;
+
+// Rows of weights whose pitch is a power of two of at least 8 KB all start at the same place of the memory channels' interleave, and
+// workgroups that walk K in step ask few channels at a time.  With a single row tile (nothing then ties the column tiles
+// together but the small activation slices) neighbouring column tiles of an XCD start two k-tiles apart, those of neighbouring
+// XCDs one, and wrap around.  28672 x 4096 at 32 / 64 / 120 rows 47.8 -> 38.6, 48.4 -> 40.2, 52.3 -> 47.0 us; 57344 x 8192 at
+// 32 rows 163 -> 153 us; 8192 x 8192 at 120 / 250 rows 46.1 -> 41.4, 59.4 -> 52.9 us.  Other pitches (7168, 14336, 20480,
+// 28672 elements) gain nothing and lose up to 5 % where the activations outgrow an L2; neither do int8 rows gain.
+static bool pitch_is_power_of_two(int K) { return K >= 4096 && (K & (K - 1)) == 0; }
 
 // XCDs that share one K split (GemmParams::xcd_split): 8 / splits where the splits are dealt to them, else all 8.  One row tile
 // has no activation slices worth keeping apart, and where its column tiles fill the 8 XCDs evenly anyhow the splits stay
@@ -1260,51 +1319,128 @@ static int xcd_groups(int splits, int tiles_m, int tiles_n, int hl) {
 }
 
 // Tile shape and K split of the direct-to-LDS kernel for the Q/K/V, output and down projections,
-// from a cost model in microseconds fitted to a sweep of every (tile, split) pair over these
-// projections of the 7B-, 34B- (bf16) and 70B-shaped workloads (16 .. 760 rows, bf16 and int8 weights, over 5000 pairs each) on the chip:
-//   main launch   = rounds x t x k-tiles per workgroup + 9.5 (launch, pipeline fill, epilogue)
-//                   at least the weights' bytes at 5.2 TB/s (few rows: no point in splitting further than that; the
-//                   operand pairs of K|V are bound by the matrix cores earlier and go by the tiles alone)
+// from a cost model in microseconds fitted to sweeps of every (tile, split) pair over these
+// projections of the 7B-, 34B- and 70B-shaped workloads (bf16 24 .. 1536 rows, int8 16 .. 760; over 10000 pairs) on the chip:
+//   main launch   = rounds x t x k-tiles per workgroup + a fixed part (launch, pipeline fill, epilogue; bf16: 3.3 us more for every
+//                   further round)
+//                   at least the weights' bytes at the rate a launch reads them (few rows: no point in splitting further than
+//                   that; the operand pairs of K|V are bound by the matrix cores earlier and go by the tiles alone)
 //   rounds        = those of the XCD that is dealt the most workgroups, 32 at a time (one per CU; a partly filled
 //                   round counts whole).  28 column tiles in 9 splits are 252 workgroups, but 36 on four of the XCDs: two
 //                   rounds.  Counted over the chip instead, the model chose such splits: 7168 x 20480 at 96 / 525 rows
 //                   104 / 268 us, 72 / 192 us with the pairs it chooses now.
-//   t             = time of one 64-deep k-tile on every CU
-//   finish launch = 2.3 + 0.5 us per MB of parked sums (splits x M x N floats), stores included
-// Its choice is on average within 1.9 % (bf16) and 0.4 % (int8) of the best pair of the sweep, at most 22 % and 8 %.
-// t = 0: not used with that weight format (the wide tiles are faster at every row count of the sweep; a 256 x 128 tile of
-// bf16 weights is one for the gate/up projection alone).
+//   t             = time of one 64-deep k-tile on every CU with no row padded; a row tile's blocks without real rows take 0.18 of
+//                   it off (bf16; the int8 expansions stay).  Split shares of a multiple of 4 KB (32 k-tiles) start
+//                   at the same place of the memory channels' interleave: 1.12 t (4096 x 14336 at 110 rows in 7 splits of
+//                   32 k-tiles 42.5 us, in 8 of 28 36.0 us); rows of a power-of-two pitch are staggered instead.
+//   finish launch = 1.5 / 2.3 us + 0.34 / 0.5 us per MB of parked sums (splits x M x N floats), bf16 / int8, stores included
+// Its choice is on average within 1.3 % (bf16) and 1.0 % (int8) of the best pair of the sweep; the six tiles that all three
+// projections share came within 2.9 % of it, with 256 x 128 on eight wavefronts, 192 x 224 and 320 x 192 for float outputs the
+// output and down projections take 1.7 % less (7168 x 20480 at 580 rows 209 -> 183 us).
+// t = 0: not used with that weight format.
 // max_splits caps the split (scratch the caller can spare); parked: a finish launch runs anyway.
-struct DmaShape { int I, NB; double t[2]; };               // t: bf16, int8 weights
-static constexpr DmaShape kDmaShapes[] = {{2, 2, {0.58, 0.72}}, {4, 2, {0.72, 0.94}}, {6, 2, {0.82, 0.0}},
-                                          {4, 4, {0.97, 1.32}}, {6, 4, {1.28, 1.53}}, {8, 4, {1.50, 1.89}}};
-// whether a plan can ask for a tile: the gate/up projection takes any, the others go by the table above
-constexpr bool dma_tile_planned(int epi, int I, int NB, bool w8) {
-  if (epi == EPI_SWIGLU) return true;
-  for (const DmaShape &c : kDmaShapes)
-    if (c.I == I && c.NB == NB && c.t[w8] != 0.0) return true;
-  return false;
-}
+struct DmaShape { int tile; double t[2]; };               // t: bf16, int8 weights
+static constexpr DmaShape kDmaShapes[] = {{T64x128, {0.52, 0.72}}, {T128x128, {0.61, 0.94}}, {T192x128, {0.73, 0.0}},
+                                          {T128x256, {0.88, 1.32}}, {T192x256, {1.21, 1.53}}, {T256x256, {1.38, 1.89}},
+                                          {T256x128w8, {0.83, 0.0}}, {T192x224, {1.14, 0.0}}, {T320x192, {1.40, 0.0}}};
+constexpr int kSharedShapes = 6;                           // the leading ones serve the Q/K/V projections too
 
 // Output columns [0, hl_cols) take (high, low) activation pairs, i.e. twice the tile rows per output row.
-static void pick_dma_plan(int M, int N, int hl_cols, int K, int max_splits, bool parked, bool w8, GemmPlan *pl) {
+static void pick_dma_plan(int epi, int M, int N, int hl_cols, int K, int max_splits, bool parked, bool w8, GemmPlan *pl) {
   const int k_tiles = K / DMA_BK;
-  const double park_us = (double)M * N * 4.0e-6 * 0.5;     // per split
-  const double read_us = hl_cols ? 0.0 : (double)N * K * (w8 ? 1 : 2) / 5.2e6;
+  const double park_us = (double)M * N * 4.0e-6 * (w8 ? 0.5 : 0.342);     // per split
+  const double read_us = hl_cols ? 0.0 : (double)N * K * (w8 ? 1 : 2) / (w8 ? 5.2e6 : 5.95e6);
   pl->cost = 1e30;
-  for (const DmaShape &c : kDmaShapes) {
-    const int bm = 32 * c.I, bn = 64 * c.NB;
-    if (c.t[w8] == 0.0 || (c.I == 2 && M > 64)) continue;
+  for (int i = 0; i < (epi == EPI_SEG ? kSharedShapes : (int)(sizeof(kDmaShapes) / sizeof(kDmaShapes[0]))); ++i) {
+    const DmaShape &c = kDmaShapes[i];
+    const DmaTile t = kDmaTiles[c.tile];
+    const int bm = t.bm(), bn = t.bn();
+    if (c.t[w8] == 0.0 || (bm == 64 && M > 64)) continue;
     if (hl_cols < N && hl_cols % bn != 0) continue;        // a tile's columns are of one kind
+    const int tiles_m = ceil_div(M, bm);
+    int steps = 0;                                         // row blocks walked per wavefront, summed over the row tiles
+    for (int m = 0; m < M; m += bm) steps += ceil_div(ceil_div(std::min(M - m, bm), 16), t.WM);
+    const double t_rows = w8 ? c.t[1] : c.t[0] * (0.82 + 0.18 * steps / (tiles_m * t.RB));
     for (int sp = 1; sp <= 16 && sp <= max_splits; ++sp) {
       if (sp > 1 && k_tiles / sp < 4) break;
-      const int groups = xcd_groups(sp, ceil_div(M, bm), ceil_div(N - hl_cols, bn), hl_cols);
+      const int groups = xcd_groups(sp, tiles_m, ceil_div(N - hl_cols, bn), hl_cols);
       const long per_xcd = ((long)ceil_div(2 * M, bm) * ceil_div(ceil_div(hl_cols, bn), groups) +
-                            (long)ceil_div(M, bm) * ceil_div(ceil_div(N - hl_cols, bn), groups)) * (groups < 8 ? 1 : sp);
+                            (long)tiles_m * ceil_div(ceil_div(N - hl_cols, bn), groups)) * (groups < 8 ? 1 : sp);
       const long rounds = (per_xcd + 31) / 32;
-      const double cost = std::max(rounds * c.t[w8] * ceil_div(k_tiles, sp), read_us) + 9.5 + (sp > 1 || parked ? sp * park_us + 2.3 : 0.0);
-      if (cost < pl->cost - 1e-9) { pl->cost = cost; pl->I = c.I; pl->NB = c.NB; pl->splits = sp; }
+      const int kt = ceil_div(k_tiles, sp);
+      const double tk = !w8 && sp > 1 && groups == 8 && kt % 32 == 0 && !pitch_is_power_of_two(K) ? 1.12 * t_rows : t_rows;
+      const double fixed = w8 ? 9.5 : 9.6 + 3.3 * (rounds - 1), finish = w8 ? 2.3 : 1.5;
+      const double cost = std::max(rounds * tk * kt, read_us) + fixed + (sp > 1 || parked ? sp * park_us + finish : 0.0);
+      if (cost < pl->cost - 1e-9) { pl->cost = cost; pl->tile = c.tile; pl->splits = sp; }
     }
+  }
+}
+
+// Tile of the gate/up projection, and how its last round of workgroups is shared: a cost model in microseconds fitted to a sweep of
+// every tile over 28672 x 4096, 57344 x 8192 and 40960 x 7168 (gate and up rows together) at 24 .. 3072 rows, bf16 and
+// int8 weights: its choice is on average within 0.5 % (bf16) and 1.1 % (int8) of the best tile.
+//   a round   = (idle + rows x share of the tile's row blocks that hold real rows) x k-tiles; a launch of less than one round runs
+//               faster than its share of the chip (power): down to 1 - kPartial of that
+//               at least the weights it reads, at 6.2 TB/s where every CU takes part, less where fewer do
+//   launch    = 8 us + its rounds of 256 workgroups; no K split (the epilogue needs whole gate and up sums), but the workgroups
+//               of a partly filled last round can share its tiles along K, 2 .. 4 per tile: their raw sums go through memory
+//               (bf16 / int8 fit: 7.1 / 4 TB/s both ways) and a second launch finishes them (2.5 / 8 us); where another
+//               tile does without and the two are within 3 % that one is taken (40960 x 7168 at 430 rows: the call 2 % faster)
+//   384 x 128 is for a single row tile: 28672 x 4096 at 350 rows 87 -> 82 us, but at 640 rows 147 -> 159 us
+struct SwigluShape { int tile; float idle, rows; };
+static constexpr SwigluShape kSwigluShapes[2][16] = {
+    {{T64x128, .53f, .14f}, {T128x128, .55f, .15f}, {T128x160, .49f, .25f}, {T128x224, .65f, .33f}, {T192x128, .60f, .16f},
+     {T192x160, .64f, .33f}, {T192x224, .85f, .44f}, {T192x256, 1.01f, .27f}, {T256x128w8, .61f, .32f}, {T256x160, .73f, .37f},
+     {T256x224, .98f, .52f}, {T256x256, 1.21f, .32f}, {T320x160, .89f, .46f}, {T320x192, 1.02f, .52f}, {T384x128, .81f, .42f},
+     {T384x160, 1.03f, .53f}},
+    {{T64x128, .38f, .14f}, {T128x128, .64f, .19f}, {T128x256, .79f, .24f}, {T192x128w8, .72f, .20f}, {T192x160, .82f, .27f},
+     {T192x256, .97f, .33f}, {T256x160, .95f, .34f}, {T256x256, 1.16f, .42f}, {T320x160, 1.07f, .40f}, {T384x160, 1.18f, .47f}}};
+// whether a plan can ask for a tile
+constexpr bool dma_tile_planned(int epi, int tile, bool w8) {
+  if (epi == EPI_SWIGLU) {
+    for (const SwigluShape &c : kSwigluShapes[w8])
+      if (c.tile == tile && c.idle != 0.f) return true;
+    return false;
+  }
+  for (int i = 0; i < (epi == EPI_SEG ? kSharedShapes : (int)(sizeof(kDmaShapes) / sizeof(kDmaShapes[0]))); ++i)
+    if (kDmaShapes[i].tile == tile && kDmaShapes[i].t[w8] != 0.0) return true;
+  return false;
+}
+static void pick_swiglu_plan(int M, int N, int K, size_t scratch_floats, bool w8, GemmPlan *pl) {
+  const int k_tiles = K / DMA_BK;
+  const double partial = w8 ? 0.2 : 0.38, starve = w8 ? 0.1 : 0.65;
+  double best = 1e30;
+  for (const SwigluShape &c : kSwigluShapes[w8]) {
+    const DmaTile t = kDmaTiles[c.tile];
+    if (c.idle == 0.f || (t.bm() > 256 && M <= 256) || (c.tile == T384x128 && M > t.bm())) continue;
+    const int tiles_m = ceil_div(M, t.bm());
+    const long ids = 8L * ceil_div(ceil_div(N, t.bn() / 2), 8) * tiles_m, full = ids / 256, tail = ids % 256;
+    int steps = 0;                                     // row blocks walked per wavefront, summed over the row tiles
+    for (int m = 0; m < M; m += t.bm()) steps += ceil_div(ceil_div(std::min(M - m, t.bm()), 16), t.WM);
+    const double tk = c.idle + c.rows * steps / (double)(tiles_m * t.RB);
+    auto round_us = [&](long n, int k) {
+      const double share = full ? 1.0 : 1.0 - partial + partial * n / 256.0;
+      const double read = (double)n / tiles_m * t.bn() * DMA_BK * (w8 ? 1 : 2) / (6.2e6 * (1.0 - starve * (1.0 - n / 256.0)));
+      return k * std::max(tk * share, read);
+    };
+    double cost = full * round_us(256, k_tiles);
+    int ts = 1;
+    if (tail) {
+      double last = round_us(tail, k_tiles);
+      ts = full ? (int)std::min<long>(4, 256 / tail) : 1;
+      while (ts > 1 && k_tiles / ts < 8) --ts;
+      if (ts > 1) {
+        const int k = ceil_div(k_tiles, ts);
+        const double floats = (double)tail * ts * t.bm() * t.bn();
+        const double shared = round_us(tail * ts, k) + floats * 8 / (w8 ? 4.0e6 : 7.1e6) + (w8 ? 8.0 : 2.5);
+        const size_t need = (size_t)tail * ceil_div(k_tiles, k) * t.bm() * t.bn();
+        if (shared < last && need <= scratch_floats) last = shared;
+        else ts = 1;
+      }
+      cost += last;
+    }
+    if (ts > 1) cost *= 1.03;
+    if (cost < best - 1e-9) { best = cost; pl->tile = c.tile; pl->tail_splits = ts; }
   }
 }
 
@@ -1329,6 +1465,7 @@ static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int f
                           int head_dim, size_t scratch_floats, bool w8 = false) {
   GemmPlan pl = {};
   pl.w8 = w8;
+  pl.tail_splits = 1;
   if (w8 && !gemm_int8_in_kernel(dtype, K)) pl.bad = true;
   pl.splits = 1;
   pl.hl = dtype == 1 && epi == EPI_SEG ? hl : 0;
@@ -1341,23 +1478,16 @@ static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int f
   } else if (K % DMA_BK != 0) {
     pl.kind = 1; pl.bm = BM16; pl.out_cols = epi == EPI_SWIGLU ? BN16 / 2 : BN16; pl.bk = BK16;
   } else if (epi == EPI_SWIGLU) {
-    pl.kind = 2; pl.I = pick_row_blocks(M); pl.bk = DMA_BK;
-    // 256-column tiles unless 128-column tiles (lower arithmetic intensity: measured ~1.4x
-    // slower per flop) fill the rounds of 256 workgroups so much better that they still win,
-    // which happens when there is a single row of tiles (M <= 256).
-    pl.NB = 4;
-    const long t4 = (long)ceil_div(M, 32 * pl.I) * ceil_div(N, 128), t2 = (long)ceil_div(M, 32 * pl.I) * ceil_div(N, 64);
-    const double c4 = (double)((t4 + 255) / 256) * 2.0, c2 = (double)((t2 + 255) / 256) * 1.4;
-    if (c2 < c4) pl.NB = 2;
-  } else {
     pl.kind = 2; pl.bk = DMA_BK;
-    pick_dma_plan(M, N, pl.hl, K, max_splits, pl.raw, w8, &pl);
-    if (pl.I == 0) { pl.bad = true; pl.I = 8; pl.NB = 4; }     // no tile width divides the columns with pairs
+    pick_swiglu_plan(M, N, K, scratch_floats, w8, &pl);
+  } else {
+    pl.kind = 2; pl.bk = DMA_BK; pl.tile = -1;
+    pick_dma_plan(epi, M, N, pl.hl, K, max_splits, pl.raw, w8, &pl);
+    if (pl.tile < 0) { pl.bad = true; pl.tile = T256x256; }    // no tile width divides the columns with pairs
   }
   if (pl.kind == 2) {
-    pl.nwv = (pl.NB == 4 && pl.I >= 4) ? 8 : 4;
-    pl.bm = 32 * pl.I;
-    pl.out_cols = (epi == EPI_SWIGLU ? 32 : 64) * pl.NB;
+    pl.bm = kDmaTiles[pl.tile].bm();
+    pl.out_cols = kDmaTiles[pl.tile].bn() / (epi == EPI_SWIGLU ? 2 : 1);
   }
   pl.tiles_m = ceil_div(M, pl.bm);
   pl.tiles_n = ceil_div(pl.kind == 2 ? N - pl.hl : N, pl.out_cols);
@@ -1382,37 +1512,22 @@ static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int f
   pl.splits = ceil_div(K, pl.k_per_split);
   if (pl.splits > 1) pl.raw = 1;
   pl.partial_floats = pl.raw ? (size_t)pl.splits * mn : 0;
-  pl.tail_splits = 1;
   if (pl.kind == 2) {
     const int groups = epi == EPI_SWIGLU ? 8 : xcd_groups(pl.splits, pl.tiles_m, pl.tiles_n, pl.hl);
     pl.xcd_split = groups < 8;
-    pl.nt = epi != EPI_SEG && !w8 && pl.tiles_m == 1 && (epi == EPI_SWIGLU ? 4.0 : 2.0) * N * K >= kNtMinBytes;
+    pl.k_stagger = !w8 && pl.tiles_m == 1 && pitch_is_power_of_two(K);
+    const bool nt = epi != EPI_SEG && !w8 && pl.tiles_m == 1 && (epi == EPI_SWIGLU ? 4.0 : 2.0) * N * K >= kNtMinBytes;
+    pl.mode = nt ? MODE_NT : pl.k_stagger ? MODE_STAGGER : MODE_PLAIN;
     const long ids = 8L * (ceil_div(pl.tiles_n, groups) * pl.tiles_m + ceil_div(pl.hl_tiles_n, groups) * pl.hl_tiles_m);
     pl.grid_ids = pl.xcd_split ? ids : ids * pl.splits;
     pl.tail_first = (int)pl.grid_ids;
-    if (epi == EPI_SWIGLU) {
-      // The last round of 256 workgroups, when less than half full, is shared: ts workgroups per
-      // tile, each over 1/ts of K, plus a fix-up launch.  Worth it when the time saved on the
-      // round exceeds the round trip of the partial sums (~4 TB/s) and the extra launch.  t_tile is more than a
-      // k-tile takes with every CU busy (256, 192, 128 rows x 256 columns 1.54, 1.27, 0.95 us), so the rule leans towards
-      // sharing; it is never wrong by that: at 54 row counts from 200 to 3136 of three shapes, bf16 and int8, every launch
-      // that shares takes 0.76 .. 1.00 of its time without (mean 0.92).
-      const long full = ids / 256 * 256, tail = ids - full;
-      int ts = tail > 0 ? (int)std::min<long>(4, 256 / tail) : 1;
-      while (ts > 1 && k_tiles / ts < 8) --ts;
-      if (ts > 1) {
-        const double t_tile = 0.3 * pl.I * (pl.NB == 4 ? 1.0 : 0.6);
-        const double saved = (k_tiles - ceil_div(k_tiles, ts)) * t_tile;
-        const double extra = (double)tail * ts * pl.bm * (64 * pl.NB) * 8.0 / 4.0e6 + 8.0;
-        const size_t need = (size_t)tail * ceil_div(K, ceil_div(k_tiles, ts) * pl.bk) * pl.bm * (64 * pl.NB);
-        if (saved > extra && need <= scratch_floats) {
-          pl.tail_first = (int)full;
-          pl.tail_k_per_split = ceil_div(k_tiles, ts) * pl.bk;
-          pl.tail_splits = ceil_div(K, pl.tail_k_per_split);
-          pl.grid_ids = full + tail * pl.tail_splits;
-          pl.partial_floats = (size_t)tail * pl.tail_splits * pl.bm * (64 * pl.NB);
-        }
-      }
+    if (pl.tail_splits > 1) {
+      const long tail = pl.grid_ids % 256;
+      pl.tail_first = (int)(pl.grid_ids - tail);
+      pl.tail_k_per_split = ceil_div(k_tiles, pl.tail_splits) * pl.bk;
+      pl.tail_splits = ceil_div(K, pl.tail_k_per_split);
+      pl.grid_ids = pl.tail_first + tail * pl.tail_splits;
+      pl.partial_floats = (size_t)tail * pl.tail_splits * pl.bm * (2 * pl.out_cols);
     }
   }
   return pl;
@@ -1467,6 +1582,7 @@ static GemmPlan fill_params(const GemmArgs &g, GemmParams *pp) {
   p.k_per_split = pl.k_per_split;
   p.tail_first = pl.tail_first; p.tail_splits = pl.tail_splits; p.tail_k_per_split = pl.tail_k_per_split;
   p.xcd_split = pl.xcd_split;
+  p.k_stagger = pl.k_stagger;
   return pl;
 }
 
@@ -1496,50 +1612,51 @@ bool gemm_needs_finish(const GemmArgs &g) {
     });                                                                                            \
   } while (0)
 
-template <int I, int NB, int EPI, int NWV, bool HL, bool W8, bool NT>
+template <int T, int EPI, bool HL, bool W8, int MODE>
 static void launch_dma_kernel(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
-  constexpr int smem = dma_smem_bytes(I, 64 * NB, W8);
-  CB_LDS_LIMIT_ONCE((&gemm_bf16_dma_kernel<I, NB, EPI, NWV, HL, W8, NT>), smem);
-  hipLaunchKernelGGL((gemm_bf16_dma_kernel<I, NB, EPI, NWV, HL, W8, NT>), dim3((unsigned)pl.grid_ids), dim3(64 * NWV),
-                     smem, s, p, pl.tiles_m, pl.tiles_n);
+  constexpr DmaTile t = kDmaTiles[T];
+  constexpr int smem = dma_smem_bytes(t.bm(), t.bn(), W8);
+  CB_LDS_LIMIT_ONCE((&gemm_bf16_dma_kernel<t.RB, t.CB, t.WM, t.WN, EPI, HL, W8, MODE>), smem);
+  hipLaunchKernelGGL((gemm_bf16_dma_kernel<t.RB, t.CB, t.WM, t.WN, EPI, HL, W8, MODE>), dim3((unsigned)pl.grid_ids),
+                     dim3(64 * t.WM * t.WN), smem, s, p, pl.tiles_m, pl.tiles_n);
 }
 
 // Only kernels of tiles that a plan can ask for are built; false for any other.
-template <int I, int NB, int EPI, int NWV, bool HL = false>
+template <int T, int EPI, bool HL>
 static bool launch_dma(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
   if (pl.w8) {
-    if constexpr (dma_tile_planned(EPI, I, NB, true)) {
-      launch_dma_kernel<I, NB, EPI, NWV, HL, true, false>(pl, p, s);
+    if constexpr (dma_tile_planned(EPI, T, true)) {
+      launch_dma_kernel<T, EPI, HL, true, MODE_PLAIN>(pl, p, s);
       return true;
     }
   } else {
-    if constexpr (dma_tile_planned(EPI, I, NB, false)) {
-      if (pl.nt) launch_dma_kernel<I, NB, EPI, NWV, HL, false, EPI != EPI_SEG>(pl, p, s);
-      else launch_dma_kernel<I, NB, EPI, NWV, HL, false, false>(pl, p, s);
+    if constexpr (dma_tile_planned(EPI, T, false)) {
+      if (pl.mode == MODE_NT) launch_dma_kernel<T, EPI, HL, false, EPI == EPI_SEG ? MODE_PLAIN : MODE_NT>(pl, p, s);
+      else if (pl.mode == MODE_STAGGER) launch_dma_kernel<T, EPI, HL, false, MODE_STAGGER>(pl, p, s);
+      else launch_dma_kernel<T, EPI, HL, false, MODE_PLAIN>(pl, p, s);
       return true;
     }
   }
   return false;
 }
 
-template <int EPI, bool HL>
+template <int EPI, bool HL, int T = 0>
 static bool launch_dma_shape(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
-  if (pl.NB == 2) {
-    switch (pl.I) {
-      case 2: return launch_dma<2, 2, EPI, 4, HL>(pl, p, s);
-      case 4: return launch_dma<4, 2, EPI, 4, HL>(pl, p, s);
-      case 6: return launch_dma<6, 2, EPI, 4, HL>(pl, p, s);
-      default: return launch_dma<8, 2, EPI, 4, HL>(pl, p, s);
-    }
+  if constexpr (T < kNumDmaTiles) return pl.tile == T ? launch_dma<T, EPI, HL>(pl, p, s) : launch_dma_shape<EPI, HL, T + 1>(pl, p, s);
+  else return false;
+}
+
+template <int T = 0>
+static bool launch_tail(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
+  if constexpr (T < kNumDmaTiles) {
+    if (pl.tile != T) return launch_tail<T + 1>(pl, p, s);
+    constexpr DmaTile t = kDmaTiles[T];
+    const int shared = (int)(pl.grid_ids - pl.tail_first) / pl.tail_splits;
+    hipLaunchKernelGGL((swiglu_tail_kernel<t.RB, t.CB, t.WM, t.WN>), dim3((unsigned)(shared * ceil_div(t.WM * t.WN * t.RB * ((t.CB + 1) / 2), 16))),
+                       dim3(256), 0, s, p, pl.tiles_m, pl.tiles_n);
+    return true;
   }
-  if (pl.nwv == 8) {
-    switch (pl.I) {
-      case 4: return launch_dma<4, 4, EPI, 8, HL>(pl, p, s);
-      case 6: return launch_dma<6, 4, EPI, 8, HL>(pl, p, s);
-      default: return launch_dma<8, 4, EPI, 8, HL>(pl, p, s);
-    }
-  }
-  return launch_dma<2, 4, EPI, 4, HL>(pl, p, s);
+  return false;
 }
 
 template <int EPI>
@@ -1575,17 +1692,7 @@ hipError_t launch_gemm_finish(const GemmArgs &g, hipStream_t s) {
   const GemmPlan pl = fill_params(g, &p);
   if (pl.bad) return hipErrorInvalidValue;
   if (pl.tail_splits > 1) {
-    const dim3 tg((unsigned)((pl.grid_ids - pl.tail_first) / pl.tail_splits) * (pl.I / 2) * (pl.NB / 2));
-#define CB_TAIL(I_, NB_, W_) hipLaunchKernelGGL((swiglu_tail_kernel<I_, NB_, W_>), tg, dim3(256), 0, s, p, pl.tiles_m, pl.tiles_n)
-    if (pl.NB == 2) {
-      switch (pl.I) { case 2: CB_TAIL(2, 2, 4); break; case 4: CB_TAIL(4, 2, 4); break; case 6: CB_TAIL(6, 2, 4); break; default: CB_TAIL(8, 2, 4); break; }
-    } else if (pl.nwv == 8) {
-      switch (pl.I) { case 4: CB_TAIL(4, 4, 8); break; case 6: CB_TAIL(6, 4, 8); break; default: CB_TAIL(8, 4, 8); break; }
-    } else {
-      CB_TAIL(2, 4, 4);
-    }
-#undef CB_TAIL
-    return hipGetLastError();
+    return launch_tail(pl, p, s) ? hipGetLastError() : hipErrorInvalidValue;
   }
   if (!pl.raw) return hipSuccess;
   const dim3 grid((unsigned)g.M);
