@@ -178,11 +178,6 @@ LayerWs carve_layer(const cb_ctx *c, char *base, int R) {
   return w;
 }
 
-__global__ void iota_kernel(int32_t *p, int n, int base) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = base + i;
-}
-
 #define CB_HIP(expr)                     \
   do {                                   \
     hipError_t e_ = (expr);              \
@@ -389,9 +384,9 @@ int fuse_layer_impl(cb_ctx *c, const cb_layer_weights *w, const float *h_in, con
     if (rows == 0) return CB_OK;
     sel_rows = ws.sel_rows;
   } else {
-    {
+    if (pos_out != row_pos || cache_row_out) {
       ProfScope ps(c, s, CB_PROF_OTHER, 0, (double)n * 8);
-      CB_HIP(hipMemcpyAsync(pos_out, row_pos, (size_t)n * 4, hipMemcpyDeviceToDevice, s));
+      if (pos_out != row_pos) CB_HIP(hipMemcpyAsync(pos_out, row_pos, (size_t)n * 4, hipMemcpyDeviceToDevice, s));
       if (cache_row_out)
         CB_HIP(hipMemcpyAsync(cache_row_out, crow, (size_t)n * 4, hipMemcpyDeviceToDevice, s));
     }
@@ -741,10 +736,9 @@ int prefill_impl(cb_ctx *c, const cb_layer_weights *layers, const void *x, const
   ProfScope *phase = new (std::nothrow) ProfScope(c, s, CB_PROF_PHASE_FIRST, 0, 0);
   struct PhaseGuard { ProfScope *&p; ~PhaseGuard() { delete p; } } phase_guard{phase};
   {
-    ProfScope ps(c, s, CB_PROF_OTHER, 0, (double)T * d * (4 + esize(c)));
-    CB_HIP(launch_to_f32(c->m.dtype, x, h_cur, (size_t)T * d, s));
-    hipLaunchKernelGGL(iota_kernel, dim3((T + 255) / 256), dim3(256), 0, s, p_cur, T, 0);
-    CB_HIP(hipGetLastError());
+    const int lo_off = xn_lo_off(c);
+    ProfScope ps(c, s, CB_PROF_NORM, 0, (double)T * d * (4 + esize(c) * (lo_off ? 3 : 2)));
+    CB_HIP(launch_input_rows(c->m.dtype, x, h_cur, p_cur, layers[0].attn_norm, ws.xn, xn_pitch(c), lo_off, T, d, c->m.rms_eps, s));
   }
   int st = CB_OK;
   if (!k_host && L > 1) {      // layer 0 overwrites all of its rows: nothing of it to re-align
@@ -768,15 +762,17 @@ int prefill_impl(cb_ctx *c, const cb_layer_weights *layers, const void *x, const
     const int32_t *forced = forced_sel ? forced_sel[l] : nullptr;
     float *dev_out = dev_dump ? dev_dump[l] : nullptr;
     const Seg seg = {n, n_suffix, k, T};
+    // without a check every row is kept and the positions stay as they are
+    int32_t *p_out = forced || k < n - n_suffix ? p_nxt : p_cur;
     // the launch that finishes a layer's output also normalises it for the next layer
     st = fuse_layer_impl(c, &layers[l], h_cur, p_cur, nullptr, &seg, 1, 0, k_cache_layers[l], v_cache_layers[l],
-                         forced, h_nxt, p_nxt, nullptr, dev_out, ws, s, l > 0,
+                         forced, h_nxt, p_out, nullptr, dev_out, ws, s, true,
                          l + 1 < L ? layers[l + 1].attn_norm : nullptr, n_suffix == 0 && l + 1 == L);
     if (st != CB_OK) return st;
     if (sel_dump && sel_dump[l] && k > 0)
-      CB_HIP(hipMemcpyAsync(sel_dump[l], p_nxt, (size_t)k * 4, hipMemcpyDeviceToDevice, s));
+      CB_HIP(hipMemcpyAsync(sel_dump[l], p_out, (size_t)k * 4, hipMemcpyDeviceToDevice, s));
     std::swap(h_cur, h_nxt);
-    std::swap(p_cur, p_nxt);
+    if (p_out != p_cur) std::swap(p_cur, p_nxt);
     n = k + n_suffix;
     if (l == 0) {
       delete phase;
@@ -920,15 +916,15 @@ int cb_fuse_prefill_batched(cb_ctx *c, const cb_layer_weights *layers, int32_t n
   if (B > 1) CB_HIP(hipMemcpyAsync(seg_tab, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, s));
 
   {
-    ProfScope ps(c, s, CB_PROF_OTHER, 0, (double)N * d * (4 + es));
-    CB_HIP(launch_to_f32(c->m.dtype, x, h_cur, (size_t)N * d, s));
+    const int lo_off = xn_lo_off(c);
+    ProfScope ps(c, s, CB_PROF_NORM, 0, (double)N * d * (4 + es * (lo_off ? 3 : 2)));
+    CB_HIP(launch_input_rows(c->m.dtype, x, h_cur, nullptr, layers[0].attn_norm, ws.xn, xn_pitch(c), lo_off, N, d, c->m.rms_eps, s));
     int o = 0;
     for (int b = 0; b < B; ++b) {
-      hipLaunchKernelGGL(iota_kernel, dim3((T[b] + 255) / 256), dim3(256), 0, s, p_cur + o, T[b], 0);
-      hipLaunchKernelGGL(iota_kernel, dim3((T[b] + 255) / 256), dim3(256), 0, s, r_cur + o, T[b], b * cache_stride);
+      CB_HIP(launch_iota(p_cur + o, T[b], 0, s));
+      CB_HIP(launch_iota(r_cur + o, T[b], b * cache_stride, s));
       o += T[b];
     }
-    CB_HIP(hipGetLastError());
   }
   std::vector<void *> kptr(L);
   for (int b = 0; b < B && L > 1; ++b) {     // layer 0 overwrites all of its rows: nothing of it to re-align
@@ -946,7 +942,7 @@ int cb_fuse_prefill_batched(cb_ctx *c, const cb_layer_weights *layers, int32_t n
     for (int b = 0; b < B; ++b) segs[b].k = keep_counts[(size_t)b * L + l];
     int st = fuse_layer_impl(c, &layers[l], h_cur, p_cur, r_cur, segs.data(), B, (size_t)cache_stride,
                              k_cache_layers[l], v_cache_layers[l], nullptr, h_nxt, p_nxt, r_nxt,
-                             dev_dump ? dev_dump[l] : nullptr, ws, s, l > 0,
+                             dev_dump ? dev_dump[l] : nullptr, ws, s, true,
                              l + 1 < L ? layers[l + 1].attn_norm : nullptr, total_suffix == 0 && l + 1 == L,
                              B > 1 ? seg_tab + (size_t)l * (B + 1) * kSegInts : nullptr);
     if (st != CB_OK) return st;

@@ -34,6 +34,22 @@ template <> struct Vec16<bf16> {
   __device__ __forceinline__ void set(int i, float v) { raw[i] = (bf16)v; }
 };
 
+// four adjacent elements
+template <typename T> __device__ __forceinline__ float4 load4(const T *s);
+template <> __device__ __forceinline__ float4 load4<float>(const float *s) { return *reinterpret_cast<const float4 *>(s); }
+template <> __device__ __forceinline__ float4 load4<bf16>(const bf16 *s) {
+  const bf16x4 v = *reinterpret_cast<const bf16x4 *>(s);
+  return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+}
+template <typename T> __device__ __forceinline__ void store4(T *d, float a, float b, float c, float e);
+template <> __device__ __forceinline__ void store4<float>(float *d, float a, float b, float c, float e) {
+  *reinterpret_cast<float4 *>(d) = make_float4(a, b, c, e);
+}
+template <> __device__ __forceinline__ void store4<bf16>(bf16 *d, float a, float b, float c, float e) {
+  bf16x4 v = {(bf16)a, (bf16)b, (bf16)c, (bf16)e};
+  *reinterpret_cast<bf16x4 *>(d) = v;
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

@@ -93,22 +93,8 @@ __device__ __forceinline__ const T *weight_row(const GemmParams &p, int gc, int 
   return reinterpret_cast<const T *>(p.w[s]) + (size_t)(gc - p.nb[s]) * p.K * es;
 }
 
-template <typename T> __device__ __forceinline__ float4 load4(const T *s);
-template <> __device__ __forceinline__ float4 load4<float>(const float *s) { return *reinterpret_cast<const float4 *>(s); }
-template <> __device__ __forceinline__ float4 load4<bf16>(const bf16 *s) {
-  const bf16x4 v = *reinterpret_cast<const bf16x4 *>(s);
-  return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
-}
 // the value a float becomes when stored in the storage type
 template <typename T> __device__ __forceinline__ float as_stored(float v) { return to_f32(from_f32<T>(v)); }
-template <typename T> __device__ __forceinline__ void store4(T *d, float a, float b, float c, float e);
-template <> __device__ __forceinline__ void store4<float>(float *d, float a, float b, float c, float e) {
-  *reinterpret_cast<float4 *>(d) = make_float4(a, b, c, e);
-}
-template <> __device__ __forceinline__ void store4<bf16>(bf16 *d, float a, float b, float c, float e) {
-  bf16x4 v = {(bf16)a, (bf16)b, (bf16)c, (bf16)e};
-  *reinterpret_cast<bf16x4 *>(d) = v;
-}
 
 // Column offset from an output column to the channel it forms a rotary pair with when heads are in
 // the (i, i + head_dim/2) order.  Segments are whole heads, so gc % head_dim is the channel.
