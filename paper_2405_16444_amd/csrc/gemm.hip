@@ -1060,6 +1060,54 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
   lds_epilogue<float, EPI, BN>(sC, CP, BM, m0, n0, blockIdx.z, p);
 }
 
+// The same for launches with few 32 x 32 tiles (f32_tile): 16 x 16 tiles (v_mfma_f32_16x16x4_f32), the four wavefronts
+// share K in turn, 16 deep, and read their operands straight from the cache into registers, all of up to 12 steps at once -- no
+// stages, no barrier before the shares are added.  A lane's 16 bytes are four k of one row; MFMA e takes element e of both operands, so
+// a wavefront's k-step is walked in an order of its own.  The weight is the first operand: lane l holds row (l % 16), columns
+// 4 (l / 16) .. + 3.
+constexpr int F32_STEPS = 12;
+template <int EPI>
+__global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmParams p) {
+  constexpr int CP = 20;
+  __shared__ __attribute__((aligned(16))) float sC[4 * 16 * CP];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, ln = lane & 15, h = lane >> 4;
+  const int m0 = blockIdx.y * 16, n0 = blockIdx.x * (EPI == EPI_SWIGLU ? 8 : 16);
+  const int kb = blockIdx.z * p.k_per_split, ke = min(p.K, kb + p.k_per_split);
+  int ar = min(m0 + ln, p.M - 1);
+  if (p.a_rows) ar = p.a_rows[ar];
+  const float *a = reinterpret_cast<const float *>(p.a) + (size_t)ar * p.lda;
+  const float *w = weight_row<float, EPI>(p, n0 + ln, 8, n0, ln);
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int k0 = kb + wave * 16 + 4 * h; k0 - 4 * h < ke; k0 += 64 * F32_STEPS) {      // uniform over the wavefront
+    float4 av[F32_STEPS], wv[F32_STEPS];
+#pragma unroll
+    for (int i = 0; i < F32_STEPS; ++i) {
+      const bool ok = k0 + 64 * i < ke;
+      av[i] = ok ? *reinterpret_cast<const float4 *>(a + k0 + 64 * i) : make_float4(0, 0, 0, 0);
+      wv[i] = ok ? *reinterpret_cast<const float4 *>(w + k0 + 64 * i) : make_float4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < F32_STEPS; ++i) {
+      if (k0 - 4 * h + 64 * i >= ke) break;                                           // uniform over the wavefront
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[i].x, av[i].x, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[i].y, av[i].y, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[i].z, av[i].z, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[i].w, av[i].w, acc, 0, 0, 0);
+    }
+  }
+  *reinterpret_cast<f32x4 *>(sC + (wave * 16 + ln) * CP + 4 * h) = acc;
+  __syncthreads();
+  if (tid < 64) {                                                  // the K shares, added in ascending order
+    f32x4 *c0 = reinterpret_cast<f32x4 *>(sC + ln * CP + 4 * h);
+    f32x4 v = *c0;
+#pragma unroll
+    for (int z = 1; z < 4; ++z) v += c0[z * 16 * CP / 4];
+    *c0 = v;
+  }
+  __syncthreads();
+  lds_epilogue<float, EPI, 16>(sC, CP, 16, m0, n0, blockIdx.z, p);
+}
+
 // ---------------------------------------------------------------------------
 // Finish launches: one workgroup per output row adds the parked partial sums in ascending split
 // order (fixed order, no atomics: bitwise reproducible) and completes the row.
@@ -1430,11 +1478,13 @@ static void pick_swiglu_plan(int M, int N, int K, size_t scratch_floats, bool w8
   }
 }
 
-// Tile of the float kernel: 64 x 64 when those occupy the chip twice over (a quarter of the loads per flop), else
-// 32 x 32 with the wavefronts sharing K (544 rows of the 256-wide model occupy 36 CUs with 64 x 64 tiles, 136 with these).
+// Tile of the float kernels: 64 x 64 when those occupy the chip twice over (a quarter of the loads per flop), else
+// 32 x 32 with the wavefronts sharing K (544 rows of the 256-wide model occupy 36 CUs with 64 x 64 tiles, 136 with these),
+// 16 x 16 where those leave most CUs idle too: 186 rows x 256 columns, 48 tiles of 32 x 32 against 192, 7.8 -> 4.6 us; with 136 tiles of
+// 32 x 32 both take 7.5 us, with 258 / 272 the small ones, which read four times as much per flop, 8.1 / 9.8 against 6.4 / 7.7 us.
 static int f32_tile(int epi, int M, int N) {
-  const long t64 = (long)ceil_div(M, 64) * ceil_div(N, epi == EPI_SWIGLU ? 32 : 64);
-  return t64 >= 512 ? 64 : 32;
+  auto tiles = [&](int t) { return (long)ceil_div(M, t) * ceil_div(N, epi == EPI_SWIGLU ? t / 2 : t); };
+  return tiles(64) >= 512 ? 64 : tiles(32) >= 96 ? 32 : 16;
 }
 // A float tile narrower than a head cannot pair channel i with i + head_dim/2 itself: it parks its sums and the
 // finish launch rotates them.
@@ -1649,7 +1699,8 @@ template <int EPI>
 static bool launch_typed(const GemmPlan &pl, const GemmParams &p, hipStream_t s) {
   const dim3 grid(pl.tiles_n, pl.tiles_m, pl.splits);
   if (pl.kind == 0) {
-    if (pl.bm == 64) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, 2, 1>), grid, dim3(256), 0, s, p);
+    if (pl.bm == 16) hipLaunchKernelGGL(gemm_f32_small_kernel<EPI>, grid, dim3(256), 0, s, p);
+    else if (pl.bm == 64) hipLaunchKernelGGL((gemm_f32_kernel<EPI, 2, 2, 1>), grid, dim3(256), 0, s, p);
     else hipLaunchKernelGGL((gemm_f32_kernel<EPI, 1, 1, 4>), grid, dim3(256), 0, s, p);
     return true;
   }

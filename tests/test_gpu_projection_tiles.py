@@ -1,11 +1,12 @@
 """Tiles of the projections that only certain sizes choose, against the oracle: the gate/up projection on every tile height and
 width (odd numbers of column blocks, loads that do not divide evenly over the wavefronts, tiles past the last row and column),
 the output projections on 192 x 224 and 320 x 192 tiles, and rows of a power-of-two pitch, whose column tiles start at
-different k-tiles and wrap around.  Tolerance: that of every bf16 layer test."""
+different k-tiles and wrap around; float projections on 16 x 16 tiles.  Tolerance: that of every layer test of the type."""
 import pytest
 
 from workloads.configs import ModelShape
 
+from test_gpu_f32_kernels import test_float_layer as float_layer
 from test_gpu_projection_depth import check_layer
 
 pytestmark = pytest.mark.gpu
@@ -46,3 +47,10 @@ def test_output_tiles(P, n_rows):
 @pytest.mark.parametrize("d,hq,hkv,d_ff", [(4096, 2, 1, 264), (136, 64, 1, 4096)])
 def test_staggered_k_ranges(P, n_rows, d, hq, hkv, d_ff):
     check_layer(P, ModelShape(1, d, hq, hkv, 64, d_ff, 1e-5, 1e4, "bf16"), "native", n_rows, 0.9, seed=37 * n_rows + d, std=4096 ** -0.5)
+
+
+# float 16 x 16 tiles: K shorter than a wavefront's share of a step, at the end of a batch of steps (768) and past it
+@pytest.mark.parametrize("rope", ["adjacent", "half"])
+@pytest.mark.parametrize("n_rows,d_ff", [(1, 8), (16, 40), (17, 760), (32, 768), (33, 776), (49, 1544)])
+def test_small_float_tiles(P, n_rows, d_ff, rope):
+    float_layer(P, (136, 3, 1, 64, d_ff, rope, n_rows, 0.7 if n_rows > 20 else 1.0))
