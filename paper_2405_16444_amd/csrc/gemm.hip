@@ -1312,6 +1312,12 @@ constexpr int kNumDmaTiles = sizeof(kDmaTiles) / sizeof(kDmaTiles[0]);
 enum { T64x128, T128x128, T192x128, T128x256, T192x256, T256x256, T128x160, T128x224, T192x128w8, T192x160, T192x224,
        T256x128w8, T256x160, T256x224, T320x160, T320x192, T384x128, T384x160 };
 
+// row blocks that a wavefront walks, summed over the row tiles: all of them but in the last tile
+static long row_block_steps(const DmaTile &t, int M) {
+  const int last = ceil_div(M, t.bm()) - 1;
+  return (long)last * t.RB + ceil_div(ceil_div(M - last * t.bm(), 16), t.WM);
+}
+
 struct GemmPlan {
   int kind;        // 0 float, 1 register-staged bf16, 2 direct-to-LDS bf16
   int tile;        // kind 2: index into kDmaTiles
@@ -1392,9 +1398,8 @@ static void pick_dma_plan(int epi, int M, int N, int hl_cols, int K, int max_spl
     if (c.t[w8] == 0.0 || (bm == 64 && M > 64)) continue;
     if (hl_cols < N && hl_cols % bn != 0) continue;        // a tile's columns are of one kind
     const int tiles_m = ceil_div(M, bm);
-    int steps = 0;                                         // row blocks walked per wavefront, summed over the row tiles
-    for (int m = 0; m < M; m += bm) steps += ceil_div(ceil_div(std::min(M - m, bm), 16), t.WM);
-    const double t_rows = w8 ? c.t[1] : c.t[0] * (0.82 + 0.18 * steps / (tiles_m * t.RB));
+    const long steps = row_block_steps(t, M);
+    const double t_rows = w8 ? c.t[1] : c.t[0] * (0.82 + 0.18 * steps / ((double)tiles_m * t.RB));
     for (int sp = 1; sp <= 16 && sp <= max_splits; ++sp) {
       if (sp > 1 && k_tiles / sp < 4) break;
       const int groups = xcd_groups(sp, tiles_m, ceil_div(N - hl_cols, bn), hl_cols);
@@ -1449,9 +1454,7 @@ static void pick_swiglu_plan(int M, int N, int K, size_t scratch_floats, bool w8
     if (c.idle == 0.f || (t.bm() > 256 && M <= 256) || (c.tile == T384x128 && M > t.bm())) continue;
     const int tiles_m = ceil_div(M, t.bm());
     const long ids = 8L * ceil_div(ceil_div(N, t.bn() / 2), 8) * tiles_m, full = ids / 256, tail = ids % 256;
-    int steps = 0;                                     // row blocks walked per wavefront, summed over the row tiles
-    for (int m = 0; m < M; m += t.bm()) steps += ceil_div(ceil_div(std::min(M - m, t.bm()), 16), t.WM);
-    const double tk = c.idle + c.rows * steps / (double)(tiles_m * t.RB);
+    const double tk = c.idle + c.rows * row_block_steps(t, M) / ((double)tiles_m * t.RB);
     auto round_us = [&](long n, int k) {
       const double share = full ? 1.0 : 1.0 - partial + partial * n / 256.0;
       const double read = (double)n / tiles_m * t.bn() * DMA_BK * (w8 ? 1 : 2) / (6.2e6 * (1.0 - starve * (1.0 - n / 256.0)));
@@ -1581,6 +1584,18 @@ size_t gemm_partial_floats(int dtype, int epi, int M, int N, int K, int hl, int 
   if (M <= 0) return 0;
   return make_plan(dtype, epi, M, N, K, hl, force_raw, rope_half, head_dim, SIZE_MAX,
                    w8 && gemm_int8_in_kernel(dtype, K)).partial_floats;
+}
+
+// For tests (no device is touched): the plan of one bf16 or float problem.  out: kind, tile rows, tile columns of the weights, K splits,
+// splits of a shared last round, mode, staggered start, finish launch; returns the floats it parks.
+extern "C" size_t cb_internal_projection_plan(int dtype, int epi, int M, int N, int K, int hl, int force_raw, int w8,
+                                              size_t scratch_floats, int *out) {
+  if (M <= 0) return 0;
+  const GemmPlan pl = make_plan(dtype, epi, M, N, K, hl, force_raw, 0, 64, scratch_floats, w8 && gemm_int8_in_kernel(dtype, K));
+  const int v[8] = {pl.kind, pl.bm, pl.out_cols * (epi == EPI_SWIGLU ? 2 : 1), pl.splits, pl.tail_splits, pl.mode, pl.k_stagger,
+                    pl.raw || pl.tail_splits > 1};
+  for (int i = 0; i < 8; ++i) out[i] = v[i];
+  return pl.partial_floats;
 }
 
 static GemmPlan fill_params(const GemmArgs &g, GemmParams *pp) {
