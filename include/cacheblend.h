@@ -164,7 +164,9 @@ int cb_fuse_layer(cb_ctx *ctx, int32_t layer, const cb_layer_weights *weights /*
  * serving loops, harnesses that forbid hipMalloc): same arguments, results and validation, minus the
  * workspace -- the layer's intermediates live in an array of CB_STATIC_SCRATCH_BYTES built into the
  * library (one copy per GPU, held until the process ends).  The call allocates nothing on the device or
- * through the HIP runtime.  A call whose cb_layer_workspace_bytes(ctx, n_rows) exceeds CB_STATIC_SCRATCH_BYTES is
+ * through the HIP runtime.  A call whose cb_layer_workspace_bytes(ctx, n_rows) is at most CB_STATIC_SCRATCH_BYTES
+ * runs as cb_fuse_layer does.  Where that is more, fewer projections are split along their inner dimension
+ * (other orders of addition, larger times); a call that does not fit then either is
  * refused with CB_EWORKSPACE before any launch; the ctx must have been created on the device that is
  * current (else CB_EINVAL).  Every call on a GPU shares that GPU's array: calls that overlap in time on
  * one GPU (two streams, two ctx objects, two threads) race on it.  The array keeps the last call's

@@ -40,6 +40,7 @@ struct cb_ctx {
   std::vector<int32_t> seg_tab_host;     // batched calls: host copy of the request tables being uploaded
   mutable std::vector<size_t> partial_memo;   // [rows] -> scratch floats layer calls with <= rows rows can use
   mutable std::vector<size_t> partial_own;    // [rows] -> the same for exactly that row count
+  mutable std::vector<size_t> partial_least;  // [rows] -> what calls with <= rows rows cannot do without
   void *static_scratch;                  // this device's copy of the built-in scratch array (cb_fuse_layer_static)
 };
 
@@ -118,31 +119,39 @@ int xn_pitch(const cb_ctx *c) { return c->m.d_model + xn_lo_off(c); }
 
 // Floats of scratch (parked projection sums, attention key-range pieces) that layer calls with up
 // to max_rows rows can use: the maximum over EVERY row count, because neither the K split of a
-// projection nor the number of key-range pieces is monotone in the row count.  Memoised per ctx.
+// projection nor the number of key-range pieces is monotone in the row count.  Memoised per ctx, with what is left of it when
+// no projection is split along K (partial_least).
 size_t partial_floats_needed(const cb_ctx *c, int max_rows) {
   const cb_model_desc &m = c->m;
   const int d = m.d_model, q_dim = m.n_q_heads * m.head_dim, kv_dim = m.n_kv_heads * m.head_dim;
   const int rh = m.rope_layout == CB_ROPE_HALF, hl = xn_lo_off(c) > 0 ? 2 * kv_dim : 0, w8 = m.weight_format == CB_W_INT8;
   std::vector<size_t> &memo = c->partial_memo;
-  if (memo.empty()) { memo.push_back(0); c->partial_own.push_back(0); }
+  if (memo.empty()) { memo.push_back(0); c->partial_own.push_back(0); c->partial_least.push_back(0); }
   while ((int)memo.size() <= max_rows) {
     const int M = (int)memo.size();
-    size_t need = gemm_partial_floats(m.dtype, EPI_SEG, M, 2 * kv_dim, d, hl, 1, rh, m.head_dim, w8);             // K|V, checked
-    need = std::max(need, gemm_partial_floats(m.dtype, EPI_SEG, M, 2 * kv_dim, d, hl, 0, rh, m.head_dim, w8));   // K|V, every row kept
-    need = std::max(need, gemm_partial_floats(m.dtype, EPI_SEG, M, q_dim, d, 0, 0, rh, m.head_dim, w8));         // Q
-    need = std::max(need, gemm_partial_floats(m.dtype, EPI_F32, M, d, q_dim, 0, 0, 0, 0, w8));
-    need = std::max(need, gemm_partial_floats(m.dtype, EPI_F32, M, d, m.d_ff, 0, 0, 0, 0, w8));
-    need = std::max(need, gemm_partial_floats(m.dtype, EPI_SWIGLU, M, m.d_ff, d, 0, 0, 0, 0, w8));
+    auto projections = [&](bool split) {
+      auto floats = [&](int epi, int N, int K, int hl_cols, int force_raw, int half) {
+        return gemm_partial_floats(m.dtype, epi, M, N, K, hl_cols, force_raw, half, m.head_dim, w8, split);
+      };
+      size_t need = floats(EPI_SEG, 2 * kv_dim, d, hl, 1, rh);                   // K|V, checked
+      need = std::max(need, floats(EPI_SEG, 2 * kv_dim, d, hl, 0, rh));          // K|V, every row kept
+      need = std::max(need, floats(EPI_SEG, q_dim, d, 0, 0, rh));                // Q
+      need = std::max(need, floats(EPI_F32, d, q_dim, 0, 0, 0));
+      need = std::max(need, floats(EPI_F32, d, m.d_ff, 0, 0, 0));
+      return std::max(need, floats(EPI_SWIGLU, m.d_ff, d, 0, 0, 0));
+    };
     // the attention KV split borrows the same scratch (the two are never live together)
-    need = std::max(need, attention_partial_floats_bound(m.dtype, M, m.n_q_heads, m.n_kv_heads, m.head_dim));
+    const size_t attn = attention_partial_floats_bound(m.dtype, M, m.n_q_heads, m.n_kv_heads, m.head_dim);
+    const size_t need = std::max(projections(true), attn);
+    c->partial_least.push_back(std::max(std::max(projections(false), attn), c->partial_least.back()));
     c->partial_own.push_back(need);
     memo.push_back(std::max(need, memo.back()));
   }
   return memo[max_rows];
 }
 
-// carve the per-layer workspace out of [base, base + avail); base may be NULL to size only
-LayerWs carve_layer(const cb_ctx *c, char *base, int R) {
+// lay the per-layer workspace out from base on (NULL: sizes only)
+LayerWs lay_out(const cb_ctx *c, char *base, int R, size_t partial_floats) {
   const cb_model_desc &m = c->m;
   const size_t es = esize(c);
   const size_t q_dim = (size_t)m.n_q_heads * m.head_dim, kv_dim = (size_t)m.n_kv_heads * m.head_dim;
@@ -160,7 +169,7 @@ LayerWs carve_layer(const cb_ctx *c, char *base, int R) {
   w.obuf = take((size_t)R * q_dim * es);
   w.act = take((size_t)R * m.d_ff * es);
   w.hmid = (float *)take((size_t)R * m.d_model * 4);
-  w.partial_floats = partial_floats_needed(c, R);
+  w.partial_floats = partial_floats;
   w.partial = (float *)take(w.partial_floats * 4);
   w.dev = (float *)take((size_t)R * 4);
   w.sel_rows = (int32_t *)take((size_t)R * 4);
@@ -176,6 +185,15 @@ LayerWs carve_layer(const cb_ctx *c, char *base, int R) {
   w.wstage = take(stage);
   w.bytes = off;
   return w;
+}
+// avail: where the workspace of the fastest plans is larger, projections park as little as fits, as long as that is possible at all
+// (unsplit; bytes > avail otherwise).
+LayerWs carve_layer(const cb_ctx *c, char *base, int R, size_t avail = SIZE_MAX) {
+  const size_t most = partial_floats_needed(c, R);
+  const LayerWs w = lay_out(c, base, R, most);
+  if (w.bytes <= avail) return w;
+  const size_t over = align_up(w.bytes - avail, 256) / 4;
+  return over + c->partial_least[R] <= most ? lay_out(c, base, R, most - over) : w;
 }
 
 #define CB_HIP(expr)                     \
@@ -324,7 +342,7 @@ int fuse_layer_impl(cb_ctx *c, const cb_layer_weights *w, const float *h_in, con
   // The split of the merged launch is capped by what the other projections of this row count park, so that a call
   // needs no more workspace for it.
   const bool w8 = m.weight_format == CB_W_INT8 && gemm_int8_in_kernel(1, d);
-  const size_t own = n < (int)c->partial_own.size() ? c->partial_own[n] : 0;
+  const size_t own = n < (int)c->partial_own.size() ? std::min(c->partial_own[n], ws.partial_floats) : 0;
   // (a float model has no operand pairs; a launch costs it as much as 0.25 GFLOP, and the sums are parked in the MLP's
   // activation buffer, which is idle here)
   const bool merged = rows > 0 && !kv_only && (dt == CB_F32 ? F >= 2 * kv_dim + q_dim && 2.0 * (n - rows) * d * q_dim < 2.5e8
@@ -617,11 +635,14 @@ int cb_realign_rope(cb_ctx *c, void *const *k_cache_layers, int32_t layer_begin,
   return CB_OK;
 }
 
-int cb_fuse_layer(cb_ctx *c, int32_t layer, const cb_layer_weights *w, const float *h_in,
-                  const int32_t *row_pos, int32_t n_rows, int32_t n_suffix, void *k_cache, void *v_cache,
-                  int32_t n_tokens_total, int32_t k_keep, const int32_t *forced_sel, float *h_out,
-                  int32_t *pos_out, float *dev_out, void *workspace, size_t workspace_bytes,
-                  void *stream) {
+namespace {
+
+// Body of cb_fuse_layer and cb_fuse_layer_static.  fit: the plans make do with the workspace there is (carve_layer)
+int fuse_one_layer(cb_ctx *c, int32_t layer, const cb_layer_weights *w, const float *h_in,
+                   const int32_t *row_pos, int32_t n_rows, int32_t n_suffix, void *k_cache, void *v_cache,
+                   int32_t n_tokens_total, int32_t k_keep, const int32_t *forced_sel, float *h_out,
+                   int32_t *pos_out, float *dev_out, void *workspace, size_t workspace_bytes, bool fit,
+                   void *stream) {
   int st = check_layer_args(c, layer, w, n_rows, n_suffix, n_tokens_total, k_keep);
   if (st != CB_OK) return st;
   if (!h_in || !row_pos || !k_cache || !v_cache || !h_out || !pos_out || !workspace) return CB_ENULL;
@@ -631,11 +652,22 @@ int cb_fuse_layer(cb_ctx *c, int32_t layer, const cb_layer_weights *w, const flo
       !aligned(workspace, 256))
     return CB_EINVAL;
   if (n_rows == 0) return CB_OK;
-  LayerWs ws = carve_layer(c, (char *)workspace, n_rows);
+  LayerWs ws = carve_layer(c, (char *)workspace, n_rows, fit ? workspace_bytes : SIZE_MAX);
   if (ws.bytes > workspace_bytes) return CB_EWORKSPACE;
   const Seg seg = {n_rows, n_suffix, k_keep, n_tokens_total};
   return fuse_layer_impl(c, w, h_in, row_pos, nullptr, &seg, 1, 0, k_cache, v_cache, forced_sel, h_out, pos_out,
                          nullptr, dev_out, ws, (hipStream_t)stream, false, nullptr, false);
+}
+
+}  // namespace
+
+int cb_fuse_layer(cb_ctx *c, int32_t layer, const cb_layer_weights *w, const float *h_in,
+                  const int32_t *row_pos, int32_t n_rows, int32_t n_suffix, void *k_cache, void *v_cache,
+                  int32_t n_tokens_total, int32_t k_keep, const int32_t *forced_sel, float *h_out,
+                  int32_t *pos_out, float *dev_out, void *workspace, size_t workspace_bytes,
+                  void *stream) {
+  return fuse_one_layer(c, layer, w, h_in, row_pos, n_rows, n_suffix, k_cache, v_cache, n_tokens_total, k_keep, forced_sel,
+                        h_out, pos_out, dev_out, workspace, workspace_bytes, false, stream);
 }
 
 size_t cb_static_scratch_bytes(void) { return CB_STATIC_SCRATCH_BYTES; }
@@ -645,16 +677,16 @@ int cb_fuse_layer_static(cb_ctx *c, int32_t layer, const cb_layer_weights *w, co
                          void *v_cache, int32_t n_tokens_total, int32_t k_keep, const int32_t *forced_sel,
                          float *h_out, int32_t *pos_out, float *dev_out, void *stream) {
   if (!c) return CB_ENULL;
-  if (n_rows > 0 && cb_layer_workspace_bytes(c, n_rows) > CB_STATIC_SCRATCH_BYTES) return CB_EWORKSPACE;
+  if (n_rows > 0 && carve_layer(c, nullptr, n_rows, CB_STATIC_SCRATCH_BYTES).bytes > CB_STATIC_SCRATCH_BYTES) return CB_EWORKSPACE;
   int device = -1;
   if (hipGetDevice(&device) != hipSuccess) return CB_EHIP;
   if (device != c->device) return CB_EINVAL;   // the ctx's device holds the scratch this call would use
   // per-launch timing creates events; this entry point creates nothing
   const int profiling = c->profiling;
   c->profiling = 0;
-  const int st = cb_fuse_layer(c, layer, w, h_in, row_pos, n_rows, n_suffix, k_cache, v_cache, n_tokens_total,
-                               k_keep, forced_sel, h_out, pos_out, dev_out, c->static_scratch,
-                               CB_STATIC_SCRATCH_BYTES, stream);
+  const int st = fuse_one_layer(c, layer, w, h_in, row_pos, n_rows, n_suffix, k_cache, v_cache, n_tokens_total,
+                                k_keep, forced_sel, h_out, pos_out, dev_out, c->static_scratch,
+                                CB_STATIC_SCRATCH_BYTES, true, stream);
   c->profiling = profiling;
   return st;
 }

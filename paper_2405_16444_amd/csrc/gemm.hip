@@ -1580,9 +1580,9 @@ static int problem_n(const GemmArgs &g) {
 }
 
 size_t gemm_partial_floats(int dtype, int epi, int M, int N, int K, int hl, int force_raw, int rope_half,
-                           int head_dim, int w8) {
+                           int head_dim, int w8, bool split) {
   if (M <= 0) return 0;
-  return make_plan(dtype, epi, M, N, K, hl, force_raw, rope_half, head_dim, SIZE_MAX,
+  return make_plan(dtype, epi, M, N, K, hl, force_raw, rope_half, head_dim, split ? SIZE_MAX : 0,
                    w8 && gemm_int8_in_kernel(dtype, K)).partial_floats;
 }
 

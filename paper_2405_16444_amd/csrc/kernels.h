@@ -112,12 +112,12 @@ struct GemmArgs {
 // (0 when the main kernel finishes the outputs itself); N is the total number of output columns
 // (d_ff for EPI_SWIGLU); hl: leading output columns with (high, low) activation pairs; force_raw: a deviation is wanted; w8: int8
 // weights (read by the kernel itself where it can).
-// For workspace sizing.
+// For workspace sizing.  split false: without any K split, the least it runs with.
 // whether the projection kernels read int8 weights themselves for this storage type and K (else the caller
 // expands them to the storage type first)
 bool gemm_int8_in_kernel(int dtype, int K);
 size_t gemm_partial_floats(int dtype, int epi, int M, int N, int K, int hl, int force_raw, int rope_half,
-                           int head_dim, int w8 = 0);
+                           int head_dim, int w8 = 0, bool split = true);
 // Whether ONE launch over hl_cols columns with (high, low) pairs and n_rest columns without, all for M rows, is estimated
 // to take less time than a launch per kind, the second for M_rest rows only (bf16 EPI_SEG).  split_floats caps the scratch.
 bool gemm_merge_pays(int M, int hl_cols, int M_rest, int n_rest, int K, int force_raw, int w8, size_t split_floats);

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import announce, dev_layers
+from gpu_util import TOL, announce, dev_layers, max_abs_rel, to_np
 from test_gpu_parity import BF16_M, F32_M, layer_case
 
 pytestmark = pytest.mark.gpu
@@ -76,3 +76,24 @@ def test_static_scratch_entry_refuses_requests_beyond_its_array(P):
         P.cb_fuse_layer_static(ctx, 0, lw, h, pos, 0, kc, vc, rows, h_out, pos_out)
     assert e.value.status == -3                      # CB_EWORKSPACE
     P.cb_destroy(ctx)
+
+
+@pytest.mark.parametrize("rows,d,d_ff", [(2063, 1536, 8960), (2190, 1536, 8960), (1629, 2304, 9216)])
+def test_static_scratch_entry_takes_what_fits_with_fewer_splits(P, rows, d, d_ff):
+    """Row counts near the largest that the array holds: the workspace of the fastest plans is larger than it or not, whatever the cost
+    models say, the call runs.  Other K splits add the same floats in another order, so the results agree to the bf16 tolerance."""
+    from workloads.configs import ModelShape
+    model = ModelShape(1, d, d // 128, 2, 128, d_ff, 1e-5, 1e4, "bf16")
+    announce("no_alloc near the size limit", rows, d, d_ff)
+    lw, h, pos, kc, vc = layer_case(model, rows + 30, rows, 40, seed=rows, std=d ** -0.5)
+    ctx = P.cb_create(model, rows + 30)
+    dlw, hd, pd = dev_layers([lw])[0], h.cuda(), pos.cuda()
+    k1, v1, k2, v2 = kc.cuda().contiguous(), vc.cuda().contiguous(), kc.cuda().contiguous(), vc.cuda().contiguous()
+    h1, p1, _ = P.cb_fuse_layer(ctx, 0, dlw, hd, pd, 40, k1, v1, rows - 40)
+    h2, p2 = torch.empty_like(h1), torch.empty_like(p1)
+    P.cb_fuse_layer_static(ctx, 0, dlw, hd, pd, 40, k2, v2, rows - 40, h2, p2)
+    torch.cuda.synchronize()
+    P.cb_destroy(ctx)
+    assert torch.equal(p1, p2)
+    for a, b in ((h2, h1), (k2, k1), (v2, v1)):
+        assert max_abs_rel(to_np(a), to_np(b)) < TOL["bf16"]
