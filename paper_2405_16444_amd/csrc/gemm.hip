@@ -1373,33 +1373,45 @@ static int xcd_groups(int splits, int tiles_m, int tiles_n, int hl) {
 //                   it off (bf16; the int8 expansions stay).  Split shares of a multiple of 4 KB (32 k-tiles) start
 //                   at the same place of the memory channels' interleave: 1.12 t (4096 x 14336 at 110 rows in 7 splits of
 //                   32 k-tiles 42.5 us, in 8 of 28 36.0 us); rows of a power-of-two pitch are staggered instead.
-//   finish launch = 1.5 / 2.3 us + 0.34 / 0.5 us per MB of parked sums (splits x M x N floats), bf16 / int8, stores included
+//   finish launch = finish + park per MB of parked sums (splits x M x N floats), stores included
 // Its choice is on average within 1.3 % (bf16) and 1.0 % (int8) of the best pair of the sweep; the six tiles that all three
 // projections share came within 2.9 % of it, with 256 x 128 on eight wavefronts, 192 x 224 and 320 x 192 for float outputs the
 // output and down projections take 1.7 % less (7168 x 20480 at 580 rows 209 -> 183 us).
-// t = 0: not used with that weight format.
+// K and V alone, all of whose columns take operand pairs, keep constants of their own (kPairs): with those of the other bf16
+// projections it chose too many splits of too wide tiles (2048 x 4096 at 64 rows in 8 splits of 64 x 128 15.7 us, in 16 of
+// 128 x 128 18.6; 2600 rows of 2048 x 7168 132 -> 142 us), over 836 sizes of 11 models 0.3 % more on average, 54 of them by more than 3 %.
+// t = 0: not used.
 // max_splits caps the split (scratch the caller can spare); parked: a finish launch runs anyway.
-struct DmaShape { int tile; double t[2]; };               // t: bf16, int8 weights
-static constexpr DmaShape kDmaShapes[] = {{T64x128, {0.52, 0.72}}, {T128x128, {0.61, 0.94}}, {T192x128, {0.73, 0.0}},
-                                          {T128x256, {0.88, 1.32}}, {T192x256, {1.21, 1.53}}, {T256x256, {1.38, 1.89}},
-                                          {T256x128w8, {0.83, 0.0}}, {T192x224, {1.14, 0.0}}, {T320x192, {1.40, 0.0}}};
+constexpr int kProjectionTiles[] = {T64x128, T128x128, T192x128, T128x256, T192x256, T256x256, T256x128w8, T192x224, T320x192};
 constexpr int kSharedShapes = 6;                           // the leading ones serve the Q/K/V projections too
+constexpr int kFloatOutputShapes = sizeof(kProjectionTiles) / sizeof(kProjectionTiles[0]);
+struct ProjectionModel {
+  double t[kFloatOutputShapes];
+  double padded;         // share of t that a row tile's blocks without real rows take off
+  double fixed, round;   // us; per further round
+  double finish, park;   // us; us per MB
+  double read;           // MB per us
+  double aligned;        // factor of t where the split shares are a multiple of 4 KB apart
+};
+static constexpr ProjectionModel kBf16 = {{0.52, 0.61, 0.73, 0.88, 1.21, 1.38, 0.83, 1.14, 1.40}, 0.18, 9.6, 3.3, 1.5, 0.342, 5.95, 1.12};
+static constexpr ProjectionModel kPairs = {{0.58, 0.72, 0.82, 0.97, 1.28, 1.50}, 0, 9.5, 0, 2.3, 0.5, 5.2, 1};
+static constexpr ProjectionModel kInt8 = {{0.72, 0.94, 0, 1.32, 1.53, 1.89}, 0, 9.5, 0, 2.3, 0.5, 5.2, 1};
+constexpr int projection_shapes(int epi) { return epi == EPI_SEG ? kSharedShapes : kFloatOutputShapes; }
 
 // Output columns [0, hl_cols) take (high, low) activation pairs, i.e. twice the tile rows per output row.
-static void pick_dma_plan(int epi, int M, int N, int hl_cols, int K, int max_splits, bool parked, bool w8, GemmPlan *pl) {
+static void pick_dma_plan(const ProjectionModel &m, int epi, int M, int N, int hl_cols, int K, int max_splits, bool parked, bool w8,
+                          GemmPlan *pl) {
   const int k_tiles = K / DMA_BK;
-  const double park_us = (double)M * N * 4.0e-6 * (w8 ? 0.5 : 0.342);     // per split
-  const double read_us = hl_cols ? 0.0 : (double)N * K * (w8 ? 1 : 2) / (w8 ? 5.2e6 : 5.95e6);
+  const double park_us = (double)M * N * 4.0e-6 * m.park;  // per split
+  const double read_us = hl_cols ? 0.0 : (double)N * K * (w8 ? 1 : 2) / (m.read * 1e6);
   pl->cost = 1e30;
-  for (int i = 0; i < (epi == EPI_SEG ? kSharedShapes : (int)(sizeof(kDmaShapes) / sizeof(kDmaShapes[0]))); ++i) {
-    const DmaShape &c = kDmaShapes[i];
-    const DmaTile t = kDmaTiles[c.tile];
+  for (int i = 0; i < projection_shapes(epi); ++i) {
+    const DmaTile t = kDmaTiles[kProjectionTiles[i]];
     const int bm = t.bm(), bn = t.bn();
-    if (c.t[w8] == 0.0 || (bm == 64 && M > 64)) continue;
+    if (m.t[i] == 0.0 || (bm == 64 && M > 64)) continue;
     if (hl_cols < N && hl_cols % bn != 0) continue;        // a tile's columns are of one kind
     const int tiles_m = ceil_div(M, bm);
-    const long steps = row_block_steps(t, M);
-    const double t_rows = w8 ? c.t[1] : c.t[0] * (0.82 + 0.18 * steps / ((double)tiles_m * t.RB));
+    const double t_rows = m.t[i] * (1.0 - m.padded + m.padded * row_block_steps(t, M) / ((double)tiles_m * t.RB));
     for (int sp = 1; sp <= 16 && sp <= max_splits; ++sp) {
       if (sp > 1 && k_tiles / sp < 4) break;
       const int groups = xcd_groups(sp, tiles_m, ceil_div(N - hl_cols, bn), hl_cols);
@@ -1407,10 +1419,10 @@ static void pick_dma_plan(int epi, int M, int N, int hl_cols, int K, int max_spl
                             (long)tiles_m * ceil_div(ceil_div(N - hl_cols, bn), groups)) * (groups < 8 ? 1 : sp);
       const long rounds = (per_xcd + 31) / 32;
       const int kt = ceil_div(k_tiles, sp);
-      const double tk = !w8 && sp > 1 && groups == 8 && kt % 32 == 0 && !pitch_is_power_of_two(K) ? 1.12 * t_rows : t_rows;
-      const double fixed = w8 ? 9.5 : 9.6 + 3.3 * (rounds - 1), finish = w8 ? 2.3 : 1.5;
-      const double cost = std::max(rounds * tk * kt, read_us) + fixed + (sp > 1 || parked ? sp * park_us + finish : 0.0);
-      if (cost < pl->cost - 1e-9) { pl->cost = cost; pl->tile = c.tile; pl->splits = sp; }
+      const double tk = sp > 1 && groups == 8 && kt % 32 == 0 && !pitch_is_power_of_two(K) ? m.aligned * t_rows : t_rows;
+      const double cost = std::max(rounds * tk * kt, read_us) + m.fixed + m.round * (rounds - 1) +
+                          (sp > 1 || parked ? sp * park_us + m.finish : 0.0);
+      if (cost < pl->cost - 1e-9) { pl->cost = cost; pl->tile = kProjectionTiles[i]; pl->splits = sp; }
     }
   }
 }
@@ -1441,8 +1453,8 @@ constexpr bool dma_tile_planned(int epi, int tile, bool w8) {
       if (c.tile == tile && c.idle != 0.f) return true;
     return false;
   }
-  for (int i = 0; i < (epi == EPI_SEG ? kSharedShapes : (int)(sizeof(kDmaShapes) / sizeof(kDmaShapes[0]))); ++i)
-    if (kDmaShapes[i].tile == tile && kDmaShapes[i].t[w8] != 0.0) return true;
+  for (int i = 0; i < projection_shapes(epi); ++i)
+    if (kProjectionTiles[i] == tile && (w8 ? kInt8 : kBf16).t[i] != 0.0) return true;
   return false;
 }
 static void pick_swiglu_plan(int M, int N, int K, size_t scratch_floats, bool w8, GemmPlan *pl) {
@@ -1499,9 +1511,9 @@ bool gemm_int8_in_kernel(int dtype, int K) { return dtype == 1 && K % DMA_BK == 
 
 // Shape of one problem.  hl: leading output columns with (high, low) activation pairs; force_raw: the caller wants the finish
 // launch (deviation, or the float output's residual + norm); scratch_floats: what `partial` holds
-// (the K split is capped by it; SIZE_MAX when sizing).
+// (the K split is capped by it; SIZE_MAX when sizing); model: another cost model than the problem's own.
 static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int force_raw, int rope_half,
-                          int head_dim, size_t scratch_floats, bool w8 = false) {
+                          int head_dim, size_t scratch_floats, bool w8 = false, const ProjectionModel *model = nullptr) {
   GemmPlan pl = {};
   pl.w8 = w8;
   pl.tail_splits = 1;
@@ -1521,7 +1533,7 @@ static GemmPlan make_plan(int dtype, int epi, int M, int N, int K, int hl, int f
     pick_swiglu_plan(M, N, K, scratch_floats, w8, &pl);
   } else {
     pl.kind = 2; pl.bk = DMA_BK; pl.tile = -1;
-    pick_dma_plan(epi, M, N, pl.hl, K, max_splits, pl.raw, w8, &pl);
+    pick_dma_plan(model ? *model : w8 ? kInt8 : pl.hl == N ? kPairs : kBf16, epi, M, N, pl.hl, K, max_splits, pl.raw, w8, &pl);
     if (pl.tile < 0) { pl.bad = true; pl.tile = T256x256; }    // no tile width divides the columns with pairs
   }
   if (pl.kind == 2) {
@@ -1639,10 +1651,13 @@ static GemmPlan fill_params(const GemmArgs &g, GemmParams *pp) {
 
 bool gemm_merge_pays(int M, int hl_cols, int M_rest, int n_rest, int K, int force_raw, int w8, size_t split_floats) {
   if (M <= 0 || M_rest <= 0 || K % DMA_BK != 0) return false;
-  const GemmPlan one = make_plan(1, EPI_SEG, M, hl_cols + n_rest, K, hl_cols, force_raw, 0, 0, split_floats, w8);
+  // one model for all three (bf16: over 7169 sizes of 11 models the calls take 0.1 % more than with the better choice each time; with a
+  // model for K and V alone and another for the rest, whose errors differ, 0.4 %)
+  const ProjectionModel *model = w8 ? &kInt8 : &kPairs;
+  const GemmPlan one = make_plan(1, EPI_SEG, M, hl_cols + n_rest, K, hl_cols, force_raw, 0, 0, split_floats, w8, model);
   if (one.bad || one.kind != 2) return false;
-  const GemmPlan kv = make_plan(1, EPI_SEG, M, hl_cols, K, hl_cols, force_raw, 0, 0, split_floats, w8);
-  const GemmPlan q = make_plan(1, EPI_SEG, M_rest, n_rest, K, 0, 0, 0, 0, split_floats, w8);
+  const GemmPlan kv = make_plan(1, EPI_SEG, M, hl_cols, K, hl_cols, force_raw, 0, 0, split_floats, w8, model);
+  const GemmPlan q = make_plan(1, EPI_SEG, M_rest, n_rest, K, 0, 0, 0, 0, split_floats, w8, model);
   return one.cost < kv.cost + q.cost;
 }
 
