@@ -1373,10 +1373,15 @@ static int xcd_groups(int splits, int tiles_m, int tiles_n, int hl) {
 //                   it off (bf16; the int8 expansions stay).  Split shares of a multiple of 4 KB (32 k-tiles) start
 //                   at the same place of the memory channels' interleave: 1.12 t (4096 x 14336 at 110 rows in 7 splits of
 //                   32 k-tiles 42.5 us, in 8 of 28 36.0 us); rows of a power-of-two pitch are staggered instead.
-//   finish launch = finish + park per MB of parked sums (splits x M x N floats), stores included
-// Its choice is on average within 1.3 % (bf16) and 1.0 % (int8) of the best pair of the sweep; the six tiles that all three
-// projections share came within 2.9 % of it, with 256 x 128 on eight wavefronts, 192 x 224 and 320 x 192 for float outputs the
-// output and down projections take 1.7 % less (7168 x 20480 at 580 rows 209 -> 183 us).
+//   finish launch = finish + park per MB of parked sums (splits x M x N floats), stores included, and 0.2 us per split where it
+//                   runs anyway (it reads a few of a row's splits at a time; where it does not, an unsplit launch's own epilogue
+//                   costs about as much).  Without that, small launches took twice the splits they gain by: 1024 x 2816 at 720
+//                   rows 17.2 -> 18.8 us.
+// Of the pairs of a sweep over 1 .. 6144 rows (profiles/projection_tiles.tsv has a part of it) its bf16 choice is on average within 1.8 %
+// (output and down; the six tiles that all three projections share come within 2.4 %) and 1.2 % (Q/K/V) of the best on the three models it was
+// fitted to, and within 1.4 % and 1.2 % on eight others of 512 .. 5120 columns; int8 within 1.0 %.  192 x 224 only pays where it
+// saves a round (7168 x 20480 at 580 rows 209 -> 183 us with 320 x 192): with t below that of 192 x 256 it was taken
+// where the rounds are the same, 7168 x 7168 at 285 rows 54 -> 56 us, 5120 x 5120 at 1600 rows 110 -> 117 us.
 // K and V alone, all of whose columns take operand pairs, keep constants of their own (kPairs): with those of the other bf16
 // projections it chose too many splits of too wide tiles (2048 x 4096 at 64 rows in 8 splits of 64 x 128 15.7 us, in 16 of
 // 128 x 128 18.6; 2600 rows of 2048 x 7168 132 -> 142 us), over 836 sizes of 11 models 0.3 % more on average, 54 of them by more than 3 %.
@@ -1389,20 +1394,20 @@ struct ProjectionModel {
   double t[kFloatOutputShapes];
   double padded;         // share of t that a row tile's blocks without real rows take off
   double fixed, round;   // us; per further round
-  double finish, park;   // us; us per MB
+  double finish, park, split;   // us; us per MB; us per split (of launches with a finish launch anyway)
   double read;           // MB per us
   double aligned;        // factor of t where the split shares are a multiple of 4 KB apart
 };
-static constexpr ProjectionModel kBf16 = {{0.52, 0.61, 0.73, 0.88, 1.21, 1.38, 0.83, 1.14, 1.40}, 0.18, 9.6, 3.3, 1.5, 0.342, 5.95, 1.12};
-static constexpr ProjectionModel kPairs = {{0.58, 0.72, 0.82, 0.97, 1.28, 1.50}, 0, 9.5, 0, 2.3, 0.5, 5.2, 1};
-static constexpr ProjectionModel kInt8 = {{0.72, 0.94, 0, 1.32, 1.53, 1.89}, 0, 9.5, 0, 2.3, 0.5, 5.2, 1};
+static constexpr ProjectionModel kBf16 = {{0.52, 0.61, 0.73, 0.88, 1.21, 1.38, 0.83, 1.22, 1.40}, 0.18, 9.6, 3.3, 1.5, 0.342, 0.2, 5.95, 1.12};
+static constexpr ProjectionModel kPairs = {{0.58, 0.72, 0.82, 0.97, 1.28, 1.50}, 0, 9.5, 0, 2.3, 0.5, 0, 5.2, 1};
+static constexpr ProjectionModel kInt8 = {{0.72, 0.94, 0, 1.32, 1.53, 1.89}, 0, 9.5, 0, 2.3, 0.5, 0, 5.2, 1};
 constexpr int projection_shapes(int epi) { return epi == EPI_SEG ? kSharedShapes : kFloatOutputShapes; }
 
 // Output columns [0, hl_cols) take (high, low) activation pairs, i.e. twice the tile rows per output row.
 static void pick_dma_plan(const ProjectionModel &m, int epi, int M, int N, int hl_cols, int K, int max_splits, bool parked, bool w8,
                           GemmPlan *pl) {
   const int k_tiles = K / DMA_BK;
-  const double park_us = (double)M * N * 4.0e-6 * m.park;  // per split
+  const double park_us = (double)M * N * 4.0e-6 * m.park + (parked ? m.split : 0.0);  // per split
   const double read_us = hl_cols ? 0.0 : (double)N * K * (w8 ? 1 : 2) / (m.read * 1e6);
   pl->cost = 1e30;
   for (int i = 0; i < projection_shapes(epi); ++i) {

@@ -55,6 +55,9 @@ def measured():
 # a matter of 1 .. 3 us in launches of 10 .. 25.
 CHOICES = {
     "K and V alone": (lambda kind, n, hl, w8: kind == "seg" and n == hl, 1.015, 1.18),
+    "output and down": (lambda kind, n, hl, w8: kind == "f32", 1.015, 1.21),
+    "K, V and Q": (lambda kind, n, hl, w8: kind == "seg" and 0 < hl < n, 1.01, 1.15),
+    "Q alone": (lambda kind, n, hl, w8: kind == "seg" and hl == 0, 1.02, 1.12),
 }
 
 
