@@ -1432,22 +1432,24 @@ static void pick_dma_plan(const ProjectionModel &m, int epi, int M, int N, int h
   }
 }
 
-// Tile of the gate/up projection, and how its last round of workgroups is shared: a cost model in microseconds fitted to a sweep of
-// every tile over 28672 x 4096, 57344 x 8192 and 40960 x 7168 (gate and up rows together) at 24 .. 3072 rows, bf16 and
-// int8 weights: its choice is on average within 0.5 % (bf16) and 1.1 % (int8) of the best tile.
+// Tile of the gate/up projection, and how its last round of workgroups is shared: a cost model in microseconds fitted to sweeps of
+// every tile at 1 .. 6144 rows, bf16 and int8 weights, of the 7B, 34B and 70B models and eight others of 512 .. 5120 columns
+// (profiles/projection_tiles.tsv has a part of them): its choice is on average within 0.9 % (bf16) and 1.0 % (int8) of the best.
 //   a round   = (idle + rows x share of the tile's row blocks that hold real rows) x k-tiles; a launch of less than one round runs
-//               faster than its share of the chip (power): down to 1 - kPartial of that
+//               faster than its share of the chip (power): down to 1 - partial of that
 //               at least the weights it reads, at 6.2 TB/s where every CU takes part, less where fewer do
 //   launch    = 8 us + its rounds of 256 workgroups; no K split (the epilogue needs whole gate and up sums), but the workgroups
-//               of a partly filled last round can share its tiles along K, 2 .. 4 per tile: their raw sums go through memory
-//               (bf16 / int8 fit: 7.1 / 4 TB/s both ways) and a second launch finishes them (2.5 / 8 us); where another
-//               tile does without and the two are within 3 % that one is taken (40960 x 7168 at 430 rows: the call 2 % faster)
+//               of a partly filled last round (or only one) can share its tiles along K, 2 .. 4 per tile: their raw sums go through memory
+//               (bf16 / int8 fit: 7.1 / 6 TB/s both ways) and a second launch finishes them (2.5 / 1 us); bf16: where another
+//               tile does without and the two are within 3 % that one is taken (40960 x 7168 at 430 rows: the call 2 % faster).
+//               Int8 weights, 28672 x 4096 at 580 rows, 256 x 256 tiles shared by three 158 us, 192 x 256 ones 165; 22016 x 4096 at 640
+//               shared by four 129, 128 x 256 ones 140; bf16, 16384 x 3072 at 128 rows, 128 tiles shared by two 34 us, alone 38
 //   384 x 128 is for a single row tile: 28672 x 4096 at 350 rows 87 -> 82 us, but at 640 rows 147 -> 159 us
 struct SwigluShape { int tile; float idle, rows; };
 static constexpr SwigluShape kSwigluShapes[2][16] = {
-    {{T64x128, .53f, .14f}, {T128x128, .55f, .15f}, {T128x160, .49f, .25f}, {T128x224, .65f, .33f}, {T192x128, .60f, .16f},
+    {{T64x128, .45f, .11f}, {T128x128, .51f, .10f}, {T128x160, .53f, .25f}, {T128x224, .65f, .33f}, {T192x128, .65f, .15f},
      {T192x160, .64f, .33f}, {T192x224, .85f, .44f}, {T192x256, 1.01f, .27f}, {T256x128w8, .61f, .32f}, {T256x160, .73f, .37f},
-     {T256x224, .98f, .52f}, {T256x256, 1.21f, .32f}, {T320x160, .89f, .46f}, {T320x192, 1.02f, .52f}, {T384x128, .81f, .42f},
+     {T256x224, .98f, .52f}, {T256x256, 1.21f, .32f}, {T320x160, .89f, .46f}, {T320x192, 1.02f, .52f}, {T384x128, .86f, .44f},
      {T384x160, 1.03f, .53f}},
     {{T64x128, .38f, .14f}, {T128x128, .64f, .19f}, {T128x256, .79f, .24f}, {T192x128w8, .72f, .20f}, {T192x160, .82f, .27f},
      {T192x256, .97f, .33f}, {T256x160, .95f, .34f}, {T256x256, 1.16f, .42f}, {T320x160, 1.07f, .40f}, {T384x160, 1.18f, .47f}}};
@@ -1464,7 +1466,7 @@ constexpr bool dma_tile_planned(int epi, int tile, bool w8) {
 }
 static void pick_swiglu_plan(int M, int N, int K, size_t scratch_floats, bool w8, GemmPlan *pl) {
   const int k_tiles = K / DMA_BK;
-  const double partial = w8 ? 0.2 : 0.38, starve = w8 ? 0.1 : 0.65;
+  const double partial = w8 ? 0.2 : 0.38, starve = w8 ? 0.1 : 0.3;
   double best = 1e30;
   for (const SwigluShape &c : kSwigluShapes[w8]) {
     const DmaTile t = kDmaTiles[c.tile];
@@ -1481,19 +1483,19 @@ static void pick_swiglu_plan(int M, int N, int K, size_t scratch_floats, bool w8
     int ts = 1;
     if (tail) {
       double last = round_us(tail, k_tiles);
-      ts = full ? (int)std::min<long>(4, 256 / tail) : 1;
+      ts = (int)std::min<long>(4, 256 / tail);
       while (ts > 1 && k_tiles / ts < 8) --ts;
       if (ts > 1) {
         const int k = ceil_div(k_tiles, ts);
         const double floats = (double)tail * ts * t.bm() * t.bn();
-        const double shared = round_us(tail * ts, k) + floats * 8 / (w8 ? 4.0e6 : 7.1e6) + (w8 ? 8.0 : 2.5);
+        const double shared = round_us(tail * ts, k) + floats * 8 / (w8 ? 6.0e6 : 7.1e6) + (w8 ? 1.0 : 2.5);
         const size_t need = (size_t)tail * ceil_div(k_tiles, k) * t.bm() * t.bn();
         if (shared < last && need <= scratch_floats) last = shared;
         else ts = 1;
       }
       cost += last;
     }
-    if (ts > 1) cost *= 1.03;
+    if (ts > 1 && !w8) cost *= 1.03;
     if (cost < best - 1e-9) { best = cost; pl->tile = c.tile; pl->tail_splits = ts; }
   }
 }

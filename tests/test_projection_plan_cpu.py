@@ -57,6 +57,8 @@ CHOICES = {
     "K and V alone": (lambda kind, n, hl, w8: kind == "seg" and n == hl, 1.015, 1.18),
     "output and down": (lambda kind, n, hl, w8: kind == "f32", 1.015, 1.21),
     "K, V and Q": (lambda kind, n, hl, w8: kind == "seg" and 0 < hl < n, 1.01, 1.15),
+    "gate and up": (lambda kind, n, hl, w8: kind == "gate_up" and not w8, 1.01, 1.11),
+    "gate and up, int8": (lambda kind, n, hl, w8: kind == "gate_up" and w8, 1.01, 1.18),
     "Q alone": (lambda kind, n, hl, w8: kind == "seg" and hl == 0, 1.02, 1.12),
 }
 
