@@ -1379,15 +1379,15 @@ static int xcd_groups(int splits, int tiles_m, int tiles_n, int hl) {
 //                   rows 17.2 -> 18.8 us.
 // Of the pairs of a sweep over 1 .. 6144 rows (profiles/projection_tiles.tsv has a part of it) its bf16 choice is on average within 1.8 %
 // (output and down; the six tiles that all three projections share come within 2.4 %) and 1.2 % (Q/K/V) of the best on the three models it was
-// fitted to, and within 1.4 % and 1.2 % on eight others of 512 .. 5120 columns; int8 within 1.0 %.  192 x 224 only pays where it
-// saves a round (7168 x 20480 at 580 rows 209 -> 183 us with 320 x 192): with t below that of 192 x 256 it was taken
-// where the rounds are the same, 7168 x 7168 at 285 rows 54 -> 56 us, 5120 x 5120 at 1600 rows 110 -> 117 us.
+// fitted to, and within 1.4 % and 1.2 % on eight others of 512 .. 5120 columns; int8 within 1.0 %.  (7168 x 20480 at 580
+// rows 209 -> 183 us with 320 x 192; 192 x 224 tiles, tried for the same launches, take the rounds of 192 x 256 ones and 4 .. 6 % longer: 7168 x 7168
+// at 285 rows 54 -> 56 us, 5120 x 5120 at 1600 rows 110 -> 117 us.)
 // K and V alone, all of whose columns take operand pairs, keep constants of their own (kPairs): with those of the other bf16
 // projections it chose too many splits of too wide tiles (2048 x 4096 at 64 rows in 8 splits of 64 x 128 15.7 us, in 16 of
 // 128 x 128 18.6; 2600 rows of 2048 x 7168 132 -> 142 us), over 836 sizes of 11 models 0.3 % more on average, 54 of them by more than 3 %.
 // t = 0: not used.
 // max_splits caps the split (scratch the caller can spare); parked: a finish launch runs anyway.
-constexpr int kProjectionTiles[] = {T64x128, T128x128, T192x128, T128x256, T192x256, T256x256, T256x128w8, T192x224, T320x192};
+constexpr int kProjectionTiles[] = {T64x128, T128x128, T192x128, T128x256, T192x256, T256x256, T256x128w8, T320x192};
 constexpr int kSharedShapes = 6;                           // the leading ones serve the Q/K/V projections too
 constexpr int kFloatOutputShapes = sizeof(kProjectionTiles) / sizeof(kProjectionTiles[0]);
 struct ProjectionModel {
@@ -1398,7 +1398,7 @@ struct ProjectionModel {
   double read;           // MB per us
   double aligned;        // factor of t where the split shares are a multiple of 4 KB apart
 };
-static constexpr ProjectionModel kBf16 = {{0.52, 0.61, 0.73, 0.88, 1.21, 1.38, 0.83, 1.22, 1.40}, 0.18, 9.6, 3.3, 1.5, 0.342, 0.2, 5.95, 1.12};
+static constexpr ProjectionModel kBf16 = {{0.52, 0.61, 0.73, 0.88, 1.21, 1.38, 0.83, 1.40}, 0.18, 9.6, 3.3, 1.5, 0.342, 0.2, 5.95, 1.12};
 static constexpr ProjectionModel kPairs = {{0.58, 0.72, 0.82, 0.97, 1.28, 1.50}, 0, 9.5, 0, 2.3, 0.5, 0, 5.2, 1};
 static constexpr ProjectionModel kInt8 = {{0.72, 0.94, 0, 1.32, 1.53, 1.89}, 0, 9.5, 0, 2.3, 0.5, 0, 5.2, 1};
 constexpr int projection_shapes(int epi) { return epi == EPI_SEG ? kSharedShapes : kFloatOutputShapes; }
@@ -1443,7 +1443,8 @@ static void pick_dma_plan(const ProjectionModel &m, int epi, int M, int N, int h
 //               (bf16 / int8 fit: 7.1 / 6 TB/s both ways) and a second launch finishes them (2.5 / 1 us); bf16: where another
 //               tile does without and the two are within 3 % that one is taken (40960 x 7168 at 430 rows: the call 2 % faster).
 //               Int8 weights, 28672 x 4096 at 580 rows, 256 x 256 tiles shared by three 158 us, 192 x 256 ones 165; 22016 x 4096 at 640
-//               shared by four 129, 128 x 256 ones 140; bf16, 16384 x 3072 at 128 rows, 128 tiles shared by two 34 us, alone 38
+//               shared by four 129, 128 x 256 ones 140; bf16, 16384 x 3072 at 128 rows, 128 tiles shared by two 34 us, alone 38;
+//               1024 x 8192 at 16 rows, 16 tiles shared by four 21 us, alone 59
 //   384 x 128 is for a single row tile: 28672 x 4096 at 350 rows 87 -> 82 us, but at 640 rows 147 -> 159 us
 struct SwigluShape { int tile; float idle, rows; };
 static constexpr SwigluShape kSwigluShapes[2][16] = {
