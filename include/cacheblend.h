@@ -282,9 +282,9 @@ int32_t cb_pick_storage_device(double recompute_delay, const double *load_delays
 /* Instrumentation for benchmarks (no operation of the paper): HIP-event timing per kernel class.
  * Classes: projections' main launches; attention (+ merge of key-range pieces); re-alignment; the K/V
  * projection's finish launch that also computes the deviation; selection + cache update; stand-alone
- * RMSNorm; copies and conversions; the other finish launches (sum of parked sums + residual + norm, SwiGLU
+ * RMSNorm, with which a prefill call's input rows are converted and numbered; copies and other conversions; the other finish launches (sum of parked sums + residual + norm, SwiGLU
  * tail); first-token head; and two PHASES of cb_fuse_prefill / cb_fuse_prefill_pipelined that span many
- * launches: everything up to the end of layer 0 (input conversion, re-alignment, the full first layer), and
+ * launches: everything up to the end of layer 0 (input rows, re-alignment, the full first layer), and
  * the selective layers 1 .. L-1 with the final copy. */
 enum { CB_PROF_GEMM = 0, CB_PROF_ATTN = 1, CB_PROF_REALIGN = 2, CB_PROF_DEV = 3,
        CB_PROF_TOPK = 4, CB_PROF_NORM = 5, CB_PROF_OTHER = 6, CB_PROF_REDUCE = 7,

@@ -226,9 +226,9 @@ __device__ __forceinline__ void lds_epilogue(const float *sC, int pitch, int row
 constexpr int DMA_BK = 64;
 // Stages of the two rings.  The waits count outstanding loads in issue order, so the depth that counts is that of the
 // SHALLOWER ring: once a wavefront waits for its youngest needed activation tile, every weight tile requested before
-// that has to be there too.  Both rings are therefore equally deep wherever the tile leaves room for three stages or more
-// (all 128-column tiles, the 256-column ones up to 128 rows, and every tile over int8 weights); the two tall bf16 tiles
-// keep two activation stages and three weight stages, their k-tiles last as long as a load takes.  With two activation
+// that has to be there too.  Both rings are therefore equally deep wherever 160 KB hold three stages or more of both (bf16: rows and
+// columns of the tile together at most 426; int8 weights: rows and half the columns); larger tiles (bf16 192 x 256, 256 x 224, 320 x 160
+// and up, 384 x 128; int8 384 x 160) keep two activation stages and three weight stages, their k-tiles last as long as a load takes.  With two activation
 // stages everywhere (and 80 KB rings, two workgroups per CU, for the small tiles) a weight tile was never more than one
 // k-tile ahead.  Launch with finish, bf16, before -> after: gate/up 28672 x 4096 at 64 / 128 / 256 rows 57 -> 54, 61 -> 58,
 // 76 -> 67 us, at 640 rows of 57344 x 8192 603 -> 554 us; down 4096 x 14336 at 64 / 128 / 256 rows 36 -> 32, 41 -> 37, 51 -> 46 us;
@@ -1308,9 +1308,10 @@ static constexpr DmaTile kDmaTiles[] = {
     {3, 4, 4, 2}, {3, 5, 4, 2}, {3, 7, 4, 2},                                    // 192 x 128, 160, 224
     {4, 4, 4, 2}, {4, 5, 4, 2}, {4, 7, 4, 2},                                    // 256 x 128, 160, 224
     {5, 5, 4, 2}, {5, 6, 4, 2}, {6, 4, 4, 2}, {6, 5, 4, 2}};                     // 320 x 160, 192; 384 x 128, 160
+// (_4x2: eight wavefronts, where the same size has four)
 constexpr int kNumDmaTiles = sizeof(kDmaTiles) / sizeof(kDmaTiles[0]);
-enum { T64x128, T128x128, T192x128, T128x256, T192x256, T256x256, T128x160, T128x224, T192x128w8, T192x160, T192x224,
-       T256x128w8, T256x160, T256x224, T320x160, T320x192, T384x128, T384x160 };
+enum { T64x128, T128x128, T192x128, T128x256, T192x256, T256x256, T128x160, T128x224, T192x128_4x2, T192x160, T192x224,
+       T256x128_4x2, T256x160, T256x224, T320x160, T320x192, T384x128, T384x160 };
 
 // row blocks that a wavefront walks, summed over the row tiles: all of them but in the last tile
 static long row_block_steps(const DmaTile &t, int M) {
@@ -1387,7 +1388,7 @@ static int xcd_groups(int splits, int tiles_m, int tiles_n, int hl) {
 // 128 x 128 18.6; 2600 rows of 2048 x 7168 132 -> 142 us), over 836 sizes of 11 models 0.3 % more on average, 54 of them by more than 3 %.
 // t = 0: not used.
 // max_splits caps the split (scratch the caller can spare); parked: a finish launch runs anyway.
-constexpr int kProjectionTiles[] = {T64x128, T128x128, T192x128, T128x256, T192x256, T256x256, T256x128w8, T320x192};
+constexpr int kProjectionTiles[] = {T64x128, T128x128, T192x128, T128x256, T192x256, T256x256, T256x128_4x2, T320x192};
 constexpr int kSharedShapes = 6;                           // the leading ones serve the Q/K/V projections too
 constexpr int kFloatOutputShapes = sizeof(kProjectionTiles) / sizeof(kProjectionTiles[0]);
 struct ProjectionModel {
@@ -1449,10 +1450,10 @@ static void pick_dma_plan(const ProjectionModel &m, int epi, int M, int N, int h
 struct SwigluShape { int tile; float idle, rows; };
 static constexpr SwigluShape kSwigluShapes[2][16] = {
     {{T64x128, .45f, .11f}, {T128x128, .51f, .10f}, {T128x160, .53f, .25f}, {T128x224, .65f, .33f}, {T192x128, .65f, .15f},
-     {T192x160, .64f, .33f}, {T192x224, .85f, .44f}, {T192x256, 1.01f, .27f}, {T256x128w8, .61f, .32f}, {T256x160, .73f, .37f},
+     {T192x160, .64f, .33f}, {T192x224, .85f, .44f}, {T192x256, 1.01f, .27f}, {T256x128_4x2, .61f, .32f}, {T256x160, .73f, .37f},
      {T256x224, .98f, .52f}, {T256x256, 1.21f, .32f}, {T320x160, .89f, .46f}, {T320x192, 1.02f, .52f}, {T384x128, .86f, .44f},
      {T384x160, 1.03f, .53f}},
-    {{T64x128, .38f, .14f}, {T128x128, .64f, .19f}, {T128x256, .79f, .24f}, {T192x128w8, .72f, .20f}, {T192x160, .82f, .27f},
+    {{T64x128, .38f, .14f}, {T128x128, .64f, .19f}, {T128x256, .79f, .24f}, {T192x128_4x2, .72f, .20f}, {T192x160, .82f, .27f},
      {T192x256, .97f, .33f}, {T256x160, .95f, .34f}, {T256x256, 1.16f, .42f}, {T320x160, 1.07f, .40f}, {T384x160, 1.18f, .47f}}};
 // whether a plan can ask for a tile
 constexpr bool dma_tile_planned(int epi, int tile, bool w8) {
@@ -1505,6 +1506,9 @@ static void pick_swiglu_plan(int M, int N, int K, size_t scratch_floats, bool w8
 // 32 x 32 with the wavefronts sharing K (544 rows of the 256-wide model occupy 36 CUs with 64 x 64 tiles, 136 with these),
 // 16 x 16 where those leave most CUs idle too: 186 rows x 256 columns, 48 tiles of 32 x 32 against 192, 7.8 -> 4.6 us; with 136 tiles of
 // 32 x 32 both take 7.5 us, with 258 / 272 the small ones, which read four times as much per flop, 8.1 / 9.8 against 6.4 / 7.7 us.
+// The line lies at the same place for any K.  Time on 16 x 16 over time on 32 x 32 tiles at K = 64 / 256 / 1024 / 4096 / 16384, 64 .. 14336
+// columns, 1 .. 1200 rows, on average: up to 63 tiles of 32 x 32 0.95 / 0.80 / 0.63 / 0.48 / 0.32, 64 .. 95 tiles 0.96 / 0.89 / 0.73 / 0.59 / 0.35, 128 .. 255
+// tiles (256 and up) 1.05 / 0.99 / 0.79 / 0.76 with single sizes up to 1.44, beyond 1.4 .. 2.
 static int f32_tile(int epi, int M, int N) {
   auto tiles = [&](int t) { return (long)ceil_div(M, t) * ceil_div(N, epi == EPI_SWIGLU ? t / 2 : t); };
   return tiles(64) >= 512 ? 64 : tiles(32) >= 96 ? 32 : 16;

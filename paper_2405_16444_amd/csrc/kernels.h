@@ -23,13 +23,14 @@ hipError_t launch_realign(int dtype, void *const *k_layers_host, int n_layers,
 hipError_t launch_to_f32(int dtype, const void *x, float *out, size_t n, hipStream_t s);
 // out[r][c] = bf16(q[r][c] * scale[r]) for an int8 matrix [rows, cols], cols % 16 == 0.
 hipError_t launch_dequant_int8(const void *q, const float *scale, void *out, int rows, int cols, hipStream_t s);
-// out[r] = rmsnorm(h[r]) * gain, r < n_rows; out has storage type and row pitch ld_out;
-// lo_off > 0: the rounding remainder of every value is stored lo_off elements after it.
 // The input rows of a call: x (storage type) as float into h, their numbers 0 .. n_rows - 1 into pos (NULL: not wanted), and their
 // RMSNorm into out as launch_rmsnorm stores it.
 hipError_t launch_input_rows(int dtype, const void *x, float *h, int32_t *pos, const void *gain, void *out, int ld_out, int lo_off,
                              int n_rows, int d, float eps, hipStream_t s);
+// p[i] = base + i, i < n.
 hipError_t launch_iota(int32_t *p, int n, int base, hipStream_t s);
+// out[r] = rmsnorm(h[r]) * gain, r < n_rows; out has storage type and row pitch ld_out;
+// lo_off > 0: the rounding remainder of every value is stored lo_off elements after it.
 hipError_t launch_rmsnorm(int dtype, const float *h, const void *gain, void *out, int ld_out, int lo_off,
                           int n_rows, int d, float eps, hipStream_t s);
 // K[pos_out[i]] = kvnew[sel_rows[i]][:kv_dim], V[...] = kvnew[...][kv_dim:], i < m.
