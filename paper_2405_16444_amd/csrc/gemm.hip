@@ -1378,6 +1378,8 @@ static int xcd_groups(int splits, int tiles_m, int tiles_n, int hl) {
 //                   runs anyway (it reads a few of a row's splits at a time; where it does not, an unsplit launch's own epilogue
 //                   costs about as much).  Without that, small launches took twice the splits they gain by: 1024 x 2816 at 720
 //                   rows 17.2 -> 18.8 us.
+//                   Sums beyond 96 MB, next to the operands too much for the memory-side cache, 0.2 us per MB more: the choice is as good
+//                   as without that (1000 .. 6144 rows, mean 0.1 % apart) and parks a quarter less, which is what workspaces are sized for.
 // Of the pairs of a sweep over 1 .. 6144 rows (profiles/projection_tiles.tsv has a part of it) its bf16 choice is on average within 1.8 %
 // (output and down; the six tiles that all three projections share come within 2.4 %) and 1.2 % (Q/K/V) of the best on the three models it was
 // fitted to, and within 1.4 % and 1.2 % on eight others of 512 .. 5120 columns; int8 within 1.0 %.  (7168 x 20480 at 580
@@ -1396,19 +1398,20 @@ struct ProjectionModel {
   double padded;         // share of t that a row tile's blocks without real rows take off
   double fixed, round;   // us; per further round
   double finish, park, split;   // us; us per MB; us per split (of launches with a finish launch anyway)
+  double far;            // us per MB beyond 96 MB of a split launch
   double read;           // MB per us
   double aligned;        // factor of t where the split shares are a multiple of 4 KB apart
 };
-static constexpr ProjectionModel kBf16 = {{0.52, 0.61, 0.73, 0.88, 1.21, 1.38, 0.83, 1.40}, 0.18, 9.6, 3.3, 1.5, 0.342, 0.2, 5.95, 1.12};
-static constexpr ProjectionModel kPairs = {{0.58, 0.72, 0.82, 0.97, 1.28, 1.50}, 0, 9.5, 0, 2.3, 0.5, 0, 5.2, 1};
-static constexpr ProjectionModel kInt8 = {{0.72, 0.94, 0, 1.32, 1.53, 1.89}, 0, 9.5, 0, 2.3, 0.5, 0, 5.2, 1};
+static constexpr ProjectionModel kBf16 = {{0.52, 0.61, 0.73, 0.88, 1.21, 1.38, 0.83, 1.40}, 0.18, 9.6, 3.3, 1.5, 0.342, 0.2, 0.2, 5.95, 1.12};
+static constexpr ProjectionModel kPairs = {{0.58, 0.72, 0.82, 0.97, 1.28, 1.50}, 0, 9.5, 0, 2.3, 0.5, 0, 0, 5.2, 1};
+static constexpr ProjectionModel kInt8 = {{0.72, 0.94, 0, 1.32, 1.53, 1.89}, 0, 9.5, 0, 2.3, 0.5, 0, 0, 5.2, 1};
 constexpr int projection_shapes(int epi) { return epi == EPI_SEG ? kSharedShapes : kFloatOutputShapes; }
 
 // Output columns [0, hl_cols) take (high, low) activation pairs, i.e. twice the tile rows per output row.
 static void pick_dma_plan(const ProjectionModel &m, int epi, int M, int N, int hl_cols, int K, int max_splits, bool parked, bool w8,
                           GemmPlan *pl) {
   const int k_tiles = K / DMA_BK;
-  const double park_us = (double)M * N * 4.0e-6 * m.park + (parked ? m.split : 0.0);  // per split
+  const double mn_mb = (double)M * N * 4.0e-6, park_us = mn_mb * m.park + (parked ? m.split : 0.0);  // per split
   const double read_us = hl_cols ? 0.0 : (double)N * K * (w8 ? 1 : 2) / (m.read * 1e6);
   pl->cost = 1e30;
   for (int i = 0; i < projection_shapes(epi); ++i) {
@@ -1427,7 +1430,7 @@ static void pick_dma_plan(const ProjectionModel &m, int epi, int M, int N, int h
       const int kt = ceil_div(k_tiles, sp);
       const double tk = sp > 1 && groups == 8 && kt % 32 == 0 && !pitch_is_power_of_two(K) ? m.aligned * t_rows : t_rows;
       const double cost = std::max(rounds * tk * kt, read_us) + m.fixed + m.round * (rounds - 1) +
-                          (sp > 1 || parked ? sp * park_us + m.finish : 0.0);
+                          (sp > 1 || parked ? sp * park_us + m.finish : 0.0) + (sp > 1 ? m.far * std::max(0.0, sp * mn_mb - 96.0) : 0.0);
       if (cost < pl->cost - 1e-9) { pl->cost = cost; pl->tile = kProjectionTiles[i]; pl->splits = sp; }
     }
   }

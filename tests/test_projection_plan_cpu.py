@@ -84,3 +84,9 @@ def test_every_tile_of_the_gate_up_projection_has_a_case_of_several_k_tiles():
         asked = {projection_plan(SWIGLU, rows, n, 4096, w8=w8)["tile"]
                  for rows in (1, 40, 100, 150, 200, 270, 330, 390, 420, 520, 580, 700, 1100, 2000) for n in range(512, 30000, 272)}
         assert asked <= {case[0] for case in cases}, asked - {case[0] for case in cases}
+
+
+# (rows, columns, K, most MB of parked sums).  Workspaces are sized for the parked sums; 184, 184 and 551 MB bought nothing over these
+@pytest.mark.parametrize("rows,n,k,most", [(1600, 7168, 20480, 140), (2048, 7168, 20480, 120), (4200, 8192, 28672, 420)])
+def test_large_launches_park_what_pays(rows, n, k, most):
+    assert projection_plan(F32, rows, n, k)["parked"] * 4e-6 <= most
