@@ -117,6 +117,7 @@ struct LayerWs {
 int xn_lo_off(const cb_ctx *c) { return c->m.dtype == CB_BF16 ? c->m.d_model : 0; }
 int xn_pitch(const cb_ctx *c) { return c->m.d_model + xn_lo_off(c); }
 
+constexpr size_t kJointFloats = 16u << 20;       // 64 MB
 // Floats of scratch (parked projection sums, attention key-range pieces) that layer calls with up
 // to max_rows rows can use: the maximum over EVERY row count, because neither the K split of a
 // projection nor the number of key-range pieces is monotone in the row count.  Memoised per ctx, with what is left of it when
@@ -142,7 +143,10 @@ size_t partial_floats_needed(const cb_ctx *c, int max_rows) {
     };
     // the attention KV split borrows the same scratch (the two are never live together)
     const size_t attn = attention_partial_floats_bound(m.dtype, M, m.n_q_heads, m.n_kv_heads, m.head_dim);
-    const size_t need = std::max(projections(true), attn);
+    // room for K|V and Q in one launch, unsplit, as long as that is within what the other uses come to at some hundred rows anyway: whether
+    // Q rides along would otherwise depend on what the gate/up or down plan of that very row count happens to park
+    const size_t joint = m.dtype == CB_BF16 ? (size_t)M * (2 * kv_dim + q_dim) : 0;
+    const size_t need = std::max(std::max(projections(true), attn), joint <= kJointFloats ? joint : 0);
     c->partial_least.push_back(std::max(std::max(projections(false), attn), c->partial_least.back()));
     c->partial_own.push_back(need);
     memo.push_back(std::max(need, memo.back()));
