@@ -130,24 +130,25 @@ size_t partial_floats_needed(const cb_ctx *c, int max_rows) {
   if (memo.empty()) { memo.push_back(0); c->partial_own.push_back(0); c->partial_least.push_back(0); }
   while ((int)memo.size() <= max_rows) {
     const int M = (int)memo.size();
-    auto projections = [&](bool split) {
-      auto floats = [&](int epi, int N, int K, int hl_cols, int force_raw, int half) {
-        return gemm_partial_floats(m.dtype, epi, M, N, K, hl_cols, force_raw, half, m.head_dim, w8, split);
-      };
-      size_t need = floats(EPI_SEG, 2 * kv_dim, d, hl, 1, rh);                   // K|V, checked
-      need = std::max(need, floats(EPI_SEG, 2 * kv_dim, d, hl, 0, rh));          // K|V, every row kept
-      need = std::max(need, floats(EPI_SEG, q_dim, d, 0, 0, rh));                // Q
-      need = std::max(need, floats(EPI_F32, d, q_dim, 0, 0, 0));
-      need = std::max(need, floats(EPI_F32, d, m.d_ff, 0, 0, 0));
-      return std::max(need, floats(EPI_SWIGLU, m.d_ff, d, 0, 0, 0));
+    auto floats = [&](int epi, int N, int K, int hl_cols, int force_raw, int half, bool split = true) {
+      return gemm_partial_floats(m.dtype, epi, M, N, K, hl_cols, force_raw, half, m.head_dim, w8, split);
     };
+    size_t need = floats(EPI_SEG, 2 * kv_dim, d, hl, 1, rh);                   // K|V, checked
+    need = std::max(need, floats(EPI_SEG, 2 * kv_dim, d, hl, 0, rh));          // K|V, every row kept
+    need = std::max(need, floats(EPI_SEG, q_dim, d, 0, 0, rh));                // Q
+    need = std::max(need, floats(EPI_F32, d, q_dim, 0, 0, 0));
+    need = std::max(need, floats(EPI_F32, d, m.d_ff, 0, 0, 0));
+    need = std::max(need, floats(EPI_SWIGLU, m.d_ff, d, 0, 0, 0));
+    // unsplit: the float outputs, K|V with a check, and Q where a float tile is narrower than a head
+    const size_t q_least = m.dtype == CB_F32 ? floats(EPI_SEG, q_dim, d, 0, 0, rh, false) : 0;
+    const size_t least = std::max((size_t)M * std::max(d, 2 * kv_dim), q_least);
     // the attention KV split borrows the same scratch (the two are never live together)
     const size_t attn = attention_partial_floats_bound(m.dtype, M, m.n_q_heads, m.n_kv_heads, m.head_dim);
     // room for K|V and Q in one launch, unsplit, as long as that is within what the other uses come to at some hundred rows anyway: whether
     // Q rides along would otherwise depend on what the gate/up or down plan of that very row count happens to park
     const size_t joint = m.dtype == CB_BF16 ? (size_t)M * (2 * kv_dim + q_dim) : 0;
-    const size_t need = std::max(std::max(projections(true), attn), joint <= kJointFloats ? joint : 0);
-    c->partial_least.push_back(std::max(std::max(projections(false), attn), c->partial_least.back()));
+    need = std::max(std::max(need, attn), joint <= kJointFloats ? joint : 0);
+    c->partial_least.push_back(std::max(std::max(least, attn), c->partial_least.back()));
     c->partial_own.push_back(need);
     memo.push_back(std::max(need, memo.back()));
   }

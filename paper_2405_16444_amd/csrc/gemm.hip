@@ -1419,18 +1419,20 @@ static void pick_dma_plan(const ProjectionModel &m, int epi, int M, int N, int h
     const int bm = t.bm(), bn = t.bn();
     if (m.t[i] == 0.0 || (bm == 64 && M > 64)) continue;
     if (hl_cols < N && hl_cols % bn != 0) continue;        // a tile's columns are of one kind
-    const int tiles_m = ceil_div(M, bm);
+    const int tiles_m = ceil_div(M, bm), tiles_n = ceil_div(N - hl_cols, bn), hl_n = ceil_div(hl_cols, bn);
+    const long hl_m = ceil_div(2 * M, bm);
     const double t_rows = m.t[i] * (1.0 - m.padded + m.padded * row_block_steps(t, M) / ((double)tiles_m * t.RB));
     for (int sp = 1; sp <= 16 && sp <= max_splits; ++sp) {
       if (sp > 1 && k_tiles / sp < 4) break;
-      const int groups = xcd_groups(sp, tiles_m, ceil_div(N - hl_cols, bn), hl_cols);
-      const long per_xcd = ((long)ceil_div(2 * M, bm) * ceil_div(ceil_div(hl_cols, bn), groups) +
-                            (long)tiles_m * ceil_div(ceil_div(N - hl_cols, bn), groups)) * (groups < 8 ? 1 : sp);
-      const long rounds = (per_xcd + 31) / 32;
       const int kt = ceil_div(k_tiles, sp);
+      const double outside = m.fixed + (sp > 1 || parked ? sp * park_us + m.finish : 0.0) + (sp > 1 ? m.far * std::max(0.0, sp * mn_mb - 96.0) : 0.0);
+      if (outside >= pl->cost && sp > 1) break;            // grows with the splits
+      if (outside + std::max(t_rows * kt, read_us) >= pl->cost) continue;      // one round
+      const int groups = xcd_groups(sp, tiles_m, tiles_n, hl_cols);
+      const long per_xcd = (hl_m * ceil_div(hl_n, groups) + (long)tiles_m * ceil_div(tiles_n, groups)) * (groups < 8 ? 1 : sp);
+      const long rounds = (per_xcd + 31) / 32;
       const double tk = sp > 1 && groups == 8 && kt % 32 == 0 && !pitch_is_power_of_two(K) ? m.aligned * t_rows : t_rows;
-      const double cost = std::max(rounds * tk * kt, read_us) + m.fixed + m.round * (rounds - 1) +
-                          (sp > 1 || parked ? sp * park_us + m.finish : 0.0) + (sp > 1 ? m.far * std::max(0.0, sp * mn_mb - 96.0) : 0.0);
+      const double cost = std::max(rounds * tk * kt, read_us) + m.round * (rounds - 1) + outside;
       if (cost < pl->cost - 1e-9) { pl->cost = cost; pl->tile = kProjectionTiles[i]; pl->splits = sp; }
     }
   }
