@@ -146,7 +146,7 @@ size_t partial_floats_needed(const cb_ctx *c, int max_rows) {
     const size_t attn = attention_partial_floats_bound(m.dtype, M, m.n_q_heads, m.n_kv_heads, m.head_dim);
     // room for K|V and Q in one launch, unsplit, as long as that is within what the other uses come to at some hundred rows anyway: whether
     // Q rides along would otherwise depend on what the gate/up or down plan of that very row count happens to park
-    const size_t joint = m.dtype == CB_BF16 ? (size_t)M * (2 * kv_dim + q_dim) : 0;
+    const size_t joint = m.dtype == CB_BF16 && d % 64 == 0 ? (size_t)M * (2 * kv_dim + q_dim) : 0;
     need = std::max(std::max(need, attn), joint <= kJointFloats ? joint : 0);
     c->partial_least.push_back(std::max(std::max(least, attn), c->partial_least.back()));
     c->partial_own.push_back(need);
